@@ -120,11 +120,12 @@ typedef struct spd_tuning {
     uint32_t bin_mode;         /* binned scan layout: 0 = per-tile regions (one pass over the pairs);
                                   1 = bucket-major (an exact counting pass first, then contiguous
                                   per-bucket items that the apply phase streams);
-                                  2 = per-(chunk of 128 tiles, bucket) regions of fixed capacity
-                                  (one pass over the pairs; words past a region's capacity are
-                                  recorded from a spill list after the apply phase) */
+                                  2 = per-(chunk of tiles, bucket) regions of fixed capacity (one
+                                  pass over the pairs; a tile's words past a region's capacity are
+                                  kept apart and listed for the bucket's apply) */
     uint32_t region_words;     /* bin_mode 2: 64-bit words per region (0: derived from the expected
-                                  load of a bucket with a wide margin; small values force spills) */
+                                  load of a bucket with a wide margin; small values force words past
+                                  the regions) */
 } spd_tuning;
 
 typedef struct spd_stats {
@@ -148,7 +149,7 @@ typedef struct spd_stats {
 #define SPD_K_FILL 7       /* clears (window reset, counters) */
 #define SPD_K_COUNT 8      /* exact-count layout (bin_mode 1): per-tile bucket counts */
 #define SPD_K_OFFSETS 9    /* exact-count layout (bin_mode 1): per-tile segment offsets */
-#define SPD_K_SPILL 10     /* region layout: words past a region's capacity */
+#define SPD_K_SPILL 10     /* no longer launched: the apply phase reads words past a region's capacity */
 #define SPD_K_KINDS 11
 
 typedef struct spd_profile {

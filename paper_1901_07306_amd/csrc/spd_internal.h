@@ -175,13 +175,14 @@ struct ClearList {
 // descriptors (any number), sorted by first_tile.
 hipError_t launch_count(const Consts &c, const BinGeometry &g, const BatchDesc *batches_dev, uint32_t n_batches,
                         uint32_t n_tiles, uint32_t *cnt, const ClearList &clear, hipStream_t s);
-// Tiles of a bucket-major launch, per slot [lo, hi), scanned in chunks of kChunk tiles that never
+// Tiles of a bucket-major or region launch, per slot [lo, hi), in chunks of `tiles` tiles that never
 // span two slots: chunks cbase[s] .. cbase[s + 1] - 1 belong to slot s.
-constexpr uint32_t kChunk = 128;
+constexpr uint32_t kChunk = 128;   // tiles of a bucket-major chunk
 struct ChunkTable {
     uint32_t lo[kMaxGroup], hi[kMaxGroup];
     uint32_t cbase[kMaxGroup + 1];
     uint32_t n;
+    uint32_t tiles;
 };
 // cnt [tiles][nb] -> loc [tiles][nb] (offset inside the tile's chunk), cstart [chunks][nb] (chunk
 // start, absolute), base [n * nb + 1] (start of each (slot, bucket), then the total).
@@ -192,10 +193,24 @@ hipError_t launch_place(const Consts &c, const BinGeometry &g, const BatchDesc *
                         const uint32_t *cstart, const ChunkTable &ct, const SlotPtrs *slots, hipStream_t s);
 // Region layout of the binned scan (one pass over the pairs): every (chunk, bucket) has a region of
 // fixed capacity in `items`; a tile takes room for its padded segment of a bucket with one atomic
-// on that region's word count, and words past a region's capacity go to the spill list, which is
-// ORed into the sketches after the apply phase.  A slot's regions start at slot_base[s]: its full
-// chunks (kChunk tiles) first, chunk_words each (the LDCA buckets, capw_l words each, then the SEAV
-// buckets, capw_s words each), then its partial last chunk, if any, sized by its own tile count.
+// on that region's word count.  The words of a segment past its region's capacity go to the tile's
+// own part of the spill array, and the segment is listed under its (slot, bucket); the apply phase
+// reads a bucket's listed segments after its regions.  A slot's regions start at slot_base[s]: its
+// full chunks (ct.tiles tiles) first, chunk_words each (the LDCA buckets, capw_l words each, then the
+// SEAV buckets, capw_s words each), then its partial last chunk, if any, sized by its own tile count.
+struct SpillSeg {
+    uint32_t start;        // first word in the spill array
+    uint32_t words;
+};
+// A tile with more sampled pairs than it could stage: its sampled pairs are read again by the apply
+// phase of the slot's SEAV buckets.
+struct ListedTile {
+    const uint32_t *pairs; // the tile's first pair
+    uint32_t n;            // pairs of the tile
+    uint32_t slot;
+    uint32_t swap;
+    uint32_t pad[3];
+};
 struct RegionArgs {
     uint64_t slot_base[kMaxGroup];
     uint32_t full[kMaxGroup];                      // full chunks of each slot
@@ -203,17 +218,15 @@ struct RegionArgs {
     uint64_t *items;
     uint32_t *cur;         // [chunks][nb] words taken in each region: zero before the launch, and
                            // zeroed again by the apply phase once read
-    uint32_t *spill_n;     // overflow words of this launch (zero before the launch)
-    uint32_t *spill_next;  // the next launch's count: zeroed by this launch's spill phase
-    uint64_t *spill_w;     // [spill_cap] overflow words
-    uint32_t *spill_tag;   // [spill_cap] (slot << 16) | bucket of each overflow word
-    uint32_t *ovf_n;       // tiles listed by this launch (zero before the launch)
-    uint32_t *ovf_next;    // the next launch's count: zeroed by this launch's spill phase
-    uint32_t *ovf;         // [ovf_cap] tiles with more sampled pairs than they could stage
+    uint32_t *seg_n;       // [slots][nb] listed segments: zero before the launch, zeroed like cur
+    SpillSeg *seg;         // per slot [nb][tiles of the slot]: at most one segment per tile and bucket
+    uint64_t *spill_w;     // [tiles][cap / 3]: word w of a tile's stage, when it is past its region
+    uint32_t *tile_n;      // tiles listed by this launch (zero before the launch)
+    uint32_t *tile_next;   // the next launch's count: zeroed by this launch's apply phase
+    ListedTile *tile;      // [tiles]
     uint64_t chunk_words;  // nb_ldca * capw_l + (nb - nb_ldca) * capw_s
     uint32_t capw_l, capw_s;
-    uint32_t spill_cap;    // at least the launch's padded words: the spill list cannot overflow
-    uint32_t ovf_cap;      // the launch's tiles: the tile list cannot overflow
+    uint32_t tile_words;   // cap / 3: words of one tile's stage
 };
 hipError_t launch_clear(const ClearList &clear, hipStream_t s);
 // Region of chunk cc (counted inside slot si) for bucket b: its first word counted from the chunk's
@@ -242,16 +255,13 @@ hipError_t launch_apply(const BinGeometry &g, const ApplySlot *slots, uint32_t n
                         const uint32_t *metaT, uint32_t n_tiles, uint32_t block, uint32_t unroll, hipStream_t s);
 hipError_t launch_apply_bm(const BinGeometry &g, const ApplySlot *slots, uint32_t n_slots, const uint32_t *items,
                            const uint32_t *base, uint32_t block, uint32_t unroll, hipStream_t s);
-hipError_t launch_apply_rg(const BinGeometry &g, const ApplySlot *slots, uint32_t n_slots, const ChunkTable &ct,
-                           const RegionArgs &ra, uint32_t block, uint32_t unroll, hipStream_t s, KTiming kt = {});
+hipError_t launch_apply_rg(const Consts &c, const BinGeometry &g, const ApplySlot *slots, uint32_t n_slots,
+                           const ChunkTable &ct, const RegionArgs &ra, uint32_t block, uint32_t unroll, hipStream_t s, KTiming kt = {});
 // The apply phase with the router OR merge fused in: the global sketch (its LDCA and SEAV) :=
 // OR of the launch's slots; 1024-lane workgroups, buckets of at most 2^20 bits.
-hipError_t launch_apply_rg_merge(const BinGeometry &g, const ApplySlot *slots, uint32_t n_slots, const ChunkTable &ct,
-                                 const RegionArgs &ra, const ApplySlot &global, uint32_t unroll, hipStream_t s,
-                                 KTiming kt = {});
-// The spill pass of a region launch over the batches bl (which the listed tiles are read from again).
-hipError_t launch_spill(const Consts &c, const BinGeometry &g, const ApplySlot *slots, uint32_t n_slots,
-                        const RegionArgs &ra, const BatchList &bl, hipStream_t s, const ApplySlot *global = nullptr);
+hipError_t launch_apply_rg_merge(const Consts &c, const BinGeometry &g, const ApplySlot *slots, uint32_t n_slots,
+                                 const ChunkTable &ct, const RegionArgs &ra, const ApplySlot &global, uint32_t unroll,
+                                 hipStream_t s, KTiming kt = {});
 hipError_t launch_or_merge(uint32_t *dst, const uint32_t *const *src, uint32_t n_src, uint64_t n_words, hipStream_t s);
 hipError_t launch_max_merge_u16(uint16_t *dst, const uint16_t *const *src, uint32_t n_src, uint64_t n_elems,
                                 hipStream_t s);

@@ -909,8 +909,11 @@ hipError_t launch_count(const Consts &c, const BinGeometry &g, const BatchDesc *
 // bit addresses, so a stage word's first item names its bucket at write-out, and the last two
 // places of each segment are first filled with an address of another bucket: those still holding
 // it after placement are the padding.
+//
+// At most 80 scalar registers: with more, a SIMD holds fewer than eight wavefronts and the compute
+// unit one workgroup of 1024 instead of two (64 Mi pairs: 320 instead of 229 us).
 template <int LR, int PPT, int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_region(Consts c, BinGeometry g, BatchList bl, SlotTable st, ChunkTable ct,
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_num_sgpr(80))) void k_region(Consts c, BinGeometry g, BatchList bl, SlotTable st, ChunkTable ct,
                                                   RegionArgs ra) {
     extern __shared__ uint32_t lds[];
     __shared__ RowLds rl;   // read after the first barrier
@@ -926,7 +929,7 @@ __global__ __launch_bounds__(BLOCK) void k_region(Consts c, BinGeometry g, Batch
     const BatchDesc B = batch_of(bl, tile);
     const SlotPtrs S = st.s[B.slot];
     const uint64_t p0 = (uint64_t)(tile - B.first_tile) * (uint64_t)(PPT * BLOCK);
-    const uint32_t cc = (tile - ct.lo[B.slot]) / kChunk, chunk = ct.cbase[B.slot] + cc;
+    const uint32_t cc = (tile - ct.lo[B.slot]) / ct.tiles, chunk = ct.cbase[B.slot] + cc;
     const uint32_t seav_base = (uint32_t)c.ldca_bits;   // SEAV bits follow the LDCA bits
 
     for (uint32_t i = tid; i < 2 * (nb + 1); i += BLOCK) cl[i] = 0;
@@ -947,13 +950,17 @@ __global__ __launch_bounds__(BLOCK) void k_region(Consts c, BinGeometry g, Batch
     else
         bin_hash_pairs<LR, PPT, BLOCK, false, true>(c, rl, g, S, pr, p0, B.n, cl, samp, misc, bits, rk);
     __syncthreads();
-    // a tile with more sampled pairs than it can stage stages none: it is listed, and the spill
-    // pass records all of its sampled pairs once the apply phase has written the buckets
+    // a tile with more sampled pairs than it can stage stages none: it is listed, and the apply
+    // phase of the SEAV buckets reads all of its sampled pairs again
     uint32_t ns = misc[0];
     if (ns > g.scap) {
         if (tid == 0) {
-            const uint32_t k = atomicAdd(ra.ovf_n, 1u);
-            if (k < ra.ovf_cap) ra.ovf[k] = tile;
+            const uint64_t left = B.n - p0;
+            ListedTile &t = ra.tile[atomicAdd(ra.tile_n, 1u)];   // (one entry per tile of the launch)
+            t.pairs = B.pairs + 2 * p0;
+            t.n = left < (uint64_t)(PPT * BLOCK) ? (uint32_t)left : (uint32_t)(PPT * BLOCK);
+            t.slot = B.slot;
+            t.swap = B.swap;
         }
         ns = 0;
     }
@@ -984,6 +991,8 @@ __global__ __launch_bounds__(BLOCK) void k_region(Consts c, BinGeometry g, Batch
             stage[pe - 2] = stage[pe - 1] = (b ^ 1u) << g.S;
         }
     }
+    uint32_t *past = misc + 1;   // (the scan scratch is free) set when a segment does not fit its region
+    if (tid == 0) *past = 0u;
     __syncthreads();
     if (full) {   // every lane's items are valid
 #pragma unroll
@@ -1002,45 +1011,62 @@ __global__ __launch_bounds__(BLOCK) void k_region(Consts c, BinGeometry g, Batch
         stage[atomicAdd(&cs[bit >> g.S], 1u)] = bit;
     }
     __syncthreads();
-    // pad every segment with its last item (the room of a thread's buckets past its first two is
-    // taken here, its offset kept in cs)
+    // Pad every segment with its last item (the room of a thread's buckets past its first two is
+    // taken here).  cs[b] becomes the distance from a stage word of bucket b to its place among the
+    // chunk's regions; a segment that does not fit its region is listed under its bucket, its
+    // remaining words go to the same places of the tile's part of the spill array.
     for (uint32_t b = tid, m = 0; b < nb; b += BLOCK, ++m) {
         const uint32_t s0 = cl[b], pe = cl[b + 1];
         if (pe > s0) {
             if ((stage[pe - 2] >> g.S) != b) stage[pe - 2] = stage[pe - 3];
             if ((stage[pe - 1] >> g.S) != b) stage[pe - 1] = stage[pe - 2];
-            if (m >= 2) cs[b] = atomicAdd(rcur + b, (pe - s0) / 3);
+            const uint32_t w0 = s0 / 3, n = (pe - s0) / 3;
+            const uint32_t o = m == 0 ? o_pre0 : m == 1 ? o_pre1 : atomicAdd(rcur + b, n);
+            uint32_t capw;
+            const uint32_t in = region_in(ra, g.nb_ldca, B.slot, cc, b, &capw);
+            cs[b] = in + o - w0;
+            if (o + n > capw) {
+                const uint32_t fit = o < capw ? capw - o : 0u;
+                const uint32_t lo = ct.lo[B.slot], nt = ct.hi[B.slot] - lo;
+                const uint32_t k = atomicAdd(ra.seg_n + B.slot * nb + b, 1u);   // below nt
+                ra.seg[(uint64_t)lo * nb + (uint64_t)b * nt + k] = SpillSeg{tile * ra.tile_words + w0 + fit, n - fit};
+                *past = 1u;
+            }
         }
-    }
-    __syncthreads();
-    // per bucket, in stage words: cl[b] = the first word past the region's room, cs[b] = the
-    // distance from a word's place in the stage to its place among the chunk's regions
-    for (uint32_t b = tid, m = 0; b < nb; b += BLOCK, ++m) {
-        const uint32_t w0 = cl[b] / 3, o = m == 0 ? o_pre0 : m == 1 ? o_pre1 : cs[b];
-        uint32_t capw;
-        const uint32_t in = region_in(ra, g.nb_ldca, B.slot, cc, b, &capw);
-        cl[b] = w0 + (o < capw ? capw - o : 0u);
-        cs[b] = in + o - w0;
     }
     __syncthreads();
     // one thread per stage word: three 21-bit offsets per 64-bit word
     const uint32_t smask = (1u << g.S) - 1u;
     const uint32_t nwords = cl[nb] / 3;
     uint64_t *dst = ra.items + chunk_at(ra, B.slot, cc);
-    for (uint32_t w = tid; w < nwords; w += BLOCK) {
+    auto word = [&](uint32_t w, uint32_t &b) {
         const uint32_t s0 = stage[3 * w], s1 = stage[3 * w + 1], s2 = stage[3 * w + 2];
-        const uint32_t b = s0 >> g.S;
+        b = s0 >> g.S;
         const uint32_t lo = (s0 & smask) | (s1 << 21), hi = ((s1 & smask) >> 11) | ((s2 & smask) << 10);
-        const uint64_t v = (uint64_t)lo | ((uint64_t)hi << 32);
-        if (w < cl[b]) {
+        return (uint64_t)lo | ((uint64_t)hi << 32);
+    };
+    if (!*past) {
+        for (uint32_t w = tid; w < nwords; w += BLOCK) {
+            uint32_t b;
+            const uint64_t v = word(w, b);
             dst[w + cs[b]] = v;
-        } else {
-            const uint32_t k = atomicAdd(ra.spill_n, 1u);
-            if (k < ra.spill_cap) {
-                ra.spill_w[k] = v;
-                ra.spill_tag[k] = (B.slot << 16) | b;
-            }
         }
+        return;
+    }
+    // cl[b] becomes the first stage word past the region's room
+    for (uint32_t b = tid; b < nb; b += BLOCK) {
+        const uint32_t w0 = cl[b] / 3;
+        uint32_t capw;
+        const uint32_t o = cs[b] + w0 - region_in(ra, g.nb_ldca, B.slot, cc, b, &capw);
+        cl[b] = w0 + (o < capw ? capw - o : 0u);
+    }
+    __syncthreads();
+    uint64_t *spill = ra.spill_w + (uint64_t)tile * ra.tile_words;
+    for (uint32_t w = tid; w < nwords; w += BLOCK) {
+        uint32_t b;
+        const uint64_t v = word(w, b);
+        if (w < cl[b]) dst[w + cs[b]] = v;
+        else spill[w] = v;
     }
 }
 
@@ -1102,11 +1128,99 @@ hipError_t launch_clear(const ClearList &clear, hipStream_t s) {
 // Apply phase of the region layout: one workgroup per (slot, bucket) ORs the used part of the
 // bucket's region in each of the slot's chunks into an LDS bitmap.  Work is split into pieces of
 // 64 * U words (one per wavefront at a time); a piece past its region's fill is skipped.
-// Bucket b of slot si: loaded into the LDS bitmap bm (zero for a fresh slot: nothing but the
-// spill pass, which runs after this, writes a slot's memory during a launch), the
-// filled part of the bucket's region in every chunk of the slot applied with LDS atomicOr, the
-// region counters read zeroed for the next launch, the bitmap stored back.  Ends with bm complete
-// and visible to the whole workgroup.
+__device__ __forceinline__ void apply_word(uint32_t *bm, uint64_t v) {
+#pragma unroll
+    for (uint32_t f = 0; f < 3; ++f) {
+        const uint32_t it = (uint32_t)(v >> (21 * f)) & 0x1FFFFFu;
+        atomicOr(&bm[it >> 5], 1u << (it & 31u));
+    }
+}
+
+// What does not fit a region is ordered by bucket too, and applied in LDS like the rest.  It was once
+// appended word by word to one list (one counter: its atomics are serialized device-wide) and recorded
+// with global atomics by a kernel of its own: 8 Mi pairs, half of them from four hosts, took 606 us of
+// binning + 1930 us of that kernel, now 47 + 105 us of binning and apply; 5 Mi pairs with 60 planted
+// hosts 84 + 36 us, now 31 us; and without such words the kernel's launch is saved (4 us).
+//
+// The listed segments of one (slot, bucket): each wavefront takes 64 at a time (one descriptor per
+// lane) and reads the first 64 words of eight segments before it waits, since most segments are
+// short; the rest of a long one follows in pieces of 64 * U words.
+template <int BLOCK, int U>
+__device__ __forceinline__ void apply_segments(const SpillSeg *__restrict__ seg, uint32_t n,
+                                               const uint64_t *__restrict__ spill_w, uint32_t wid, uint32_t lane,
+                                               uint32_t *bm) {
+    constexpr uint32_t NW = BLOCK / 64, G = 8;
+    // few segments: fewer of them per wavefront, so that every wavefront has some
+    const uint32_t per = n >= 64 * NW ? 64u : (n + NW - 1) / NW;
+    for (uint32_t d0 = wid * per; d0 < n; d0 += NW * per) {
+        const uint32_t m = n - d0 < per ? n - d0 : per;
+        const SpillSeg mine = seg[d0 + (lane < m ? lane : m - 1)];
+        for (uint32_t j0 = 0; j0 < m; j0 += G) {
+            uint64_t v[G];
+            uint32_t len[G], st[G];
+#pragma unroll
+            for (uint32_t j = 0; j < G; ++j) {
+                const uint32_t k = j0 + j < m ? j0 + j : m - 1;   // (a repeated segment is masked below)
+                st[j] = __builtin_amdgcn_readlane(mine.start, k);
+                len[j] = __builtin_amdgcn_readlane(mine.words, k);
+                v[j] = spill_w[(uint64_t)st[j] + (lane < len[j] ? lane : len[j] - 1)];
+            }
+#pragma unroll
+            for (uint32_t j = 0; j < G; ++j)
+                if (j0 + j < m && lane < len[j]) apply_word(bm, v[j]);
+            for (uint32_t j = 0; j < G && j0 + j < m; ++j) {
+                const uint32_t s0 = __builtin_amdgcn_readlane(mine.start, j0 + j);
+                const uint32_t l0 = __builtin_amdgcn_readlane(mine.words, j0 + j);
+                for (uint32_t w0 = 64; w0 < l0; w0 += 64 * U) {
+                    uint64_t x[U];
+#pragma unroll
+                    for (uint32_t k = 0; k < U; ++k) {
+                        const uint32_t w = w0 + k * 64 + lane;
+                        x[k] = spill_w[(uint64_t)s0 + (w < l0 ? w : l0 - 1)];
+                    }
+#pragma unroll
+                    for (uint32_t k = 0; k < U; ++k)
+                        if (w0 + k * 64 + lane < l0) apply_word(bm, x[k]);
+                }
+            }
+        }
+    }
+}
+
+// The sampled pairs of the slot's listed tiles whose SEAV bits lie in this bucket (first_bit: the
+// bucket's first bit of the SEAV).  Rare, and wide: the method constants are read from the kernel
+// arguments (they are the first one) behind an opaque pointer, so that nothing of this is loaded on
+// the path of a launch that lists no tile.
+typedef __attribute__((address_space(4))) const Consts ArgConsts;
+template <int BLOCK>
+__device__ __forceinline__ void apply_listed(const RegionArgs &ra, uint32_t n, uint32_t si, uint32_t S, uint64_t first_bit,
+                                             uint32_t *bm) {
+    auto args = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    ArgConsts &c = *(ArgConsts *)args;
+    for (uint32_t t = 0; t < n; ++t) {
+        const ListedTile T = ra.tile[t];
+        if (T.slot != si) continue;
+        const u32x2 *pairs = reinterpret_cast<const u32x2 *>(T.pairs);
+        for (uint32_t i = threadIdx.x; i < T.n; i += BLOCK) {
+            const u32x2 pr = load_pair(pairs, i, T.swap);
+            if (mas_hi(pr.y, c.mul[0], c.add[0]) & c.tau_mask) continue;
+            const uint32_t b = mas_hi(pr.y, c.mul[1], c.add[1]) >> 29;
+            const uint32_t rp = pr.x & c.rmask, lp = (uint32_t)((uint64_t)pr.x >> c.r);
+            for (uint32_t r = 0; r < c.sr; ++r) {
+                const uint32_t byte = rp * c.sea_bytes + c.row_off[r] + row_index(lp, c.isb[r], c.ibn[r], c.L);
+                const uint64_t bit = (uint64_t)byte * 8u + b - first_bit;   // (wraps below the bucket)
+                if (bit >> S) continue;
+                atomicOr(&bm[bit >> 5], 1u << (bit & 31u));
+            }
+        }
+    }
+}
+
+// Bucket b of slot si: loaded into the LDS bitmap bm (zero for a fresh slot: nothing else writes a
+// slot's memory during a launch), the filled part of the bucket's region in every chunk of the slot,
+// then its listed segments and tiles, applied with LDS atomicOr, the counters read zeroed for the
+// next launch, the bitmap stored back.  Ends with bm complete and visible to the whole workgroup.
 template <int BLOCK, int U>
 __device__ __forceinline__ void apply_bucket(const BinGeometry &g, const ApplySlot &A, uint32_t si, uint32_t b,
                                              const ChunkTable &ct, const RegionArgs &ra, uint32_t *bm) {
@@ -1120,38 +1234,42 @@ __device__ __forceinline__ void apply_bucket(const BinGeometry &g, const ApplySl
     } else {
         for (uint32_t w = tid; w < words; w += BLOCK) bm[w] = dst[w];
     }
+    const uint32_t n_seg = ra.seg_n[si * g.nb + b], n_tile = b < g.nb_ldca ? 0u : *ra.tile_n;
     __syncthreads();
     const uint32_t c0 = ct.cbase[si], nch = ct.cbase[si + 1] - c0;
-    uint32_t capw;
-    (void)region_in(ra, g.nb_ldca, si, 0, b, &capw);   // the largest capacity of the slot's chunks
-    const uint32_t ppc = (capw + PIECE - 1) / PIECE;
-    for (uint32_t u = wid; u < nch * ppc; u += NW) {
-        const uint32_t cc = u / ppc, w0 = (u - cc * ppc) * PIECE;
+    // pieces of PIECE words, dealt to the wavefronts in turn over all chunks
+    uint32_t p0 = wid;   // this wavefront's next piece, counted from the chunk's first
+    for (uint32_t cc = 0; cc < nch; ++cc) {
         uint32_t cap_c;
         const uint64_t at = chunk_at(ra, si, cc) + region_in(ra, g.nb_ldca, si, cc, b, &cap_c);
         uint32_t len = ra.cur[(uint64_t)(c0 + cc) * g.nb + b];
         len = len < cap_c ? len : cap_c;
-        if (w0 >= len) continue;
+        const uint32_t np = (len + PIECE - 1) / PIECE;
         const uint64_t *src = ra.items + at;
-        uint64_t v[U];
+        for (; p0 < np; p0 += NW) {
+            const uint32_t w0 = p0 * PIECE;
+            uint64_t v[U];
 #pragma unroll
-        for (uint32_t k = 0; k < U; ++k) {
-            const uint32_t ww = w0 + k * 64 + lane;
-            v[k] = __builtin_nontemporal_load(src + (ww < len ? ww : len - 1));   // unconditional loads
-        }
-#pragma unroll
-        for (uint32_t k = 0; k < U; ++k) {
-            if (w0 + k * 64 + lane >= len) continue;
-#pragma unroll
-            for (uint32_t f = 0; f < 3; ++f) {
-                const uint32_t it = (uint32_t)(v[k] >> (21 * f)) & 0x1FFFFFu;
-                atomicOr(&bm[it >> 5], 1u << (it & 31u));
+            for (uint32_t k = 0; k < U; ++k) {
+                const uint32_t ww = w0 + k * 64 + lane;
+                v[k] = __builtin_nontemporal_load(src + (ww < len ? ww : len - 1));   // unconditional loads
             }
+#pragma unroll
+            for (uint32_t k = 0; k < U; ++k)
+                if (w0 + k * 64 + lane < len) apply_word(bm, v[k]);
         }
+        p0 -= np;
     }
+    if (n_seg) {
+        const uint32_t lo = ct.lo[si], nt = ct.hi[si] - lo;
+        apply_segments<BLOCK, U>(ra.seg + (uint64_t)lo * g.nb + (uint64_t)b * nt, n_seg, ra.spill_w, wid, lane, bm);
+    }
+    if (n_tile) apply_listed<BLOCK>(ra, n_tile, si, g.S, (uint64_t)(b - g.nb_ldca) << g.S, bm);
     __syncthreads();
-    // the region counters of this (slot, bucket) start the next launch at zero
+    // the counters of this (slot, bucket) start the next launch at zero, and so does its tile count
     for (uint32_t cc = tid; cc < nch; cc += BLOCK) ra.cur[(uint64_t)(c0 + cc) * g.nb + b] = 0u;
+    if (tid == 0) ra.seg_n[si * g.nb + b] = 0u;
+    if (tid == 0 && b == 0 && si == 0) *ra.tile_next = 0u;
     const uint32_t words4 = words / 4;
     if (words4) {
         for (uint32_t w = tid; w < words4; w += BLOCK)
@@ -1161,9 +1279,9 @@ __device__ __forceinline__ void apply_bucket(const BinGeometry &g, const ApplySl
     }
 }
 
-// One workgroup per (slot, bucket).
+// One workgroup per (slot, bucket).  (The first argument is read by apply_listed.)
 template <int BLOCK, int U>
-__global__ __launch_bounds__(BLOCK) void k_apply_rg(BinGeometry g, ApplyTable at, ChunkTable ct, RegionArgs ra) {
+__global__ __launch_bounds__(BLOCK) void k_apply_rg(Consts, BinGeometry g, ApplyTable at, ChunkTable ct, RegionArgs ra) {
     extern __shared__ uint32_t bm[];
     const uint32_t blk = blockIdx.x;
     const uint32_t si = blk / g.nb, b = blk % g.nb;
@@ -1175,8 +1293,8 @@ __global__ __launch_bounds__(BLOCK) void k_apply_rg(BinGeometry g, ApplyTable at
 // 32 words per lane of 1024), then writes it to the global sketch's bucket.  The global's previous
 // content is replaced.
 template <int U>
-__global__ __launch_bounds__(1024) void k_apply_rg_merge(BinGeometry g, ApplyTable at, uint32_t n_slots, ChunkTable ct,
-                                                         RegionArgs ra, ApplySlot gs) {
+__global__ __launch_bounds__(1024) void k_apply_rg_merge(Consts, BinGeometry g, ApplyTable at, uint32_t n_slots,
+                                                         ChunkTable ct, RegionArgs ra, ApplySlot gs) {
     extern __shared__ uint32_t bm[];
     constexpr uint32_t BLOCK = 1024, PER = 32;   // words per lane of a 2^20-bit bucket
     const uint32_t words = 1u << (g.S - 5);
@@ -1198,17 +1316,17 @@ __global__ __launch_bounds__(1024) void k_apply_rg_merge(BinGeometry g, ApplyTab
 }
 
 template <int U>
-static void launch_apply_rg_u(const BinGeometry &g, const ApplyTable &at, const ChunkTable &ct, const RegionArgs &ra,
+static void launch_apply_rg_u(const Consts &c, const BinGeometry &g, const ApplyTable &at, const ChunkTable &ct, const RegionArgs &ra,
                               dim3 grid, uint32_t lds, uint32_t block, hipStream_t s, KTiming kt) {
     if (block == 1024)
-        hipExtLaunchKernelGGL((k_apply_rg<1024, U>), grid, dim3(1024), lds, s, kt.start, kt.stop, 0, g, at, ct, ra);
+        hipExtLaunchKernelGGL((k_apply_rg<1024, U>), grid, dim3(1024), lds, s, kt.start, kt.stop, 0, c, g, at, ct, ra);
     else if (block == 512)
-        hipExtLaunchKernelGGL((k_apply_rg<512, U>), grid, dim3(512), lds, s, kt.start, kt.stop, 0, g, at, ct, ra);
-    else hipExtLaunchKernelGGL((k_apply_rg<256, U>), grid, dim3(256), lds, s, kt.start, kt.stop, 0, g, at, ct, ra);
+        hipExtLaunchKernelGGL((k_apply_rg<512, U>), grid, dim3(512), lds, s, kt.start, kt.stop, 0, c, g, at, ct, ra);
+    else hipExtLaunchKernelGGL((k_apply_rg<256, U>), grid, dim3(256), lds, s, kt.start, kt.stop, 0, c, g, at, ct, ra);
 }
 
-hipError_t launch_apply_rg(const BinGeometry &g, const ApplySlot *slots, uint32_t n_slots, const ChunkTable &ct,
-                           const RegionArgs &ra, uint32_t block, uint32_t unroll, hipStream_t s, KTiming kt) {
+hipError_t launch_apply_rg(const Consts &c, const BinGeometry &g, const ApplySlot *slots, uint32_t n_slots,
+                           const ChunkTable &ct, const RegionArgs &ra, uint32_t block, uint32_t unroll, hipStream_t s, KTiming kt) {
     ApplyTable at{};
     if (n_slots == 0 || n_slots > (uint32_t)kMaxGroup || ct.n != n_slots) return hipErrorInvalidValue;
     if (block != 1024 && block != 512 && block != 256) return hipErrorInvalidConfiguration;
@@ -1216,95 +1334,28 @@ hipError_t launch_apply_rg(const BinGeometry &g, const ApplySlot *slots, uint32_
     const uint32_t lds = (1u << (g.S - 5)) * 4u;
     dim3 grid(n_slots * g.nb);
     switch (unroll) {
-    case 8: launch_apply_rg_u<4>(g, at, ct, ra, grid, lds, block, s, kt); break;
-    case 16: launch_apply_rg_u<8>(g, at, ct, ra, grid, lds, block, s, kt); break;
-    case 32: launch_apply_rg_u<16>(g, at, ct, ra, grid, lds, block, s, kt); break;
+    case 8: launch_apply_rg_u<4>(c, g, at, ct, ra, grid, lds, block, s, kt); break;
+    case 16: launch_apply_rg_u<8>(c, g, at, ct, ra, grid, lds, block, s, kt); break;
+    case 32: launch_apply_rg_u<16>(c, g, at, ct, ra, grid, lds, block, s, kt); break;
     default: return hipErrorInvalidConfiguration;
     }
     return hipGetLastError();
 }
 
-hipError_t launch_apply_rg_merge(const BinGeometry &g, const ApplySlot *slots, uint32_t n_slots, const ChunkTable &ct,
-                                 const RegionArgs &ra, const ApplySlot &global, uint32_t unroll, hipStream_t s,
-                                 KTiming kt) {
+hipError_t launch_apply_rg_merge(const Consts &c, const BinGeometry &g, const ApplySlot *slots, uint32_t n_slots,
+                                 const ChunkTable &ct, const RegionArgs &ra, const ApplySlot &global, uint32_t unroll,
+                                 hipStream_t s, KTiming kt) {
     ApplyTable at{};
     if (n_slots == 0 || n_slots > (uint32_t)kMaxGroup || ct.n != n_slots || g.S > 20) return hipErrorInvalidValue;
     for (uint32_t i = 0; i < n_slots; ++i) at.s[i] = slots[i];
     const uint32_t lds = (1u << (g.S - 5)) * 4u;
     const dim3 grid(g.nb), block(1024);
     switch (unroll) {
-    case 8: hipExtLaunchKernelGGL((k_apply_rg_merge<4>), grid, block, lds, s, kt.start, kt.stop, 0, g, at, n_slots, ct, ra, global); break;
-    case 16: hipExtLaunchKernelGGL((k_apply_rg_merge<8>), grid, block, lds, s, kt.start, kt.stop, 0, g, at, n_slots, ct, ra, global); break;
-    case 32: hipExtLaunchKernelGGL((k_apply_rg_merge<16>), grid, block, lds, s, kt.start, kt.stop, 0, g, at, n_slots, ct, ra, global); break;
+    case 8: hipExtLaunchKernelGGL((k_apply_rg_merge<4>), grid, block, lds, s, kt.start, kt.stop, 0, c, g, at, n_slots, ct, ra, global); break;
+    case 16: hipExtLaunchKernelGGL((k_apply_rg_merge<8>), grid, block, lds, s, kt.start, kt.stop, 0, c, g, at, n_slots, ct, ra, global); break;
+    case 32: hipExtLaunchKernelGGL((k_apply_rg_merge<16>), grid, block, lds, s, kt.start, kt.stop, 0, c, g, at, n_slots, ct, ra, global); break;
     default: return hipErrorInvalidConfiguration;
     }
-    return hipGetLastError();
-}
-
-// The spill pass, once the apply phase has written every bucket back (normally nothing to do): the
-// words that did not fit their region, and the sampled pairs of the tiles the binning kernel listed
-// (more than a tile could stage), re-read from the batch; both recorded with global atomics.  The
-// counts of consecutive launches alternate between two words each: this launch clears the next
-// one's.
-__global__ __launch_bounds__(256) void k_spill(Consts c, BinGeometry g, ApplyTable at, RegionArgs ra, ApplySlot gs,
-                                               uint32_t also_global, BatchList bl) {
-    __shared__ RowLds rl;
-    __shared__ uint32_t *lp[kMaxGroup];
-    __shared__ uint32_t *sp[kMaxGroup];
-    rows_to_lds(rl, c);
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        *ra.spill_next = 0u;
-        *ra.ovf_next = 0u;
-    }
-    if (threadIdx.x < (uint32_t)kMaxGroup) {
-        lp[threadIdx.x] = at.s[threadIdx.x].ldca;
-        sp[threadIdx.x] = at.s[threadIdx.x].seav_w;
-    }
-    __syncthreads();
-    const uint32_t n0 = *ra.spill_n, n = n0 < ra.spill_cap ? n0 : ra.spill_cap;
-    const uint32_t words = 1u << (g.S - 5);
-    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
-        const uint64_t v = ra.spill_w[i];
-        const uint32_t tag = ra.spill_tag[i], si = tag >> 16, b = tag & 0xFFFFu;
-        uint32_t *dst = b < g.nb_ldca ? lp[si] + (uint64_t)b * words : sp[si] + (uint64_t)(b - g.nb_ldca) * words;
-        // (with the merge fused into the apply phase, the global sketch gets the word too)
-        uint32_t *gd = b < g.nb_ldca ? gs.ldca + (uint64_t)b * words : gs.seav_w + (uint64_t)(b - g.nb_ldca) * words;
-#pragma unroll
-        for (uint32_t f = 0; f < 3; ++f) {
-            const uint32_t it = (uint32_t)(v >> (21 * f)) & 0x1FFFFFu;
-            global_or(dst + (it >> 5), 1u << (it & 31u));
-            if (also_global) global_or(gd + (it >> 5), 1u << (it & 31u));
-        }
-    }
-    // listed tiles, one workgroup per tile at a time
-    const uint32_t t0 = *ra.ovf_n, nt = t0 < ra.ovf_cap ? t0 : ra.ovf_cap;
-    for (uint32_t t = blockIdx.x; t < nt; t += gridDim.x) {
-        const uint32_t tile = ra.ovf[t];
-        const BatchDesc B = batch_of(bl, tile);
-        const uint64_t p0 = (uint64_t)(tile - B.first_tile) * g.tile_pairs;
-        const uint64_t p1 = p0 + g.tile_pairs < B.n ? p0 + g.tile_pairs : B.n;
-        const u32x2 *pairs = reinterpret_cast<const u32x2 *>(B.pairs);
-        uint32_t *seav_w = sp[B.slot];
-        for (uint64_t i = p0 + threadIdx.x; i < p1; i += 256) {
-            const u32x2 pr = load_pair(pairs, i, B.swap);
-            if (!sampled(pr.y, c)) continue;
-            const uint32_t b = se_bit(pr.y, c);
-            for (uint32_t r = 0; r < c.sr; ++r) {
-                const uint32_t bit = seav_byte_l(pr.x, r, rl, c) * 8u + b;
-                global_or(seav_w + (bit >> 5), 1u << (bit & 31u));
-                if (also_global) global_or(gs.seav_w + (bit >> 5), 1u << (bit & 31u));
-            }
-        }
-    }
-}
-
-hipError_t launch_spill(const Consts &c, const BinGeometry &g, const ApplySlot *slots, uint32_t n_slots,
-                        const RegionArgs &ra, const BatchList &bl, hipStream_t s, const ApplySlot *global) {
-    ApplyTable at{};
-    if (n_slots == 0 || n_slots > (uint32_t)kMaxGroup) return hipErrorInvalidValue;
-    for (uint32_t i = 0; i < n_slots; ++i) at.s[i] = slots[i];
-    const ApplySlot gs = global ? *global : ApplySlot{};
-    hipLaunchKernelGGL(k_spill, dim3(32), dim3(256), 0, s, c, g, at, ra, gs, global ? 1u : 0u, bl);   // normally nothing to do
     return hipGetLastError();
 }
 

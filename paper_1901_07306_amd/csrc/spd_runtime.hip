@@ -112,7 +112,7 @@ struct spd_ctx {
     uint64_t aux_words = 0;
     bool aux_zero = false;           // region layout: every aux word is zero between launches
     uint32_t close_per_cu[3] = {0, 0, 0};   // resident end-of-window workgroups per CU (64, 128, 256 lanes)
-    uint32_t spill_parity = 0;       // region layout: which of two spill counts the next launch uses
+    uint32_t list_parity = 0;        // region layout: which of two tile-list counts the next launch uses
     CloseBuf cbuf;                  // end-of-window buffers of spd_close_window
     Slot *merge_into = nullptr;     // spd_scan_batches_merge: the global slot, while its scan runs
     bool merge_group = false;       // the region launch being enqueued covers the whole merged call
@@ -541,11 +541,11 @@ void scratch_need(const BinGeometry &g, uint32_t bin_mode, uint64_t tiles, uint6
 }
 
 // Region layout: 64-bit words per (chunk, bucket) region of a chunk of t tiles whose bucket expects
-// E items: 1.25 E plus eight standard deviations of a binomial count, the padding of t tiles (at
-// most two items each) and a margin, three items per word.  Room past the fill costs memory, not
-// traffic.
+// E items: 2 E (a bucket that holds a heavy host gets far more than its share) plus eight standard
+// deviations of a binomial count, the padding of t tiles (at most two items each) and a margin, three
+// items per word.  Room past the fill costs memory, not traffic.
 static uint32_t region_capw(double E, double t) {
-    return (uint32_t)std::ceil((1.25 * E + 8.0 * std::sqrt(E) + 2.0 * t + 64.0) / 3.0);
+    return (uint32_t)std::ceil((2.0 * E + 8.0 * std::sqrt(E) + 2.0 * t + 64.0) / 3.0);
 }
 
 // Expected items per tile of one LDCA bucket and of one SEAV bucket.
@@ -560,58 +560,79 @@ static uint32_t region_cap(const spd_ctx *ctx, double e_tile, double t) {
     return ctx->tune.region_words ? ctx->tune.region_words : region_capw(e_tile * t, t);
 }
 
+// 32-bit words per tile of a region launch beside the regions: every word of the tile's stage has a
+// place in the spill array, every bucket may list one segment of the tile, and the tile itself may
+// be listed.
+static uint64_t region_tile_words(const BinGeometry &g) {
+    return (uint64_t)(g.cap / 3) * 2 + (uint64_t)g.nb * (sizeof(SpillSeg) / 4) + sizeof(ListedTile) / 4;
+}
+
 // The region layout of one launch over the slots of ct (pointers left null): items_words = 32-bit
-// words of the regions, the spill words, the spill tags and the tile list; cur_words = two spill
-// counts, two tile-list counts and the region counters, a multiple of 4.
+// words of the regions, the spill words, the segment lists and the tile list; cur_words = two
+// tile-list counts, the segment counts and the region counters, a multiple of 4.
 void region_layout(const spd_ctx *ctx, const BinGeometry &g, const ChunkTable &ct, uint64_t tiles, RegionArgs *ra,
                    uint64_t *items_words, uint64_t *cur_words) {
     double el, es;
     region_load(ctx, g, &el, &es);
     const uint64_t nbs = g.nb - g.nb_ldca;
     *ra = RegionArgs{};
-    ra->capw_l = region_cap(ctx, el, kChunk);
-    ra->capw_s = region_cap(ctx, es, kChunk);
+    ra->capw_l = region_cap(ctx, el, ct.tiles);
+    ra->capw_s = region_cap(ctx, es, ct.tiles);
     ra->chunk_words = (uint64_t)g.nb_ldca * ra->capw_l + nbs * ra->capw_s;
     uint64_t words = 0;
     for (uint32_t k = 0; k < ct.n; ++k) {
-        const uint32_t nt = ct.hi[k] - ct.lo[k], rem = nt % kChunk;
+        const uint32_t nt = ct.hi[k] - ct.lo[k], rem = nt % ct.tiles;
         ra->slot_base[k] = words;
-        ra->full[k] = nt / kChunk;
+        ra->full[k] = nt / ct.tiles;
         ra->capl_last[k] = rem ? region_cap(ctx, el, rem) : ra->capw_l;
         ra->caps_last[k] = rem ? region_cap(ctx, es, rem) : ra->capw_s;
         words += ra->full[k] * ra->chunk_words + (rem ? g.nb_ldca * ra->capl_last[k] + nbs * ra->caps_last[k] : 0);
     }
-    // every padded word of the launch fits the spill list: at most cap / 3 words per tile; every
-    // tile fits the tile list
-    ra->spill_cap = (uint32_t)std::min<uint64_t>(tiles * g.cap / 3, 0xFFFFFFFFull);
-    ra->ovf_cap = (uint32_t)tiles;
-    *items_words = words * 2 + (uint64_t)ra->spill_cap * 3 + tiles;
-    *cur_words = (4 + (uint64_t)ct.cbase[ct.n] * g.nb + 3) / 4 * 4;
+    ra->tile_words = g.cap / 3;
+    *items_words = words * 2 + tiles * region_tile_words(g);
+    *cur_words = (4 + ((uint64_t)ct.cbase[ct.n] + ct.n) * g.nb + 3) / 4 * 4;
+}
+
+// Tiles per chunk of a region launch over `tiles` tiles.  The binning kernel deals the tiles to the
+// XCDs in eight contiguous ranges, and the tiles of a chunk fill each other's lines: one chunk per
+// XCD keeps that in one L2, and its regions, as long as they can be, are read back in long runs (8
+// routers x 16 Mi pairs, apply with merge: 462 us with chunks of 128 tiles, 414 us so).
+constexpr uint32_t kMinRegionChunk = 64;
+static uint32_t region_chunk(uint64_t tiles) {
+    return (uint32_t)std::max<uint64_t>(kMinRegionChunk, (tiles + kXcds - 1) / kXcds);
+}
+
+static void chunk_table(ChunkTable *ct, const ApplySlot *as, uint32_t nsl, uint32_t chunk_tiles) {
+    *ct = ChunkTable{};
+    ct->n = nsl;
+    ct->tiles = chunk_tiles;
+    for (uint32_t k = 0; k < nsl; ++k) {
+        ct->lo[k] = as[k].tile_lo;
+        ct->hi[k] = as[k].tile_hi;
+        ct->cbase[k + 1] = ct->cbase[k] + (as[k].tile_hi - as[k].tile_lo + chunk_tiles - 1) / chunk_tiles;
+    }
 }
 
 // Upper bound of region_layout's sizes over every launch of at most `tiles` tiles in at most
-// kMaxGroup slots.  A partial chunk of r tiles takes at most A r + B sqrt(r) + C words (A, B, C
-// from region_capw, the ceiling included in C), and over at most kMaxGroup partial chunks of R
-// tiles in all, sum sqrt(r) <= sqrt(kMaxGroup R).
+// kMaxGroup slots.  A launch has at most kXcds full chunks and kMaxGroup partial ones.  A chunk of t
+// tiles takes at most A t + B sqrt(t) + C words (A, B, C from region_capw, the ceiling included in C),
+// and over n chunks of `tiles` tiles in all, sum sqrt(t) <= sqrt(n tiles).
 void region_bound(const spd_ctx *ctx, const BinGeometry &g, uint64_t tiles, uint64_t *items_words,
                   uint64_t *cur_words) {
     double el, es;
     region_load(ctx, g, &el, &es);
-    const double nbl = g.nb_ldca, nbs = g.nb - g.nb_ldca;
+    const double nbl = g.nb_ldca, nbs = g.nb - g.nb_ldca, n = kXcds + kMaxGroup;
     double words;
     if (ctx->tune.region_words) {
-        words = ((double)tiles + kMaxGroup) * (nbl + nbs) * ctx->tune.region_words;
+        words = n * (nbl + nbs) * ctx->tune.region_words;
     } else {
-        const double chunk_words = nbl * region_capw(el * kChunk, kChunk) + nbs * region_capw(es * kChunk, kChunk);
-        const double R = (double)std::min<uint64_t>(tiles, (uint64_t)kMaxGroup * (kChunk - 1));
-        const double A = (nbl * (1.25 * el + 2.0) + nbs * (1.25 * es + 2.0)) / 3.0;
+        const double A = (nbl * (2.0 * el + 2.0) + nbs * (2.0 * es + 2.0)) / 3.0;
         const double B = 8.0 * (nbl * std::sqrt(el) + nbs * std::sqrt(es)) / 3.0;
         const double C = (nbl + nbs) * (64.0 / 3.0 + 1.0);
-        words = (double)(tiles / kChunk) * chunk_words + A * R + B * std::sqrt(kMaxGroup * R) + kMaxGroup * C;
+        words = A * (double)tiles + B * std::sqrt(n * (double)tiles) + n * C;
     }
-    const uint64_t spill = std::min<uint64_t>(tiles * g.cap / 3, 0xFFFFFFFFull);
-    *items_words = (uint64_t)std::ceil(words) * 2 + spill * 3 + tiles;
-    *cur_words = (4 + (tiles / kChunk + kMaxGroup) * g.nb + 3) / 4 * 4;
+    *items_words = (uint64_t)std::ceil(words) * 2 + tiles * region_tile_words(g);
+    *cur_words = (4 + (uint64_t)(kXcds + 2 * kMaxGroup) * g.nb + 3) / 4 * 4;
 }
 
 void free_scratch(spd_ctx *ctx) {
@@ -647,9 +668,9 @@ spd_status ensure_scratch(spd_ctx *ctx, uint64_t items_words, uint64_t meta_word
     return SPD_OK;
 }
 
-// Scratch of one region-layout group: the item regions and spill list (`items`), the spill counts
-// and region counters (`aux`), whether every aux word is known to be zero, and which of the two
-// spill counts the group uses.
+// Scratch of one region-layout group: the item regions, spill words and lists (`items`), the counters
+// (`aux`), whether every aux word is known to be zero, and which of the two tile-list counts the
+// group uses.
 struct RegionScratch {
     uint32_t *items;
     uint64_t items_words;
@@ -660,9 +681,8 @@ struct RegionScratch {
 };
 
 // One group of the region layout in the given scratch: clear the counters (unless known zero), bin
-// into the regions, apply every (slot, bucket), then the spill pass.  A fresh slot needs no clear:
-// the apply phase writes all of its buckets from zero, and only the spill pass, after it, writes
-// the slot directly.  SPD_E_INVALID (nothing enqueued) if the group's layout does not fit the
+// into the regions, apply every (slot, bucket).  A fresh slot needs no clear: the apply phase writes
+// all of its buckets from zero, and nothing else writes the slot.  SPD_E_INVALID (nothing enqueued) if the group's layout does not fit the
 // scratch.
 spd_status region_launch_at(spd_ctx *ctx, const BinGeometry &g, const BatchDesc *bd, uint32_t nbd, uint32_t tiles,
                             const ChunkTable &ct, const SlotPtrs *sp, const ApplySlot *as, uint32_t nsl,
@@ -673,17 +693,16 @@ spd_status region_launch_at(spd_ctx *ctx, const BinGeometry &g, const BatchDesc 
     if (ra.chunk_words >= (1ull << 31)) return fail(ctx, SPD_E_INVALID, "region layout: chunk too large");
     if (items_words > rs.items_words || cur_words > rs.aux_words)
         return fail(ctx, SPD_E_INVALID, "region layout larger than its scratch");
-    const uint64_t region_words = items_words - (uint64_t)ra.spill_cap * 3 - ra.ovf_cap;   // 32-bit words
+    const uint64_t region_words = items_words - tiles * region_tile_words(g);   // 32-bit words, even
     const uint32_t par = *rs.parity;
     ra.items = reinterpret_cast<uint64_t *>(rs.items);
-    ra.spill_w = reinterpret_cast<uint64_t *>(rs.items + region_words);
-    ra.spill_tag = rs.items + region_words + (uint64_t)ra.spill_cap * 2;
-    ra.ovf = rs.items + region_words + (uint64_t)ra.spill_cap * 3;
-    ra.spill_n = rs.aux + par;
-    ra.spill_next = rs.aux + (par ^ 1u);
-    ra.ovf_n = rs.aux + 2 + par;
-    ra.ovf_next = rs.aux + 2 + (par ^ 1u);
-    ra.cur = rs.aux + 4;
+    ra.spill_w = ra.items + region_words / 2;
+    ra.seg = reinterpret_cast<SpillSeg *>(ra.spill_w + (uint64_t)tiles * ra.tile_words);
+    ra.tile = reinterpret_cast<ListedTile *>(ra.seg + (uint64_t)tiles * g.nb);
+    ra.tile_n = rs.aux + par;
+    ra.tile_next = rs.aux + (par ^ 1u);
+    ra.seg_n = rs.aux + 4;
+    ra.cur = ra.seg_n + (uint64_t)ct.n * g.nb;
     // a few batches travel in the kernel arguments; more go through the pinned staging ring
     BatchList bl{};
     bl.n = nbd;
@@ -703,10 +722,15 @@ spd_status region_launch_at(spd_ctx *ctx, const BinGeometry &g, const BatchDesc 
         cl.words[cl.n++] = rs.aux_words;
         SPD_HIP(ctx, launch_clear(cl, s));
     }
-    *rs.aux_zero = false;   // until the launch's apply and spill phases are enqueued
+    *rs.aux_zero = false;   // until the launch's apply phase is enqueued
     {
         ProfKernel pk(ctx, SPD_K_BIN);
         SPD_HIP(ctx, launch_region(ctx->c, g, bl, tiles, ct, sp, ra, s, pk.kt));
+    }
+    if (!inl) {
+        // the staging slot may be rewritten once the binning kernel (its only reader) has read it
+        SPD_HIP(ctx, hipEventRecord(ctx->bd_ev[ctx->bd_next], s));
+        ctx->bd_next = (ctx->bd_next + 1) % kBdRing;
     }
     // the router merge fused into the apply phase (1024-lane workgroups hold a bucket's OR in
     // registers), when this launch covers every router of a merged call
@@ -719,18 +743,10 @@ spd_status region_launch_at(spd_ctx *ctx, const BinGeometry &g, const BatchDesc 
     {
         ProfKernel pk(ctx, SPD_K_APPLY);
         if (fuse)
-            SPD_HIP(ctx, launch_apply_rg_merge(g, as, nsl, ct, ra, gas, ctx->tune.apply_unroll, s, pk.kt));
+            SPD_HIP(ctx, launch_apply_rg_merge(ctx->c, g, as, nsl, ct, ra, gas, ctx->tune.apply_unroll, s, pk.kt));
         else
-            SPD_HIP(ctx, launch_apply_rg(g, as, nsl, ct, ra, ctx->tune.apply_block, ctx->tune.apply_unroll, s, pk.kt));
-    }
-    {
-        ProfScope ps(ctx, SPD_K_SPILL, s);
-        SPD_HIP(ctx, launch_spill(ctx->c, g, as, nsl, ra, bl, s, fuse ? &gas : nullptr));
-        if (!inl) {
-            // the staging slot may be rewritten once the spill pass (the last reader) has read it
-            SPD_HIP(ctx, hipEventRecord(ctx->bd_ev[ctx->bd_next], s));
-            ctx->bd_next = (ctx->bd_next + 1) % kBdRing;
-        }
+            SPD_HIP(ctx, launch_apply_rg(ctx->c, g, as, nsl, ct, ra, ctx->tune.apply_block, ctx->tune.apply_unroll, s,
+                                         pk.kt));
     }
     if (fuse) ctx->merged = true;
     *rs.parity = par ^ 1u;
@@ -749,7 +765,7 @@ spd_status region_launch(spd_ctx *ctx, const BinGeometry &g, const std::vector<B
     spd_status st = ensure_scratch(ctx, items_words, 0, s);
     if (!st) st = ensure_aux(ctx, cur_words, s);
     if (st) return st;
-    const RegionScratch rs{ctx->items, ctx->items_words, ctx->aux, ctx->aux_words, &ctx->aux_zero, &ctx->spill_parity};
+    const RegionScratch rs{ctx->items, ctx->items_words, ctx->aux, ctx->aux_words, &ctx->aux_zero, &ctx->list_parity};
     return region_launch_at(ctx, g, bd.data(), (uint32_t)bd.size(), tiles, ct, sp, as, nsl, rs, s);
 }
 
@@ -904,17 +920,10 @@ spd_status scan_work(spd_ctx *ctx, std::vector<WorkItem> &ws, hipStream_t s) {
         } else {
             if ((uint64_t)tiles * g.cap >= (1ull << 32))
                 return fail(ctx, SPD_E_INVALID, "launch too large for 32-bit item offsets");
-            // chunks of kChunk tiles, per slot
             ChunkTable ct{};
-            ct.n = nsl;
-            for (uint32_t k = 0; k < nsl; ++k) {
-                ct.lo[k] = as[k].tile_lo;
-                ct.hi[k] = as[k].tile_hi;
-                ct.cbase[k + 1] = ct.cbase[k] + (as[k].tile_hi - as[k].tile_lo + kChunk - 1) / kChunk;
-            }
-            const uint32_t chunks = ct.cbase[nsl];
             if (ctx->tune.bin_mode == 2) {
                 // the exact-count layout (less scratch) if the region layout does not fit the budget
+                chunk_table(&ct, as, nsl, region_chunk(tiles));
                 ctx->merge_group = ctx->merge_into && group_start == 0 && i0 == ws.size();
                 spd_status st = region_launch(ctx, g, bd, tiles, ct, sp, as, nsl, s);
                 ctx->merge_group = false;
@@ -925,6 +934,8 @@ spd_status scan_work(spd_ctx *ctx, std::vector<WorkItem> &ws, hipStream_t s) {
                     continue;
                 }
             }
+            chunk_table(&ct, as, nsl, kChunk);
+            const uint32_t chunks = ct.cbase[nsl];
             spd_status st = ensure_scratch(ctx, items_words, meta_words, s);
             if (!st) st = ensure_aux(ctx, (uint64_t)nsl * g.nb + 1 + (uint64_t)chunks * g.nb, s);
             if (st) return st;
@@ -996,10 +1007,9 @@ spd_status scan_noalloc(spd_ctx *ctx, Slot *sl, const uint32_t *pairs, uint64_t 
     // the layout grows with the tile count, so a binary search finds it
     const uint64_t cap = SPD_NOALLOC_SCRATCH_BYTES;
     auto layout_of = [&](uint32_t tiles, ChunkTable *ct, uint64_t *iw, uint64_t *cw) {
-        *ct = ChunkTable{};
-        ct->n = 1;
-        ct->hi[0] = tiles;
-        ct->cbase[1] = (tiles + kChunk - 1) / kChunk;
+        ApplySlot as{};
+        as.tile_hi = tiles;
+        chunk_table(ct, &as, 1, region_chunk(tiles));
         RegionArgs ra{};
         region_layout(ctx, g, *ct, tiles, &ra, iw, cw);
         return ra.chunk_words < (1ull << 31);
