@@ -49,7 +49,7 @@ __device__ __forceinline__ uint32_t row_index(uint32_t lp, uint32_t isb, uint32_
 }
 
 // Inverse placement used by Eq. 3: the LP bits that a row index c of row (isb, ibn) stands for.
-__device__ __forceinline__ uint32_t row_bits_in_lp(uint32_t c, uint32_t isb, uint32_t L) {
+__host__ __device__ __forceinline__ uint32_t row_bits_in_lp(uint32_t c, uint32_t isb, uint32_t L) {
     uint64_t t = (uint64_t)c << isb;
     uint64_t lmask = (L == 32) ? 0xFFFFFFFFull : ((1ull << L) - 1ull);
     return (uint32_t)((t | (t >> L)) & lmask);
@@ -104,6 +104,26 @@ __host__ __device__ __forceinline__ uint32_t at_active(uint32_t v, uint32_t ct, 
     return ((ct - v) & (kAtCodes - 1u)) < K ? 1u : 0u;   // ct = at_code(t)
 }
 constexpr uint32_t kAtMaxK = 254;   // G = 255 - K >= 1
+
+// The same test on the four counters of a 32-bit word at once.  Per byte, e = (ct - v) mod 256 without
+// borrows between bytes; e < K for K <= 128 is "top bit clear and the low 7 bits below K".  For a larger
+// K the complement is tested: 255 - e < 256 - K (at most 127) says that the counter is not active.
+struct AtView {
+    uint32_t ct4;    // the current slice's code in every byte
+    uint32_t k4;     // min(K, 256 - K) in every byte
+    uint32_t flip;   // all ones when K > 128
+};
+__host__ __device__ __forceinline__ AtView at_view(uint32_t ct, uint32_t K) {
+    const bool wide = K > 128u;
+    return AtView{ct * 0x01010101u, (wide ? 256u - K : K) * 0x01010101u, wide ? ~0u : 0u};
+}
+// Bit 7 of byte j of the result is set iff counter j of w is active.
+__host__ __device__ __forceinline__ uint32_t at_active4(uint32_t w, const AtView &a) {
+    constexpr uint32_t H = 0x80808080u, L = 0x7F7F7F7Fu;
+    const uint32_t e = (((a.ct4 | H) - (w & L)) ^ ((a.ct4 ^ ~w) & H)) ^ a.flip;
+    const uint32_t d = ((e & L) | H) - a.k4;   // top bit: low 7 bits of e at least k4
+    return (~(e | d) ^ a.flip) & H;
+}
 
 // What the end-of-window kernel reads: bits, 16-bit time stamps, or AT counters.
 enum CloseMode : int { kCloseBits = 0, kCloseStamps = 1, kCloseAt = 2 };
@@ -268,27 +288,38 @@ hipError_t launch_max_merge_u16(uint16_t *dst, const uint16_t *const *src, uint3
 hipError_t launch_renormalize_u16(uint16_t *p, uint64_t n, uint16_t off, hipStream_t s);
 hipError_t launch_bit_view(const uint16_t *ts, uint64_t n_bits, uint16_t thr, uint32_t *out_words, hipStream_t s);
 
+// The last workgroup of a close is found by counting: one 64-bit count per line (workgroups in the
+// low half, candidates in the high one), kCloseGroups of them and a root, all zero between closes.
+// Atomics on one address are serialized device-wide (about 16 ns each).
+constexpr uint32_t kCloseGroups = 32;
+constexpr uint32_t kCloseLine = 16;                                    // 64-bit words per line
+constexpr uint32_t kCloseCountBytes = (kCloseGroups + 1) * kCloseLine * 8;
 struct CloseArgs {
-    const uint8_t *seav;     // the SEAV as bits (sliding: the bit view of its counters)
+    const uint8_t *seav;     // the SEAV as bits, or its counters
+    const uint16_t *seav_ts;
+    const uint8_t *seav_at;
     const uint32_t *ldca;
     const uint16_t *ldca_ts;   // sliding: the LDCA's counters, read by the ULDC filter
     const uint8_t *ldca_at;
     uint32_t thr;        // sliding, 16-bit stamps: stamp threshold of the bit view
-    uint32_t at_ct;      // sliding, AT pool: code of the current slice
-    uint32_t at_k;       // sliding, AT pool: window length K
+    AtView at;           // sliding, AT pool: which counters are active
     uint32_t *rec;       // (ip, z0) pairs
-    uint32_t *counters;  // [0] reported, [1] candidates; zero at launch, left zero by k_close_out
+    uint32_t *counters;  // [0] reported, zero between closes; [2] the last close's sequence number
+    uint64_t *counts;    // see kCloseGroups
     uint32_t *host_out;  // host-visible: the counters, then the first host_recs records
     uint32_t host_recs;
     uint32_t rec_cap;
     uint32_t n_rp;
-    uint32_t list_stride;
     uint32_t qcap;
-    uint32_t stage_words;  // LDS words per wavefront holding one SEA
     uint32_t parts_log2;   // each SEA's candidates are searched by 2^parts_log2 wavefronts
+    uint32_t lp_mask[kMaxRows];   // the LP bits of each row
 };
+// LDS words per wavefront: every SE may be hot, then the queue.
+__host__ __device__ __forceinline__ uint32_t close_wave_words(uint32_t sea_bytes, uint32_t qcap) {
+    return sea_bytes + qcap;
+}
 hipError_t launch_close(const Consts &c, const CloseArgs &a, int mode, uint32_t block, uint32_t grid, hipStream_t s);
 // Workgroups of the end-of-window kernel that one compute unit holds at once (registers and LDS).
-uint32_t close_blocks_per_cu(int mode, uint32_t block, uint32_t lds_bytes);
+uint32_t close_blocks_per_cu(int mode, uint32_t block, uint32_t sr, uint32_t lds_bytes);
 
 }  // namespace spd

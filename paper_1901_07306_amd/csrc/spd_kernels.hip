@@ -258,24 +258,6 @@ struct CPoolTable {
 // Byte k of a 16-byte vector.
 __device__ __forceinline__ uint32_t byte_of(const u32x4 &v, uint32_t k) { return (v[k >> 2] >> (8 * (k & 3))) & 0xFFu; }
 
-// Activity of the four AT counters packed in one 32-bit word, four at a time (SIMD within a
-// register): bit 7 of byte j of the result is set iff counter j is active, i.e. its age
-// (ct - v) mod 256 is below K.  The per-byte difference is taken without borrows between bytes;
-// the per-byte compare with K needs K <= 128, so larger windows decode byte by byte.
-__device__ __forceinline__ uint32_t at_active_bytes(uint32_t w, uint32_t ct, uint32_t K) {
-    constexpr uint32_t H = 0x80808080u, L = 0x7F7F7F7Fu;
-    if (K <= 128u) {
-        const uint32_t ct4 = ct * 0x01010101u, k4 = K * 0x01010101u;
-        const uint32_t e = ((ct4 | H) - (w & L)) ^ ((ct4 ^ ~w) & H);   // (ct - v) mod 256 per byte
-        const uint32_t d = ((e & L) | H) - k4;                          // top bit: low 7 bits of e >= K
-        return ~(e | d) & H;
-    }
-    uint32_t r = 0;
-#pragma unroll
-    for (uint32_t j = 0; j < 4; ++j) r |= at_active((w >> (8 * j)) & 0xFFu, ct, K) << (8 * j + 7);
-    return r;
-}
-
 __global__ __launch_bounds__(256) void k_at_sweep(PoolTable pt, uint32_t n, uint64_t lo16, uint64_t hi16, uint32_t ct,
                                                   uint32_t K) {
     const uint64_t stride = (uint64_t)gridDim.x * 256;
@@ -347,22 +329,22 @@ hipError_t launch_at_merge(uint8_t *dst, const uint8_t *const *src, uint32_t n_s
     return hipGetLastError();
 }
 
-// Bit view of AT counters: 32 counters (two 16-byte vectors) per output word.
-__global__ __launch_bounds__(256) void k_bit_view_at(const uint8_t *__restrict__ at, uint64_t n_words, uint32_t ct,
-                                                     uint32_t K, uint32_t *__restrict__ out) {
+// The bits of eight counters (two words) as one byte: counter j of a at bit j, of b at bit 4 + j.
+__device__ __forceinline__ uint32_t at_byte(uint32_t a, uint32_t b, const AtView &v) {
+    const uint32_t p = (at_active4(a, v) >> 7) | (at_active4(b, v) >> 3);   // bits 8 j and 8 j + 4
+    return (p | p >> 7 | p >> 14 | p >> 21) & 0xFFu;
+}
+// 32 counters (two 16-byte vectors) as one word of bits, in order.
+__device__ __forceinline__ uint32_t at_word(const u32x4 &x, const u32x4 &y, const AtView &v) {
+    return at_byte(x.x, x.y, v) | at_byte(x.z, x.w, v) << 8 | at_byte(y.x, y.y, v) << 16 | at_byte(y.z, y.w, v) << 24;
+}
+
+// Bit view of AT counters.
+__global__ __launch_bounds__(256) void k_bit_view_at(const uint8_t *__restrict__ at, uint64_t n_words, AtView v,
+                                                     uint32_t *__restrict__ out) {
     const uint64_t stride = (uint64_t)gridDim.x * 256;
-    for (uint64_t w = blockIdx.x * (uint64_t)256 + threadIdx.x; w < n_words; w += stride) {
-        const u32x4 a = reinterpret_cast<const u32x4 *>(at)[2 * w], b = reinterpret_cast<const u32x4 *>(at)[2 * w + 1];
-        uint32_t v = 0;
-#pragma unroll
-        for (uint32_t q = 0; q < 4; ++q) {
-            // counters 4q..4q+3 of each vector: activity bits at 0, 8, 16, 24, gathered into 4 bits
-            const uint32_t ma = at_active_bytes(a[q], ct, K) >> 7, mb = at_active_bytes(b[q], ct, K) >> 7;
-            v |= ((ma | ma >> 7 | ma >> 14 | ma >> 21) & 0xFu) << (4 * q);
-            v |= ((mb | mb >> 7 | mb >> 14 | mb >> 21) & 0xFu) << (16 + 4 * q);
-        }
-        out[w] = v;
-    }
+    for (uint64_t w = blockIdx.x * (uint64_t)256 + threadIdx.x; w < n_words; w += stride)
+        out[w] = at_word(reinterpret_cast<const u32x4 *>(at)[2 * w], reinterpret_cast<const u32x4 *>(at)[2 * w + 1], v);
 }
 
 hipError_t launch_bit_view_at(const uint8_t *at, uint64_t n_bits, uint32_t ct, uint32_t K, uint32_t *out_words,
@@ -370,7 +352,7 @@ hipError_t launch_bit_view_at(const uint8_t *at, uint64_t n_bits, uint32_t ct, u
     if (n_bits % 32) return hipErrorInvalidValue;
     const uint64_t words = n_bits / 32;
     const uint32_t grid = (uint32_t)((words + 255) / 256 < 8192 ? (words + 255) / 256 : 8192);
-    hipLaunchKernelGGL(k_bit_view_at, dim3(grid ? grid : 1), dim3(256), 0, s, at, words, ct, K, out_words);
+    hipLaunchKernelGGL(k_bit_view_at, dim3(grid ? grid : 1), dim3(256), 0, s, at, words, at_view(ct, K), out_words);
     return hipGetLastError();
 }
 
@@ -1761,63 +1743,88 @@ hipError_t launch_bit_view(const uint16_t *ts, uint64_t n_bits, uint16_t thr, ui
 }
 
 // ------------------------------------------------------------------------------ end of window
-// Bit view of the two 16-bit stamps packed in one 32-bit word (stamp j in half j).
+// What the end of window reads: bits, or the counters of a sliding window, of which 32 stand for a
+// word of bits.
+template <int MODE>
+struct RawWord {
+    u32x4 v[MODE == kCloseStamps ? 4 : 2];
+};
+template <>
+struct RawWord<kCloseBits> {
+    uint32_t v;
+};
+template <int MODE>
+__device__ __forceinline__ RawWord<MODE> load_raw(const void *p) {
+    RawWord<MODE> r;
+#pragma unroll
+    for (uint32_t q = 0; q < (MODE == kCloseStamps ? 4u : 2u); ++q) r.v[q] = reinterpret_cast<const u32x4 *>(p)[q];
+    return r;
+}
+template <>
+__device__ __forceinline__ RawWord<kCloseBits> load_raw<kCloseBits>(const void *p) {
+    return RawWord<kCloseBits>{*reinterpret_cast<const uint32_t *>(p)};
+}
+// The two 16-bit stamps of a 32-bit word as bits.
 __device__ __forceinline__ uint32_t ts_bits2(uint32_t w, uint32_t thr) {
     return ((w & 0xFFFFu) >= thr ? 1u : 0u) | ((w >> 16) >= thr ? 2u : 0u);
 }
-
-// at_active_bytes with the close's window.
-__device__ __forceinline__ uint32_t at_active4(uint32_t w, const CloseArgs &a) { return at_active_bytes(w, a.at_ct, a.at_k); }
-
-// One SEAV byte as bits.  With counters (sliding window) the end of window reads a bit view of
-// the SEAV made by a streaming kernel just before it (a.seav), so every mode reads bytes here.
 template <int MODE>
-__device__ __forceinline__ uint32_t load_se(const CloseArgs &a, uint64_t byte) {
-    return a.seav[byte];
-}
-
-// The counters behind one LDCA word (word < 2^27: a sketch has fewer than 2^32 bits), as loaded:
-// 32 16-bit stamps (four 16-byte vectors) or 32 AT counters (two).
-template <int MODE>
-struct LdcRaw {
-    u32x4 v[MODE == kCloseStamps ? 4 : 2];
-};
-template <int MODE>
-__device__ __forceinline__ LdcRaw<MODE> load_ldc_raw(const CloseArgs &a, uint32_t word) {
-    LdcRaw<MODE> r;
-    const u32x4 *t = MODE == kCloseStamps ? reinterpret_cast<const u32x4 *>(a.ldca_ts + (uint64_t)word * 32)
-                                          : reinterpret_cast<const u32x4 *>(a.ldca_at + (uint64_t)word * 32);
-#pragma unroll
-    for (uint32_t q = 0; q < (MODE == kCloseStamps ? 4u : 2u); ++q) r.v[q] = t[q];
-    return r;
-}
-// Their bit view.
-template <int MODE>
-__device__ __forceinline__ uint32_t decode_ldc(const CloseArgs &a, const LdcRaw<MODE> &r) {
-    uint32_t v = 0;
-    if (MODE == kCloseStamps) {
+__device__ __forceinline__ uint32_t decode_raw(const CloseArgs &a, const RawWord<MODE> &r) {
+    if constexpr (MODE == kCloseBits) {
+        return r.v;
+    } else if constexpr (MODE == kCloseAt) {
+        return at_word(r.v[0], r.v[1], a.at);
+    } else {
+        uint32_t v = 0;
 #pragma unroll
         for (uint32_t q = 0; q < 4; ++q) {
             const u32x4 x = r.v[q];
-            v |= (ts_bits2(x.x, a.thr) | ts_bits2(x.y, a.thr) << 2 | ts_bits2(x.z, a.thr) << 4 |
-                  ts_bits2(x.w, a.thr) << 6) << (8 * q);
+            v |= (ts_bits2(x.x, a.thr) | ts_bits2(x.y, a.thr) << 2 | ts_bits2(x.z, a.thr) << 4 | ts_bits2(x.w, a.thr) << 6)
+                 << (8 * q);
         }
-    } else {
-        // 32 counters in a fixed permuted order (counter 4h + j at bit 8j + h): the LDCs of a
-        // candidate are all read the same way, so the AND of its rows and the popcount are unchanged
-        const u32x4 x = r.v[0], y = r.v[1];
-        v = (at_active4(x.x, a) >> 7) | (at_active4(x.y, a) >> 6) | (at_active4(x.z, a) >> 5) |
-            (at_active4(x.w, a) >> 4) | (at_active4(y.x, a) >> 3) | (at_active4(y.y, a) >> 2) |
-            (at_active4(y.z, a) >> 1) | at_active4(y.w, a);
+        return v;
     }
-    return v;
 }
-
-// One LDCA word as bits.
+// The ones of an LDC word.  AT counters are packed in a fixed permuted order (counter 4h + j at bit
+// 8j + h): the LDCs of a candidate are all read the same way, so the AND of its rows and its weight
+// are unchanged.
 template <int MODE>
-__device__ __forceinline__ uint32_t load_ldc_word(const CloseArgs &a, uint32_t word) {
-    if (MODE == kCloseBits) return a.ldca[word];
-    return decode_ldc<MODE>(a, load_ldc_raw<MODE>(a, word));
+__device__ __forceinline__ uint32_t decode_ldc(const CloseArgs &a, const RawWord<MODE> &r) {
+    if constexpr (MODE == kCloseAt) {
+        const u32x4 x = r.v[0], y = r.v[1];
+        return (at_active4(x.x, a.at) >> 7) | (at_active4(x.y, a.at) >> 6) | (at_active4(x.z, a.at) >> 5) |
+               (at_active4(x.w, a.at) >> 4) | (at_active4(y.x, a.at) >> 3) | (at_active4(y.y, a.at) >> 2) |
+               (at_active4(y.z, a.at) >> 1) | at_active4(y.w, a.at);
+    } else {
+        return decode_raw<MODE>(a, r);
+    }
+}
+// 32 bits of the SEAV from byte `byte` on; one byte of it; word `word` of the LDCA (below 2^27: a
+// sketch has fewer than 2^32 bits).
+template <int MODE>
+__device__ __forceinline__ RawWord<MODE> load_sea(const CloseArgs &a, uint32_t byte) {
+    if constexpr (MODE == kCloseBits) return load_raw<MODE>(a.seav + byte);
+    else if constexpr (MODE == kCloseAt) return load_raw<MODE>(a.seav_at + byte * 8u);
+    else return load_raw<MODE>(a.seav_ts + (uint64_t)byte * 8);
+}
+template <int MODE>
+__device__ __forceinline__ uint32_t load_se(const CloseArgs &a, uint64_t byte) {
+    if constexpr (MODE == kCloseBits) {
+        return a.seav[byte];
+    } else if constexpr (MODE == kCloseAt) {
+        const uint32_t *t = reinterpret_cast<const uint32_t *>(a.seav_at + byte * 8);
+        return at_byte(t[0], t[1], a.at);
+    } else {
+        const u32x4 x = *reinterpret_cast<const u32x4 *>(a.seav_ts + byte * 8);
+        return ts_bits2(x.x, a.thr) | ts_bits2(x.y, a.thr) << 2 | ts_bits2(x.z, a.thr) << 4 | ts_bits2(x.w, a.thr) << 6;
+    }
+}
+template <int MODE>
+__device__ __forceinline__ RawWord<MODE> load_ldc(const CloseArgs &a, uint32_t word) {
+    // (bits and AT counters: a 32-bit byte offset from a scalar base)
+    if constexpr (MODE == kCloseBits) return load_raw<MODE>(reinterpret_cast<const uint8_t *>(a.ldca) + word * 4u);
+    else if constexpr (MODE == kCloseAt) return load_raw<MODE>(a.ldca_at + word * 32u);
+    else return load_raw<MODE>(a.ldca_ts + (uint64_t)word * 32);
 }
 
 // Orders LDS traffic between lanes of one wavefront (writes by some lanes, reads by others).
@@ -1831,333 +1838,398 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
     return v;
 }
 
-// ULDC of every queued candidate: AND of its LR LDCs, z0 = k - popcount; report if z0 <= z_theta.
-// Four candidates at a time, 16 lanes each; a lane reads 8 words of each of two LDCs before it
+// One super point: to the device records, and the first ones straight to host-visible memory, written
+// through (the workgroup waits for them before it counts itself finished).
+__device__ __forceinline__ void report(const CloseArgs &a, uint32_t h, uint32_t z0) {
+    const uint32_t slot = atomicAdd(&a.counters[0], 1u);
+    const uint64_t v = (uint64_t)h | (uint64_t)z0 << 32;
+    if (slot < a.rec_cap) reinterpret_cast<uint64_t *>(a.rec)[slot] = v;
+    if (slot < a.host_recs)
+        __hip_atomic_store(reinterpret_cast<uint64_t *>(a.host_out + 4) + slot, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// ULDC of candidates cand(e), e < n, of which this wavefront takes its share (share of NS): AND of
+// the LR LDCs, z0 = k - popcount, reported if z0 <= z_theta.
+// Bits: four candidates at a time, 16 lanes each; a lane reads 8 words of each of two LDCs before it
 // waits, so one round trip to memory serves four candidates (k = 4096, LR = 2).
-// Counter modes (a window of time stamps or AT counters): an LDC word is 32 counters (64 or 32
-// bytes), so one candidate takes the whole wavefront: each lane reads two words of every row, all
-// rows' loads in flight together (one round trip per candidate for k up to 4096).
-template <int MODE>
-__device__ void filter_queue_counters(const CloseArgs &a, const Consts &c, const uint32_t *queue, uint32_t qn,
-                                      uint32_t lane) {
+// Counters: an LDC word is 32 counters (64 or 32 bytes), so one candidate takes the whole wavefront:
+// each lane reads two words of a row at a time; AT counters of two rows are loaded before either is
+// decoded (the larger 16-bit stamps go one row at a time).
+template <int MODE, typename Get>
+__device__ __forceinline__ void filter_candidates(const CloseArgs &a, const Consts &c, Get cand, uint32_t n, uint32_t share,
+                                                  uint32_t NS, uint32_t lane) {
     const uint32_t words = 1u << (c.log2k - 5);
-    for (uint32_t e = 0; e < qn; ++e) {
+    if constexpr (MODE == kCloseBits) {
+        constexpr uint32_t G = 16, W = 8, RB = 2, PER = 64 / G;
+        const uint32_t grp = lane / G, sub = lane % G;
+        for (uint32_t e0 = share * PER; e0 < n; e0 += NS * PER) {
+            const bool live = e0 + grp < n;
+            const uint32_t h = cand(live ? e0 + grp : e0);
+            uint32_t ones = 0;
+            for (uint32_t w0 = 0; w0 < words; w0 += G * W) {
+                uint32_t u[W];
+#pragma unroll
+                for (uint32_t k = 0; k < W; ++k) u[k] = 0xFFFFFFFFu;
+                for (uint32_t r0 = 0; r0 < c.lr; r0 += RB) {
+                    uint32_t v[RB][W];
+#pragma unroll
+                    for (uint32_t rr = 0; rr < RB; ++rr) {
+                        const uint32_t r = r0 + rr < c.lr ? r0 + rr : c.lr - 1;   // a repeated row is harmless
+                        const uint32_t base = ((r << c.log2lc) | ldc_col(h, r, c)) << (c.log2k - 5);
+#pragma unroll
+                        for (uint32_t k = 0; k < W; ++k) {
+                            const uint32_t w = w0 + k * G + sub;
+                            v[rr][k] = load_ldc<MODE>(a, base + (w < words ? w : words - 1)).v;
+                        }
+                    }
+#pragma unroll
+                    for (uint32_t rr = 0; rr < RB; ++rr)
+#pragma unroll
+                        for (uint32_t k = 0; k < W; ++k) u[k] &= v[rr][k];
+                }
+#pragma unroll
+                for (uint32_t k = 0; k < W; ++k)
+                    if (w0 + k * G + sub < words) ones += __popc(u[k]);
+            }
+            for (uint32_t o = G / 2; o > 0; o >>= 1) ones += __shfl_xor(ones, o, 64);
+            const uint32_t z0 = (1u << c.log2k) - ones;
+            if (live && sub == 0 && z0 <= c.z_theta) report(a, h, z0);
+        }
+    } else {
+        for (uint32_t e = share; e < n; e += NS) {
+            const uint32_t h = cand(e);
+            uint32_t ones = 0;
+            for (uint32_t w0 = 0; w0 < words; w0 += 128) {
+                const uint32_t wa = w0 + lane < words ? w0 + lane : words - 1;
+                const uint32_t wb = w0 + 64 + lane < words ? w0 + 64 + lane : words - 1;
+                uint32_t ua = 0xFFFFFFFFu, ub = 0xFFFFFFFFu;
+                constexpr uint32_t RB = MODE == kCloseAt ? 2 : 1;
+                for (uint32_t r0 = 0; r0 < c.lr; r0 += RB) {
+                    RawWord<MODE> x[RB], y[RB];
+#pragma unroll
+                    for (uint32_t rr = 0; rr < RB; ++rr) {
+                        const uint32_t r = r0 + rr < c.lr ? r0 + rr : c.lr - 1;
+                        const uint32_t base = ((r << c.log2lc) | ldc_col(h, r, c)) << (c.log2k - 5);
+                        x[rr] = load_ldc<MODE>(a, base + wa);
+                        y[rr] = load_ldc<MODE>(a, base + wb);
+                    }
+#pragma unroll
+                    for (uint32_t rr = 0; rr < RB; ++rr) {
+                        ua &= decode_ldc<MODE>(a, x[rr]);
+                        ub &= decode_ldc<MODE>(a, y[rr]);
+                    }
+                }
+                ones += (w0 + lane < words ? __popc(ua) : 0u) + (w0 + 64 + lane < words ? __popc(ub) : 0u);
+            }
+            ones = wave_sum(ones);
+            const uint32_t z0 = (1u << c.log2k) - ones;
+            if (lane == 0 && z0 <= c.z_theta) report(a, h, z0);
+        }
+    }
+}
+
+// The same for a queue that has filled up (crowded SEAs only): one candidate at a time, little code.
+template <int MODE>
+__device__ __forceinline__ void filter_queue(const CloseArgs &a, const Consts &c, const uint32_t *queue, uint32_t n,
+                                             uint32_t lane) {
+    const uint32_t words = 1u << (c.log2k - 5);
+    for (uint32_t e = 0; e < n; ++e) {
         const uint32_t h = queue[e];
         uint32_t ones = 0;
-        for (uint32_t w0 = 0; w0 < words; w0 += 128) {
-            const uint32_t wa = w0 + lane < words ? w0 + lane : words - 1;
-            const uint32_t wb = w0 + 64 + lane < words ? w0 + 64 + lane : words - 1;
-            uint32_t ua = 0xFFFFFFFFu, ub = 0xFFFFFFFFu;
-            // a runtime loop over the rows keeps the decoding code small (instruction cache); AT
-            // counters of two rows at a time are loaded before either is decoded (one round trip
-            // per two rows; the larger 16-bit stamps go one row at a time)
-            if constexpr (MODE == kCloseAt) {
-                for (uint32_t r = 0; r < c.lr; r += 2) {
-                    const uint32_t r1 = r + 1 < c.lr ? r + 1 : r;
-                    const uint32_t b0 = ((r << c.log2lc) | ldc_col(h, r, c)) << (c.log2k - 5);
-                    const uint32_t b1 = ((r1 << c.log2lc) | ldc_col(h, r1, c)) << (c.log2k - 5);
-                    const LdcRaw<MODE> x0 = load_ldc_raw<MODE>(a, b0 + wa), y0 = load_ldc_raw<MODE>(a, b0 + wb);
-                    const LdcRaw<MODE> x1 = load_ldc_raw<MODE>(a, b1 + wa), y1 = load_ldc_raw<MODE>(a, b1 + wb);
-                    ua &= decode_ldc<MODE>(a, x0) & decode_ldc<MODE>(a, x1);
-                    ub &= decode_ldc<MODE>(a, y0) & decode_ldc<MODE>(a, y1);
-                }
-            } else {
-                for (uint32_t r = 0; r < c.lr; ++r) {
-                    const uint32_t b0 = ((r << c.log2lc) | ldc_col(h, r, c)) << (c.log2k - 5);
-                    ua &= load_ldc_word<MODE>(a, b0 + wa);
-                    ub &= load_ldc_word<MODE>(a, b0 + wb);
-                }
-            }
-            ones += (w0 + lane < words ? __popc(ua) : 0u) + (w0 + 64 + lane < words ? __popc(ub) : 0u);
+        for (uint32_t w = lane; w < words; w += 64) {
+            uint32_t u = 0xFFFFFFFFu;
+            for (uint32_t r = 0; r < c.lr; ++r)
+                u &= decode_ldc<MODE>(a, load_ldc<MODE>(a, (((r << c.log2lc) | ldc_col(h, r, c)) << (c.log2k - 5)) + w));
+            ones += __popc(u);
         }
-        ones = wave_sum(ones);
-        const uint32_t z0 = (1u << c.log2k) - ones;
-        if (lane == 0 && z0 <= c.z_theta) {
-            const uint32_t slot = atomicAdd(&a.counters[0], 1u);
-            if (slot < a.rec_cap) {
-                a.rec[2 * slot] = h;
-                a.rec[2 * slot + 1] = z0;
-            }
-        }
+        const uint32_t z0 = (1u << c.log2k) - wave_sum(ones);
+        if (lane == 0 && z0 <= c.z_theta) report(a, h, z0);
     }
 }
 
-template <int MODE>
-__device__ void filter_queue(const CloseArgs &a, const Consts &c, const uint32_t *queue, uint32_t qn, uint32_t lane) {
-    if (MODE != kCloseBits) {
-        filter_queue_counters<MODE>(a, c, queue, qn, lane);
-        return;
-    }
-    constexpr uint32_t G = 16, W = 8, RB = 2;
-    const uint32_t words = 1u << (c.log2k - 5);
-    const uint32_t grp = lane / G, sub = lane % G;
-    for (uint32_t e0 = 0; e0 < qn; e0 += 64 / G) {
-        const bool live = e0 + grp < qn;
-        const uint32_t h = queue[live ? e0 + grp : e0];
-        uint32_t ones = 0;
-        for (uint32_t w0 = 0; w0 < words; w0 += G * W) {
-            uint32_t u[W];
-#pragma unroll
-            for (uint32_t k = 0; k < W; ++k) u[k] = 0xFFFFFFFFu;
-            for (uint32_t r0 = 0; r0 < c.lr; r0 += RB) {
-                uint32_t v[RB][W];
-#pragma unroll
-                for (uint32_t rr = 0; rr < RB; ++rr) {
-                    const uint32_t r = r0 + rr < c.lr ? r0 + rr : c.lr - 1;   // a repeated row is harmless
-                    const uint32_t base = ((r << c.log2lc) | ldc_col(h, r, c)) << (c.log2k - 5);
-#pragma unroll
-                    for (uint32_t k = 0; k < W; ++k) {
-                        const uint32_t w = w0 + k * G + sub;
-                        v[rr][k] = load_ldc_word<MODE>(a, base + (w < words ? w : words - 1));
-                    }
-                }
-#pragma unroll
-                for (uint32_t rr = 0; rr < RB; ++rr)
-#pragma unroll
-                    for (uint32_t k = 0; k < W; ++k) u[k] &= v[rr][k];
-            }
-#pragma unroll
-            for (uint32_t k = 0; k < W; ++k)
-                if (w0 + k * G + sub < words) ones += __popc(u[k]);
-        }
-        for (uint32_t o = G / 2; o > 0; o >>= 1) ones += __shfl_xor(ones, o, 64);
-        const uint32_t z0 = (1u << c.log2k) - ones;
-        if (live && sub == 0 && z0 <= c.z_theta) {
-            uint32_t slot = atomicAdd(&a.counters[0], 1u);
-            if (slot < a.rec_cap) {
-                a.rec[2 * slot] = h;
-                a.rec[2 * slot + 1] = z0;
-            }
-        }
-    }
-}
-
-template <int MODE, int BLOCK>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(5))) void k_close(Consts c, CloseArgs a) {
+// One wavefront per work item, an SEA or one of its 2^parts_log2 parts.  An SEA's words go straight
+// from memory to registers (those of the next item are loaded before the current one is worked on);
+// hot SEs are found four at a time by a bytewise popcount and listed in LDS in the SEA's order, so that
+// a row's are neighbours and every wavefront of an SEA sees the same list.
+// Candidates wait in a queue per wavefront; when the workgroup's items are done, its wavefronts share
+// the filtering of all of them, so that an SEA with many candidates does not hold up one wavefront.
+// Bound by latency: a round trip for the SEAs, one or two per candidate filtered.
+// (64 Mi pairs, 16384 SEAs, 16 700 candidates: 39.6 us and a separate kernel of 4 us that copied the
+// counts and records out, now 25 us with both; 8 routers, 36 000 candidates 87 + 4 -> 44; a sliding
+// window of AT counters 89 + 4 and 17 for a bit view of the SEAV -> 64; of stamps, 1024 SEAs, 67 + 4
+// and 5 -> 28.)
+// RMAX: SR itself when it is 4, else 8 (the rows' registers).
+template <int MODE, int BLOCK, int RMAX>
+__global__ __launch_bounds__(BLOCK) void k_close(Consts c, CloseArgs a) {
     extern __shared__ uint32_t lds[];
     constexpr uint32_t NW = BLOCK / 64;
-    const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
-    const uint32_t per_wave = c.sr * a.list_stride + a.qcap + a.stage_words;
-    uint32_t *lists = lds + wid * per_wave;      // row i: entries (cell << 8 | SE value)
-    uint32_t *queue = lists + c.sr * a.list_stride;
-    uint8_t *sea8 = reinterpret_cast<uint8_t *>(queue + a.qcap);   // the SEA of the current RP
-    const bool staged = a.stage_words != 0;
+    constexpr uint32_t U = MODE == kCloseBits ? 8 : 2;   // words in flight per lane
+    __shared__ uint32_t wave_q[NW], wave_cand[NW];
+    const uint32_t sr = RMAX == 4 ? 4u : c.sr;
+    const uint32_t lane = threadIdx.x & 63u, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t per_wave = close_wave_words(c.sea_bytes, a.qcap);
+    // hot SEs row after row: (the LP bits each stands for, or, of more than 24, its cell) << 8 | value
+    uint32_t *list = lds + wid * per_wave;
+    const bool lp24 = c.L <= 24u;
+    uint32_t *queue = list + c.sea_bytes;
     const uint64_t lane_lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     const uint64_t lmask = (c.L == 32) ? 0xFFFFFFFFull : ((1ull << c.L) - 1ull);
-    uint32_t n_cand = 0;
+    uint32_t n_cand = 0, qn = 0;
     // work items: (SEA, part); the 2^parts_log2 parts of a SEA take interleaved shares of its tuples
-    // (or of its LPs), so they find disjoint candidates
+    // (or of its LPs), or of the candidates when the tuples are few: disjoint candidates either way
     const uint32_t P = 1u << a.parts_log2, part_mask = P - 1u;
-    const uint64_t n_items = (uint64_t)a.n_rp << a.parts_log2;
+    const uint32_t n_items = a.n_rp << a.parts_log2, step = gridDim.x * NW;   // at most 2^30
+    // an SEA's words; the last one is read from the SEA's last four bytes
+    const uint32_t sea_words = (c.sea_bytes + 3) / 4, last_byte = c.sea_bytes - 4;
+    auto word_byte = [&](uint32_t w) { return w < sea_words ? min(4 * w, last_byte) : 0u; };
+    RawWord<MODE> raw[U];
+    auto fetch = [&](uint32_t wi, uint32_t w0) {
+        const uint32_t sea = (wi >> a.parts_log2) * c.sea_bytes;   // below 2^29
+#pragma unroll
+        for (uint32_t k = 0; k < U; ++k)
+            if (w0 + k * 64 < sea_words) raw[k] = load_sea<MODE>(a, sea + word_byte(w0 + k * 64 + lane));
+    };
+    auto flush = [&]() {
+        wave_lds_sync();
+        filter_queue<MODE>(a, c, queue, qn, lane);
+        n_cand += qn;
+        qn = 0;
+        wave_lds_sync();
+    };
 
-    for (uint64_t wi = (uint64_t)blockIdx.x * NW + wid; wi < n_items; wi += (uint64_t)gridDim.x * NW) {
-        const uint32_t rp = (uint32_t)(wi >> a.parts_log2), part = (uint32_t)wi & part_mask;
-        const uint64_t sea = (uint64_t)rp * c.sea_bytes;
-        // stage the whole SEA in LDS (when it fits) with 32-bit loads, up to eight in flight per lane
-        // (an SEA is a whole number of words, rows of 2^IBN >= 4 bytes, and so is its offset)
-        auto se_at = [&](uint32_t byte) -> uint32_t { return staged ? sea8[byte] : load_se<MODE>(a, sea + byte); };
-        const uint32_t sea_words = c.sea_bytes >> 2;
-        const uint32_t *sea32 = reinterpret_cast<const uint32_t *>(a.seav + sea);
-        uint32_t *stage32 = reinterpret_cast<uint32_t *>(sea8);
-        for (uint32_t w0 = 0; staged && w0 < sea_words; w0 += 64 * 8) {
-            uint32_t v[8];
+    uint32_t wi = blockIdx.x * NW + wid;
+    if (wi < n_items) fetch(wi, 0);
+    for (; wi < n_items; wi += step) {
+        const uint32_t rp = wi >> a.parts_log2, part = wi & part_mask, sea = rp * c.sea_bytes;
+        uint32_t n_hot = 0;
+        for (uint32_t w0 = 0; w0 < sea_words; w0 += 64 * U) {
+            uint32_t v[U];
 #pragma unroll
-            for (uint32_t k = 0; k < 8; ++k) {
+            for (uint32_t k = 0; k < U; ++k) {
                 const uint32_t w = w0 + k * 64 + lane;
-                v[k] = w0 + k * 64 < sea_words ? sea32[w < sea_words ? w : sea_words - 1] : 0u;
-            }
-#pragma unroll
-            for (uint32_t k = 0; k < 8; ++k)
-                if (w0 + k * 64 + lane < sea_words) stage32[w0 + k * 64 + lane] = v[k];
-        }
-        wave_lds_sync();
-        // Row loops run over kMaxRows with constant indices (guarded by the row count), so the
-        // per-row arrays stay in registers and the row constants are read from the kernel
-        // arguments directly.
-        uint32_t cnt[kMaxRows];
-        bool empty = false;
-#pragma unroll
-        for (uint32_t i = 0; i < (uint32_t)kMaxRows; ++i) {
-            cnt[i] = 1;
-            if (i >= c.sr || empty) continue;
-            const uint32_t cells = 1u << c.ibn[i];
-            uint32_t n_hot = 0;
-            for (uint32_t c0 = 0; c0 < cells; c0 += 64) {
-                const uint32_t cell = c0 + lane;
-                uint32_t v = cell < cells ? se_at(c.row_off[i] + cell) : 0u;
-                const bool hot = __popc(v) >= kSeHot;
-                const uint64_t bal = __ballot(hot);
-                if (hot) lists[i * a.list_stride + n_hot + __popcll(bal & lane_lt)] = (cell << 8) | v;
-                n_hot += (uint32_t)__popcll(bal);
-            }
-            cnt[i] = n_hot;
-            empty = n_hot == 0;
-        }
-        if (empty) continue;
-        wave_lds_sync();
-        uint64_t total = 1;
-#pragma unroll
-        for (uint32_t i = 0; i < (uint32_t)kMaxRows; ++i) total *= cnt[i];
-        uint32_t qn = 0;
-        if (total <= lmask + 1ull) {
-            // the product CIS of the hot lists (Section 3.2), one tuple per lane.  A lane's tuple
-            // index is kept as mixed-radix digits (row 0 least significant) and advanced by 64 each
-            // round by adding the digits of 64, computed once per SEA: no division in the loop.
-            uint32_t dg[kMaxRows], st[kMaxRows];
-            {
-                uint32_t rem = part * 64u + lane, inc = 64u * P;
-#pragma unroll
-                for (uint32_t i = 0; i < (uint32_t)kMaxRows; ++i) {
-                    dg[i] = rem % cnt[i];
-                    rem /= cnt[i];
-                    st[i] = inc % cnt[i];
-                    inc /= cnt[i];
+                v[k] = 0;
+                if (w0 + k * 64 < sea_words) {
+                    v[k] = decode_raw<MODE>(a, raw[k]);
+                    v[k] = w < sea_words ? v[k] >> (8 * (4 * w - word_byte(w))) : 0u;
                 }
             }
-            for (uint64_t u0 = (uint64_t)part * 64u; u0 < total; u0 += 64u * P) {
-                const uint64_t u = u0 + lane;
+            if (w0 + 64 * U < sea_words) fetch(wi, w0 + 64 * U);
+            else if (wi + step < n_items) fetch(wi + step, 0);
+#pragma unroll
+            for (uint32_t k = 0; k < U; ++k) {
+                if (w0 + k * 64 >= sea_words) continue;
+                // bytes of weight >= kSeHot
+                uint32_t t = v[k] - ((v[k] >> 1) & 0x55555555u);
+                t = (t & 0x33333333u) + ((t >> 2) & 0x33333333u);
+                t = (t + (t >> 4)) & 0x0F0F0F0Fu;
+                uint32_t hot = (t + (0x80u - kSeHot) * 0x01010101u) & 0x80808080u;
+                if (!__ballot(hot != 0)) continue;
+                // places by lane: a prefix sum of the lanes' counts (0 to 4), one bit at a time
+                const uint32_t n = __popc(hot);
+                const uint64_t b0 = __ballot(n & 1u), b1 = __ballot(n & 2u), b2 = __ballot(n & 4u);
+                uint32_t pos = n_hot + (uint32_t)(__popcll(b0 & lane_lt) + 2 * __popcll(b1 & lane_lt) + 4 * __popcll(b2 & lane_lt));
+                n_hot += (uint32_t)(__popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2));
+                const uint32_t byte0 = 4 * (w0 + k * 64 + lane);
+                while (hot) {
+                    const uint32_t j = (uint32_t)__builtin_ctz(hot) >> 3;
+                    hot &= hot - 1;
+                    list[pos++] = (byte0 + j) << 8 | ((v[k] >> (8 * j)) & 0xFFu);
+                }
+            }
+        }
+        if (n_hot < sr) continue;
+        wave_lds_sync();
+        // the rows' parts of the list: begin[i] = entries before row i; cells become LP bits (Eq. 3).
+        // Row loops run over RMAX with constant indices (guarded by the row count), so the per-row
+        // arrays stay in registers and the row constants are read from the kernel arguments directly.
+        uint32_t begin[RMAX];
+#pragma unroll
+        for (uint32_t i = 0; i < (uint32_t)RMAX; ++i) begin[i] = 0;
+        for (uint32_t e0 = 0; e0 < n_hot; e0 += 64) {
+            const bool in = e0 + lane < n_hot;
+            const uint32_t e = list[in ? e0 + lane : e0], byte = e >> 8;
+            uint32_t off = 0, isb = c.isb[0];
+#pragma unroll
+            for (uint32_t i = 1; i < (uint32_t)RMAX; ++i) {
+                if (i >= sr) continue;
+                const bool past = byte >= c.row_off[i];
+                off = past ? c.row_off[i] : off;
+                isb = past ? c.isb[i] : isb;
+                begin[i] += (uint32_t)__popcll(__ballot(in && !past));
+            }
+            const uint32_t cell = byte - off;
+            if (in) list[e0 + lane] = (lp24 ? row_bits_in_lp(cell, isb, c.L) : cell) << 8 | (e & 0xFFu);
+        }
+        uint32_t cnt[RMAX];
+        uint64_t prod = 1;
+#pragma unroll
+        for (uint32_t i = 0; i < (uint32_t)RMAX; ++i) {
+            cnt[i] = 1;
+            if (i >= sr) continue;
+            const bool last = i + 1 >= (uint32_t)RMAX || i + 1 >= sr;
+            cnt[i] = (last ? n_hot : begin[i + 1 < (uint32_t)RMAX ? i + 1 : i]) - begin[i];
+            prod = min(prod * cnt[i], 1ull << 33);   // (past every LP count)
+        }
+        if (prod == 0) continue;
+        wave_lds_sync();
+        if (prod <= lmask) {
+            const uint32_t total = (uint32_t)prod;
+            // the product CIS of the hot lists (Section 3.2), one tuple per lane: the tuple number's
+            // mixed-radix digits (row 0 least significant) pick its entries.  A digit's quotient is
+            // exact in single precision below 2^20: (u + 1/2) / cnt is at least 1 / (2 cnt) from an
+            // integer, and the product's relative error is below 2^-22.  (Integer divisions took three
+            // quarters of this kernel: 64 Mi pairs, 16384 SEAs of one tuple on average.)  Few tuples
+            // are enumerated by every part, which keeps its share of the candidates: their filtering
+            // is what takes time then.
+            const bool all = total <= 256u, small = total <= (1u << 20);
+            const uint32_t first = all ? 0u : part * 64u, stride = all ? 64u : 64u * P;
+            float rcp[RMAX];
+#pragma unroll
+            for (uint32_t i = 0; i < (uint32_t)RMAX; ++i) rcp[i] = __builtin_amdgcn_rcpf((float)cnt[i]);
+            uint32_t found = 0;
+            uint32_t u0 = first, rounds = first < total ? ((total - 1 - first) >> (all ? 6u : 6u + a.parts_log2)) + 1 : 0u;
+            for (; rounds; --rounds, u0 += stride) {
                 bool cand = false;
                 uint32_t h = 0;
-                if (u < total) {
-                    uint32_t lp = 0, seu = 0xFFu;
-                    uint32_t ci[kMaxRows];
+                if (lane < total - u0) {
+                    uint32_t u = u0 + lane, lp = 0, seu = 0xFFu;
+                    uint32_t bits[RMAX];
 #pragma unroll
-                    for (uint32_t i = 0; i < (uint32_t)kMaxRows; ++i) {
-                        ci[i] = 0;
-                        if (i >= c.sr) continue;
-                        uint32_t e = lists[i * a.list_stride + dg[i]];
-                        ci[i] = e >> 8;
-                        seu &= e & 0xFFu;
-                        lp |= row_bits_in_lp(ci[i], c.isb[i], c.L);
+                    for (uint32_t i = 0; i < (uint32_t)RMAX; ++i) {
+                        bits[i] = 0;
+                        if (i >= sr) continue;
+                        uint32_t q = 0;
+                        if (i + 1 < sr) q = small ? (uint32_t)(((float)u + 0.5f) * rcp[i]) : u / cnt[i];
+                        const uint32_t e = list[begin[i] + u - q * cnt[i]];
+                        u = q;
+                        bits[i] = lp24 ? e >> 8 : row_bits_in_lp(e >> 8, c.isb[i], c.L);
+                        seu &= e;
+                        lp |= bits[i];
                     }
-                    // Eq. 3: the rebuilt LP must give back every row index (overlap bits agree)
-                    bool ok = __popc(seu) >= kSeHot;
+                    // Eq. 3: the rebuilt LP must give back every row's bits (overlap bits agree)
+                    uint32_t differ = 0;
 #pragma unroll
-                    for (uint32_t i = 0; i < (uint32_t)kMaxRows; ++i)
-                        if (i < c.sr) ok = ok && (row_index(lp, c.isb[i], c.ibn[i], c.L) == ci[i]);
-                    if (ok) {
-                        cand = true;
-                        h = (uint32_t)(((uint64_t)lp << c.r) | rp);
-                    }
+                    for (uint32_t i = 0; i < (uint32_t)RMAX; ++i)
+                        if (i < sr) differ |= (lp & a.lp_mask[i]) ^ bits[i];
+                    cand = __popc(seu) >= kSeHot && differ == 0;
+                    h = (uint32_t)(((uint64_t)lp << c.r) | rp);
                 }
-                // advance the digits by 64 P; each sum stays below twice its radix, so it wraps at
-                // most once (rows past the row count have radix 1 and stay 0)
-                uint32_t carry = 0;
-#pragma unroll
-                for (uint32_t i = 0; i < (uint32_t)kMaxRows; ++i) {
-                    const uint32_t d = dg[i] + st[i] + carry;
-                    carry = d >= cnt[i] ? 1u : 0u;
-                    dg[i] = carry ? d - cnt[i] : d;
+                uint64_t bal = __ballot(cand);
+                if (!bal) continue;
+                if (all && P > 1) {
+                    const uint32_t j = found + (uint32_t)__popcll(bal & lane_lt);
+                    found += (uint32_t)__popcll(bal);
+                    cand = cand && (j & part_mask) == part;
+                    bal = __ballot(cand);
                 }
-                const uint64_t bal = __ballot(cand);
                 if (cand) queue[qn + __popcll(bal & lane_lt)] = h;
                 qn += (uint32_t)__popcll(bal);
-                if (qn + 64 > a.qcap) {
-                    wave_lds_sync();
-                    filter_queue<MODE>(a, c, queue, qn, lane);
-                    n_cand += qn;
-                    qn = 0;
-                }
+                if (qn + 64 > a.qcap) flush();
             }
         } else {
-            // more tuples than hosts in this SEA: test every LP directly (the candidate definition)
+            // as many tuples as hosts in this SEA, or more: test every LP directly (the candidate definition)
             for (uint64_t l0 = (uint64_t)part * 64u; l0 <= lmask; l0 += 64u * P) {
                 const uint64_t l = l0 + lane;
                 bool cand = false;
                 if (l <= lmask) {
                     uint32_t seu = 0xFFu;
 #pragma unroll
-                    for (uint32_t i = 0; i < (uint32_t)kMaxRows; ++i)
-                        if (i < c.sr) seu &= se_at(c.row_off[i] + row_index((uint32_t)l, c.isb[i], c.ibn[i], c.L));
+                    for (uint32_t i = 0; i < (uint32_t)RMAX; ++i)
+                        if (i < sr)
+                            seu &= load_se<MODE>(a, sea + c.row_off[i] + row_index((uint32_t)l, c.isb[i], c.ibn[i], c.L));
                     cand = __popc(seu) >= kSeHot;
                 }
                 const uint64_t bal = __ballot(cand);
                 if (cand) queue[qn + __popcll(bal & lane_lt)] = (uint32_t)((l << c.r) | rp);
                 qn += (uint32_t)__popcll(bal);
-                if (qn + 64 > a.qcap) {
-                    wave_lds_sync();
-                    filter_queue<MODE>(a, c, queue, qn, lane);
-                    n_cand += qn;
-                    qn = 0;
-                }
+                if (qn + 64 > a.qcap) flush();
             }
         }
-        wave_lds_sync();
-        filter_queue<MODE>(a, c, queue, qn, lane);
-        n_cand += qn;
-        wave_lds_sync();
     }
-    // one global atomic per workgroup: atomics on one address are serialized device-wide
-    __shared__ uint32_t wave_cand[NW];
-    if (lane == 0) wave_cand[wid] = n_cand;
+    // the candidates left in the wavefronts' queues, shared out among them
+    if (lane == 0) {
+        wave_q[wid] = qn;
+        wave_cand[wid] = n_cand + qn;
+    }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t sum = 0;
-        for (uint32_t w = 0; w < NW; ++w) sum += wave_cand[w];
-        if (sum) atomicAdd(&a.counters[1], sum);
+    uint32_t left = 0, sum = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < NW; ++w) {
+        left += __builtin_amdgcn_readfirstlane(wave_q[w]);
+        sum += wave_cand[w];
     }
+    if (left) {
+        auto get = [&](uint32_t e) {
+            uint32_t w = 0;
+#pragma unroll
+            for (uint32_t i = 0; i + 1 < NW; ++i) {   // past the first w queues
+                const bool past = w == i && e >= wave_q[i];
+                e -= past ? wave_q[i] : 0u;
+                w += past ? 1u : 0u;
+            }
+            return lds[w * per_wave + c.sea_bytes + e];
+        };
+        filter_candidates<MODE>(a, c, get, left, wid, NW, lane);
+    }
+    // Every wavefront's records have been written through to host memory before its workgroup counts
+    // itself finished, so no cache has to be written back (a release per workgroup cost 11 us over
+    // 1280 of them); the last workgroup publishes the counts and, last of all, the close's sequence
+    // number, which the host may poll instead of waiting for the stream.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x) return;
+    auto finish = [](uint64_t *p, uint64_t v, uint32_t members, uint32_t &cand) {
+        const uint64_t old = __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + v;
+        cand = (uint32_t)(old >> 32);
+        if ((uint32_t)old != members) return false;
+        *p = 0;   // for the next close (nobody else reads it in this one)
+        return true;
+    };
+    const uint32_t grp = blockIdx.x % kCloseGroups, groups = min(gridDim.x, kCloseGroups);
+    uint32_t cand;
+    if (!finish(a.counts + (1 + grp) * kCloseLine, (uint64_t)sum << 32 | 1u, (gridDim.x - grp + kCloseGroups - 1) / kCloseGroups, cand))
+        return;
+    if (!finish(a.counts, (uint64_t)cand << 32 | 1u, groups, cand)) return;
+    const uint32_t n = __hip_atomic_load(&a.counters[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t seq = a.counters[2] + 1u;
+    a.counters[0] = 0u;
+    a.counters[2] = seq;
+    __hip_atomic_store(a.host_out, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(a.host_out + 1, cand, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __hip_atomic_store(a.host_out + 2, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// After k_close (the launch boundary orders every workgroup's records before this): the counts
-// and the first records go to host-visible memory, so that no copy follows, and the counters are
-// zeroed for the next launch.  One workgroup.
-// Last of all it writes the close's sequence number (counters[2] + 1, kept in counters[2]) to the
-// host, after a system-scope fence, so that the host may poll that word instead of waiting for the
-// stream.
-__global__ __launch_bounds__(256) void k_close_out(CloseArgs a) {
-    const uint32_t n = a.counters[0], cand = a.counters[1];
-    const uint32_t m = min(min(n, a.rec_cap), a.host_recs);
-    const uint2 *src = reinterpret_cast<const uint2 *>(a.rec);
-    uint2 *dst = reinterpret_cast<uint2 *>(a.host_out + 4);
-    for (uint32_t i = threadIdx.x; i < m; i += 256) dst[i] = src[i];
-    __threadfence_system();   // this thread's records reach the host before the sequence number
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint32_t seq = a.counters[2] + 1u;
-        a.host_out[0] = n;
-        a.host_out[1] = cand;
-        a.counters[0] = 0u;
-        a.counters[1] = 0u;
-        a.counters[2] = seq;
-        __threadfence_system();
-        __hip_atomic_store(a.host_out + 2, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
-}
-
+// The instance for a mode, a workgroup size and a row count.
+typedef void (*CloseKernel)(Consts, CloseArgs);
+template <int MODE, int BLOCK>
+static CloseKernel close_kernel_rows(uint32_t sr) { return sr == 4 ? k_close<MODE, BLOCK, 4> : k_close<MODE, BLOCK, 8>; }
 template <int MODE>
-static uint32_t close_occupancy(uint32_t block, uint32_t lds_bytes) {
+static CloseKernel close_kernel_block(uint32_t block, uint32_t sr) {
+    return block == 256 ? close_kernel_rows<MODE, 256>(sr)
+         : block == 128 ? close_kernel_rows<MODE, 128>(sr)
+         : block == 64  ? close_kernel_rows<MODE, 64>(sr) : nullptr;
+}
+static CloseKernel close_kernel(int mode, uint32_t block, uint32_t sr) {
+    return mode == kCloseStamps ? close_kernel_block<kCloseStamps>(block, sr)
+         : mode == kCloseAt     ? close_kernel_block<kCloseAt>(block, sr)
+                                : close_kernel_block<kCloseBits>(block, sr);
+}
+
+uint32_t close_blocks_per_cu(int mode, uint32_t block, uint32_t sr, uint32_t lds_bytes) {
     int n = 0;
-    hipError_t e = hipErrorInvalidValue;
-    if (block == 256) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_close<MODE, 256>, 256, lds_bytes);
-    else if (block == 128) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_close<MODE, 128>, 128, lds_bytes);
-    else if (block == 64) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_close<MODE, 64>, 64, lds_bytes);
+    const CloseKernel k = close_kernel(mode, block, sr);
+    const hipError_t e =
+        k ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(k), (int)block, lds_bytes)
+          : hipErrorInvalidValue;
     return (e == hipSuccess && n > 0) ? (uint32_t)n : 1u;
 }
 
-uint32_t close_blocks_per_cu(int mode, uint32_t block, uint32_t lds_bytes) {
-    if (mode == kCloseStamps) return close_occupancy<kCloseStamps>(block, lds_bytes);
-    if (mode == kCloseAt) return close_occupancy<kCloseAt>(block, lds_bytes);
-    return close_occupancy<kCloseBits>(block, lds_bytes);
-}
-
-template <int MODE>
-static hipError_t launch_close_mode(const Consts &c, const CloseArgs &a, uint32_t block, uint32_t grid, uint32_t lds,
-                                    hipStream_t s) {
-    if (block == 256) hipLaunchKernelGGL((k_close<MODE, 256>), dim3(grid), dim3(256), lds, s, c, a);
-    else if (block == 128) hipLaunchKernelGGL((k_close<MODE, 128>), dim3(grid), dim3(128), lds, s, c, a);
-    else if (block == 64) hipLaunchKernelGGL((k_close<MODE, 64>), dim3(grid), dim3(64), lds, s, c, a);
-    else return hipErrorInvalidConfiguration;
-    return hipGetLastError();
-}
-
 hipError_t launch_close(const Consts &c, const CloseArgs &a, int mode, uint32_t block, uint32_t grid, hipStream_t s) {
-    const uint32_t lds = (block / 64) * (c.sr * a.list_stride + a.qcap + a.stage_words) * 4u;
-    hipError_t e = hipErrorInvalidValue;
-    if (mode == kCloseStamps) e = launch_close_mode<kCloseStamps>(c, a, block, grid, lds, s);
-    else if (mode == kCloseAt) e = launch_close_mode<kCloseAt>(c, a, block, grid, lds, s);
-    else if (mode == kCloseBits) e = launch_close_mode<kCloseBits>(c, a, block, grid, lds, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_close_out, dim3(1), dim3(256), 0, s, a);
+    const CloseKernel k = close_kernel(mode, block, c.sr);
+    if (!k) return hipErrorInvalidConfiguration;
+    const uint32_t lds = (block / 64) * close_wave_words(c.sea_bytes, a.qcap) * 4u;
+    hipLaunchKernelGGL(k, dim3(grid), dim3(block), lds, s, c, a);
     return hipGetLastError();
 }
 

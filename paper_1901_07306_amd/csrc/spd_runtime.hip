@@ -43,15 +43,14 @@ constexpr uint32_t kRecChunk = 4096;   // records copied back together with the 
 
 // Device and pinned host buffers of one end-of-window pass.
 struct CloseBuf {
-    // one device buffer: 4 counters ([0] reported, [1] candidates, both zero between launches;
-    // [2] the sequence number of the last close) then the (ip, z0) records.  The end-of-window
-    // launch itself copies the counters and the first kRecChunk records to h_counters, and the
-    // sequence number last.
+    // one device buffer: 4 counters ([0] reported, zero between launches; [2] the sequence number of
+    // the last close) then the (ip, z0) records.  The end-of-window launch itself writes the counts
+    // ([0] reported, [1] candidates) and the first kRecChunk records to h_counters, and the sequence
+    // number last.
     uint32_t *counters = nullptr;
     uint32_t *rec = nullptr;          // counters + 4
     uint32_t rec_cap = 0;
     uint32_t *h_counters = nullptr;   // pinned and mapped, same layout, kRecChunk records
-    uint8_t *seav_bits = nullptr;     // sliding: the bit view of the SEAV counters the close reads
     uint32_t *d_counters = nullptr;   // h_counters' device address
     uint32_t *h_rec = nullptr;        // pinned, all records when there are more than kRecChunk
     uint32_t h_rec_cap = 0;
@@ -114,6 +113,8 @@ struct spd_ctx {
     uint32_t close_per_cu[3] = {0, 0, 0};   // resident end-of-window workgroups per CU (64, 128, 256 lanes)
     uint32_t list_parity = 0;        // region layout: which of two tile-list counts the next launch uses
     CloseBuf cbuf;                  // end-of-window buffers of spd_close_window
+    uint64_t *close_counts = nullptr;   // finished workgroups of the running close (a context's closes
+                                        // run one after another)
     Slot *merge_into = nullptr;     // spd_scan_batches_merge: the global slot, while its scan runs
     bool merge_group = false;       // the region launch being enqueued covers the whole merged call
     bool merged = false;            // the merge was fused into that launch's apply phase
@@ -1079,9 +1080,10 @@ spd_status close_buf_init(spd_ctx *ctx, CloseBuf &cb) {
         spd_status st = close_rec_alloc(ctx, cb, kRecInit);
         if (st) return st;
     }
-    if (ctx->sliding && !cb.seav_bits) {
-        spd_status st = dev_alloc(ctx, &cb.seav_bits, ctx->seav_alloc);
+    if (!ctx->close_counts) {
+        spd_status st = dev_alloc(ctx, &ctx->close_counts, kCloseCountBytes);
         if (st) return st;
+        SPD_HIP(ctx, hipMemset(ctx->close_counts, 0, kCloseCountBytes));   // once; each launch leaves them zero
     }
     if (!cb.h_counters) {
         SPD_HIP(ctx, hipHostMalloc((void **)&cb.h_counters, 16 + (uint64_t)kRecChunk * 8, hipHostMallocMapped));
@@ -1096,7 +1098,6 @@ void close_buf_free(spd_ctx *ctx, CloseBuf &cb) {
     cb.graph = nullptr;
     dev_free(ctx, &cb.counters, 16 + (uint64_t)cb.rec_cap * 8);
     cb.rec = nullptr;
-    dev_free(ctx, &cb.seav_bits, ctx->seav_alloc);
     if (cb.h_counters) (void)hipHostFree(cb.h_counters);
     if (cb.h_rec) (void)hipHostFree(cb.h_rec);
     cb.h_counters = nullptr;
@@ -1110,72 +1111,59 @@ int close_mode(const spd_ctx *ctx) { return ctx->at ? kCloseAt : ctx->sliding ? 
 // Arguments and launch shape of the end-of-window kernel for one slot.
 spd_status close_args(spd_ctx *ctx, const Slot &sl, const CloseBuf &cb, CloseArgs *a, uint32_t *block, uint32_t *grid) {
     *a = CloseArgs{};
-    a->seav = ctx->sliding ? cb.seav_bits : sl.seav;
+    a->seav = sl.seav;
+    a->seav_ts = sl.seav_ts;
+    a->seav_at = sl.seav_at;
     a->ldca = sl.ldca;
     a->ldca_ts = sl.ldca_ts;
     a->ldca_at = sl.ldca_at;
-    a->at_ct = at_code(ctx->slice);
-    a->at_k = ctx->K;
+    a->at = at_view(at_code(ctx->slice), ctx->K);
     if (ctx->sliding) {
         const int64_t lo = (int64_t)ctx->slice - (int64_t)ctx->K + 2;
         a->thr = lo < 1 ? 1u : (uint32_t)lo;
     }
     a->counters = cb.counters;
+    a->counts = ctx->close_counts;
     a->rec = cb.rec;
     a->rec_cap = cb.rec_cap;
     a->host_out = cb.d_counters;
     a->host_recs = std::min(cb.rec_cap, kRecChunk);
     a->n_rp = 1u << ctx->p.r;
-    uint32_t max_ibn = 0;
-    for (uint32_t i = 0; i < ctx->p.sr; ++i) max_ibn = std::max(max_ibn, ctx->d.ibn[i]);
-    a->list_stride = 1u << max_ibn;
     a->qcap = 256;
-    // each wavefront stages its SEA in LDS when that fits next to the hot lists (else it reads
-    // the SEA from global memory)
-    const uint64_t lists = (uint64_t)ctx->p.sr * a->list_stride + a->qcap;
-    const uint64_t stage = (ctx->d.sea_bytes + 3) / 4;
-    a->stage_words = (lists + stage) * 4ull <= kMaxLds ? (uint32_t)stage : 0u;
-    const uint64_t per_wave = lists + a->stage_words;
+    for (uint32_t i = 0; i < ctx->p.sr; ++i)
+        a->lp_mask[i] = row_bits_in_lp((1u << ctx->d.ibn[i]) - 1u, ctx->d.isb[i], ctx->c.L);
+    const uint64_t per_wave = close_wave_words(ctx->c.sea_bytes, a->qcap);   // LDS words
     uint32_t b = ctx->tune.close_block;
     while (b > 64 && (b / 64) * per_wave * 4ull > kMaxLds) b /= 2;
     if ((b / 64) * per_wave * 4ull > kMaxLds)
         return fail(ctx, SPD_E_INVALID, "SEA rows too large for the end-of-window kernel");
     const uint32_t waves = b / 64;
     *block = b;
-    // one round of resident workgroups; each wavefront then takes (SEA, part) items round robin.
-    // With fewer SEAs than resident wavefronts, each SEA's candidate search is split into parts
-    // (a power of two, at most 64) so that every wavefront has work.
+    // one round of resident workgroups; each wavefront then takes (SEA, part) items round robin
     if (!ctx->close_per_cu[b / 128])
-        ctx->close_per_cu[b / 128] = close_blocks_per_cu(close_mode(ctx), b, (uint32_t)((b / 64) * per_wave * 4));
+        ctx->close_per_cu[b / 128] = close_blocks_per_cu(close_mode(ctx), b, ctx->p.sr, (uint32_t)((b / 64) * per_wave * 4));
     const uint64_t resident = (uint64_t)ctx->n_cu * ctx->close_per_cu[b / 128];
+    // With few SEAs, each SEA's candidate search is split into parts (a power of two, at most 64) as
+    // long as there are at most two wavefronts per SIMD: every part reads its whole SEA again (64 SEAs
+    // of 2 KiB, 1,000,000 pairs: 11.6 us with 32 parts, 15.5 with 64).  In
+    // sliding mode every SEA is split at least in two: its candidates' filters read 8 or 16 times the
+    // bytes, and the split halves the longest run of one wavefront (65.8 -> 63.7 us, 16384 SEAs).
     a->parts_log2 = 0;
-    while (a->parts_log2 < 6 && ((uint64_t)a->n_rp << (a->parts_log2 + 1)) <= resident * waves) a->parts_log2++;
-    // In sliding mode a candidate's filter reads the counters behind its LDCs (8 or 16 bits a bit),
-    // so filtering, not the SEA, dominates a work item: every SEA is split at least in two, which
-    // halves the longest run of candidates one wavefront filters.
+    while (a->parts_log2 < 6 && ((uint64_t)a->n_rp << (a->parts_log2 + 1)) <= 8ull * ctx->n_cu) a->parts_log2++;
     if (ctx->sliding && a->parts_log2 < 1) a->parts_log2 = 1;
-    // With few SEAs (small sketches), one level finer than the resident wavefronts ask for: the
-    // largest SEA's share then bounds the pass less (64 SEAs of 2 KiB, 1,000,000 pairs: the close
-    // 21.7 -> 20.5 us).
-    if (a->n_rp <= 1024 && a->parts_log2 < 6) a->parts_log2++;
     const uint64_t want = (((uint64_t)a->n_rp << a->parts_log2) + waves - 1) / waves;
     *grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(want, resident));
     return SPD_OK;
 }
 
-// The device part of the end of window: k_close, then k_close_out, which leaves the counters and
-// the first kRecChunk records in pinned host memory (and the device counters zero).  Asynchronous
-// on s.
+// The device part of the end of window: k_close, which leaves the counts and the first kRecChunk
+// records in pinned host memory (and the device counters zero).  Asynchronous on s.
 spd_status close_launch_ops(spd_ctx *ctx, const Slot &sl, CloseBuf &cb, hipStream_t s) {
     CloseArgs a;
     uint32_t block, grid;
     spd_status st = close_args(ctx, sl, cb, &a, &block, &grid);
     if (st) return st;
     ProfScope ps(ctx, SPD_K_CLOSE, s);
-    if (ctx->at)   // the SEAV's bit view first, streamed at full bandwidth (canonical bit order)
-        SPD_HIP(ctx, launch_bit_view_at(sl.seav_at, ctx->seav_alloc * 8, a.at_ct, ctx->K, reinterpret_cast<uint32_t *>(cb.seav_bits), s));
-    else if (ctx->sliding)
-        SPD_HIP(ctx, launch_bit_view(sl.seav_ts, ctx->seav_alloc * 8, (uint16_t)a.thr, reinterpret_cast<uint32_t *>(cb.seav_bits), s));
     SPD_HIP(ctx, launch_close(ctx->c, a, close_mode(ctx), block, grid, s));
     ++cb.seq;
     return SPD_OK;
@@ -1458,6 +1446,7 @@ void spd_destroy(spd_ctx *ctx) {
         }
         if (ctx->h2d_s) (void)hipStreamDestroy(ctx->h2d_s);
         close_buf_free(ctx, ctx->cbuf);
+        dev_free(ctx, &ctx->close_counts, kCloseCountBytes);
         for (auto &pc : ctx->pend) {
             close_buf_free(ctx, pc.cb);
             if (pc.done) (void)hipEventDestroy(pc.done);
@@ -1737,6 +1726,8 @@ spd_status spd_close_end(spd_ctx *ctx, uint32_t ticket, spd_superpoint *out_host
             *n_out = n;
             return fail(ctx, SPD_E_TRUNCATED, "more super points than the close's record buffer held");
         }
+        // (the records past the first chunk are in device memory, complete when the kernel has ended)
+        if (n > kRecChunk) SPD_HIP(ctx, hipEventSynchronize(pc.done));
         spd_status st = close_report(ctx, pc.cb, n, ctx->copy_s, &res);
         if (st) return st;
     }
