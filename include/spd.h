@@ -104,9 +104,13 @@ typedef struct spd_batch {
 
 /* Launch tuning.  Every setting gives the same sketch bits; only speed changes. */
 typedef struct spd_tuning {
-    uint64_t direct_max_pairs; /* batches up to this size use the direct-atomic scan kernel */
-    uint32_t bucket_bits;      /* binned scan: log2 of sketch bits per LDS bucket (12..20) */
-    uint32_t tile_pairs;       /* binned scan: pairs per tile (power of two, 2048..16384) */
+    uint64_t direct_max_pairs; /* batches up to this size use the direct-atomic scan kernel; at the default
+                                  (2^18) spd_scan, spd_scan_host and the batch scans take the binned
+                                  kernels below it too where those are faster */
+    uint32_t bucket_bits;      /* binned scan: log2 of sketch bits per LDS bucket (12..20), at most */
+    uint32_t tile_pairs;       /* binned scan: pairs per tile (power of two, 2048..16384), at most: bin_mode 2
+                                  with workgroups of 1024 and tiles of 8192 or less chooses both for the
+                                  launch */
     uint32_t bin_block;        /* binned scan: threads per workgroup of the binning kernel (256..1024) */
     uint32_t apply_block;      /* binned scan: threads per workgroup of the apply kernel (256..1024) */
     uint32_t direct_block;     /* direct scan: threads per workgroup */

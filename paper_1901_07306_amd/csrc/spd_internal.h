@@ -263,7 +263,7 @@ __host__ __device__ __forceinline__ uint64_t chunk_at(const RegionArgs &ra, uint
     return ra.slot_base[si] + (uint64_t)cc * ra.chunk_words;
 }
 hipError_t launch_region(const Consts &c, const BinGeometry &g, const BatchList &bl, uint32_t n_tiles,
-                         const ChunkTable &ct, const SlotPtrs *slots, const RegionArgs &ra, hipStream_t s, KTiming kt = {});
+                         const ChunkTable &ct, const RegionArgs &ra, hipStream_t s, KTiming kt = {});
 struct ApplySlot {
     uint32_t *ldca;
     uint32_t *seav_w;

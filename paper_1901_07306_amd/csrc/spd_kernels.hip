@@ -398,9 +398,8 @@ __device__ void bucket_offsets(uint32_t *cl, uint32_t *cs, uint32_t nb, uint32_t
 }
 
 // Bit addresses of a tile's pairs: LDCA items are counted per bucket in cl (the returned rank is
-// kept per item), sampled pairs are staged in samp; once samp is full the rest are recorded directly
-// (DEFER: only counted, the caller hands the whole tile's sampled pairs to a later pass).
-template <int LR, int PPT, int BLOCK, bool FULL, bool DEFER>
+// kept per item), sampled pairs are staged in samp; once samp is full the rest are recorded directly.
+template <int LR, int PPT, int BLOCK, bool FULL>
 __device__ __forceinline__ void bin_hash_pairs(const Consts &c, const RowLds &rl, const BinGeometry &g, const SlotPtrs &S,
                                                const u32x2 (&pr)[PPT], uint64_t p0, uint64_t n, uint32_t *cl,
                                                uint32_t *samp, uint32_t *misc, uint32_t (&bits)[PPT * LR],
@@ -428,7 +427,7 @@ __device__ __forceinline__ void bin_hash_pairs(const Consts &c, const RowLds &rl
             if (e < g.scap) {
                 samp[2 * e] = hip;
                 samp[2 * e + 1] = b;
-            } else if (!DEFER) {
+            } else {
                 // more sampled pairs than the tile reserved: record them directly
                 uint32_t *seav_w = reinterpret_cast<uint32_t *>(S.seav);
                 for (uint32_t r = 0; r < c.sr; ++r) {
@@ -483,9 +482,9 @@ __global__ __launch_bounds__(BLOCK) void k_bin(Consts c, BinGeometry g, BatchTab
     uint32_t bits[PPT * LR], rk[(PPT * LR + 1) / 2];
     // a full tile (all but the last of a batch) needs no per-pair range test
     if (p0 + (uint64_t)(PPT * BLOCK) <= B.n)
-        bin_hash_pairs<LR, PPT, BLOCK, true, false>(c, rl, g, S, pr, p0, B.n, cl, samp, misc, bits, rk);
+        bin_hash_pairs<LR, PPT, BLOCK, true>(c, rl, g, S, pr, p0, B.n, cl, samp, misc, bits, rk);
     else
-        bin_hash_pairs<LR, PPT, BLOCK, false, false>(c, rl, g, S, pr, p0, B.n, cl, samp, misc, bits, rk);
+        bin_hash_pairs<LR, PPT, BLOCK, false>(c, rl, g, S, pr, p0, B.n, cl, samp, misc, bits, rk);
     __syncthreads();
     // a tile with more sampled pairs than it can stage records all of them directly (the decision
     // depends only on the tile's sampled count, so a counting pass can repeat it)
@@ -884,64 +883,153 @@ hipError_t launch_count(const Consts &c, const BinGeometry &g, const BatchDesc *
 
 // ---- region layout (one pass over the pairs)
 
-// A tile's items binned in LDS as in k_bin (ranks per bucket, then segment bases), with each
-// bucket's segment padded to whole 64-bit words (copies of its last item).  Each non-empty segment
-// takes room in its (chunk, bucket) region with one atomic; the atomics are issued before the
-// items are placed in the stage, so their round trip overlaps that work.  The stage holds full
-// bit addresses, so a stage word's first item names its bucket at write-out, and the last two
-// places of each segment are first filled with an address of another bucket: those still holding
-// it after placement are the padding.
+// Inclusive prefix sum over the wavefront, and over rows of 16 lanes, in registers (DPP: no LDS round
+// trip per step).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_add(uint32_t v) {
+    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ uint32_t row_scan(uint32_t v) {
+    v = dpp_add<0x111, 0xF>(v);   // row_shr 1, 2, 4, 8
+    v = dpp_add<0x112, 0xF>(v);
+    v = dpp_add<0x114, 0xF>(v);
+    return dpp_add<0x118, 0xF>(v);
+}
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+    v = row_scan(v);
+    v = dpp_add<0x142, 0xA>(v);   // lane 15 of rows 0 and 2 to rows 1 and 3
+    return dpp_add<0x143, 0xC>(v);   // lane 31 to rows 2 and 3
+}
+
+// Pair tid + j * BLOCK of a tile from pair p0 of batch B, as stored; lanes past the batch's end read its
+// last pair (they are masked later), so that all loads are in flight together.
+template <int PPT, int BLOCK>
+__device__ __forceinline__ void load_tile(const BatchDesc &B, uint64_t p0, u32x2 (&pr)[PPT]) {
+    const u32x2 *pairs = reinterpret_cast<const u32x2 *>(B.pairs) + p0;
+    if (p0 + (uint64_t)(PPT * BLOCK) <= B.n) {
+#pragma unroll
+        for (int j = 0; j < PPT; ++j) pr[j] = load_pair(pairs + j * BLOCK, threadIdx.x, 0u);
+    } else {
+        const uint32_t last = (uint32_t)(B.n - p0 - 1);
+#pragma unroll
+        for (int j = 0; j < PPT; ++j) {
+            const uint32_t i = (uint32_t)(j * BLOCK) + threadIdx.x;
+            pr[j] = load_pair(pairs, i < last ? i : last, 0u);
+        }
+    }
+}
+
+// Bit addresses of a tile's pairs: LDCA items are counted per bucket in cl and the returned rank kept
+// per item; sampled pairs are staged in samp while it has room and counted in *n_samp.  H1 is tested on
+// its low 24 bits first, which a 24-bit product gives.  A lane keeps its last sampled pair and stages it
+// at the end, or when it meets another, so that the wavefront does not wait for an LDS counter at every
+// pair that some lane samples.
+template <int LR, int PPT, int BLOCK, bool FULL>
+__device__ __forceinline__ void region_hash(const Consts &c, const BinGeometry &g, const u32x2 (&pr)[PPT], uint32_t left,
+                                            uint32_t *cl, uint32_t *samp, uint32_t *n_samp, uint32_t (&bits)[PPT * LR],
+                                            uint32_t (&rk)[(PPT * LR + 1) / 2]) {
+    const uint32_t tid = threadIdx.x;
+    const uint32_t low = c.tau_mask & 0xFFFFFFu;
+    uint32_t s_hip = 0, s_oip = 0;
+    bool has = false;
+    auto stage_sample = [&]() {
+        const uint32_t e = atomicAdd(n_samp, 1u);
+        if (e < g.scap) {
+            samp[2 * e] = s_hip;
+            samp[2 * e + 1] = se_bit(s_oip, c);
+        }
+    };
+#pragma unroll
+    for (int j = 0; j < PPT; ++j) {
+        const bool valid = FULL || (uint32_t)(j * BLOCK) + tid < left;
+        const uint32_t hip = pr[j].x, oip = pr[j].y;
+        const uint32_t q = ldc_bit(oip, c);
+#pragma unroll
+        for (int r = 0; r < LR; ++r) {
+            const int k = j * LR + r;
+            const uint32_t bit = ldca_bit((uint32_t)r, ldc_col(hip, (uint32_t)r, c), q, c);
+            const uint32_t rank = valid ? atomicAdd(&cl[bit >> g.S], 1u) : 0xFFFFu;
+            bits[k] = bit;
+            if (k & 1)
+                rk[k / 2] |= rank << 16;
+            else
+                rk[k / 2] = rank;
+        }
+        // the low 24 bits of H1 (its high product enters modulo 2^24), the others when they count
+        const uint32_t h1 = (uint32_t)(((uint64_t)(uint32_t)c.mul[0] * oip + c.add[0]) >> 32) +
+                            __umul24((uint32_t)(c.mul[0] >> 32), oip);
+        bool hit = valid && (h1 & low) == 0u;
+        if (c.tau_mask > 0xFFFFFFu) hit = hit && sampled(oip, c);
+        if (__ballot(hit && has)) {
+            if (hit && has) stage_sample();
+        }
+        s_hip = hit ? hip : s_hip;
+        s_oip = hit ? oip : s_oip;
+        has = has || hit;
+    }
+    if (has) stage_sample();
+}
+
+// A tile's items binned in LDS (ranks per bucket, then segment bases), with each bucket's segment
+// padded to whole 64-bit words (copies of its last item).  Each non-empty segment takes room in its
+// (chunk, bucket) region with one atomic; the atomics are issued before the items are placed in the
+// stage, so their round trip overlaps that work.  The stage holds full bit addresses, so a stage word's
+// first item names its bucket at write-out, and the last two places of each segment are first filled
+// with an address of another bucket: those still holding it after placement are the padding.
 //
 // At most 80 scalar registers: with more, a SIMD holds fewer than eight wavefronts and the compute
 // unit one workgroup of 1024 instead of two (64 Mi pairs: 320 instead of 229 us).
 template <int LR, int PPT, int BLOCK>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_num_sgpr(80))) void k_region(Consts c, BinGeometry g, BatchList bl, SlotTable st, ChunkTable ct,
-                                                  RegionArgs ra) {
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_num_sgpr(80))) void k_region(Consts c, BinGeometry g, BatchList bl,
+                                                                                       ChunkTable ct, RegionArgs ra) {
     extern __shared__ uint32_t lds[];
     __shared__ RowLds rl;   // read after the first barrier
     rows_to_lds(rl, c);
+    constexpr uint32_t NW = BLOCK / 64;
     const uint32_t nb = g.nb;
-    uint32_t *cl = lds;                  // [nb + 1] LDCA counts, then padded counts, then bases
-    uint32_t *cs = cl + (nb + 1);        // [nb + 1] SEAV counts, then SEAV cursors
+    uint32_t *cl = lds;                  // [nb + 1] LDCA counts, then bases
+    uint32_t *cs = cl + (nb + 1);        // [nb + 1] SEAV counts, then SEAV cursors, then distances
     uint32_t *stage = lds + ((2 * (nb + 1) + 3) & ~3u);   // [cap] full bit addresses, bucket-major
     uint32_t *samp = stage + g.cap;      // [2 * scap] sampled (hip, H2 bit)
-    uint32_t *misc = samp + 2 * g.scap;  // [0] sampled count, [1..17] scan scratch
-    const uint32_t tid = threadIdx.x;
+    uint32_t *misc = samp + 2 * g.scap;  // [0] sampled count, [1] a segment is past its region, [2..17] scan
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // each thread owns `per` consecutive buckets
+    const uint32_t per = (nb + BLOCK - 1) / BLOCK;
+    const uint32_t b_beg = tid * per < nb ? tid * per : nb, b_end = b_beg + per < nb ? b_beg + per : nb;
+
     const uint32_t tile = xcd_contiguous(blockIdx.x, gridDim.x);   // neighbouring tiles on one XCD
     const BatchDesc B = batch_of(bl, tile);
-    const SlotPtrs S = st.s[B.slot];
     const uint64_t p0 = (uint64_t)(tile - B.first_tile) * (uint64_t)(PPT * BLOCK);
-    const uint32_t cc = (tile - ct.lo[B.slot]) / ct.tiles, chunk = ct.cbase[B.slot] + cc;
-    const uint32_t seav_base = (uint32_t)c.ldca_bits;   // SEAV bits follow the LDCA bits
-
-    for (uint32_t i = tid; i < 2 * (nb + 1); i += BLOCK) cl[i] = 0;
-    if (tid == 0) misc[0] = 0;
-    const u32x2 *pairs = reinterpret_cast<const u32x2 *>(B.pairs);
-    const uint64_t last = B.n - 1;
-    const bool full = p0 + (uint64_t)(PPT * BLOCK) <= B.n;
     u32x2 pr[PPT];
-#pragma unroll
-    for (int j = 0; j < PPT; ++j) {
-        const uint64_t idx = p0 + (uint64_t)j * BLOCK + tid;
-        pr[j] = load_pair(pairs, idx < B.n ? idx : last, B.swap);
-    }
+    load_tile<PPT, BLOCK>(B, p0, pr);
+    const uint32_t left = B.n - p0 < (uint64_t)(PPT * BLOCK) ? (uint32_t)(B.n - p0) : (uint32_t)(PPT * BLOCK);
+    const bool full = left == (uint32_t)(PPT * BLOCK);
+    const uint32_t slot = B.slot, t_lo = ct.lo[slot], cc = (tile - t_lo) / ct.tiles;
+    const uint32_t seav_base = (uint32_t)c.ldca_bits;   // SEAV bits follow the LDCA bits
+    const uint32_t smask = (1u << g.S) - 1u;
+    for (uint32_t i = tid; i < 2 * (nb + 1); i += BLOCK) cl[i] = 0;
+    if (tid < 2) misc[tid] = 0;
     __syncthreads();
+    if (B.swap) {   // destination-keyed
+#pragma unroll
+        for (int j = 0; j < PPT; ++j) pr[j] = u32x2{pr[j].y, pr[j].x};
+    }
     uint32_t bits[PPT * LR], rk[(PPT * LR + 1) / 2];
     if (full)
-        bin_hash_pairs<LR, PPT, BLOCK, true, true>(c, rl, g, S, pr, p0, B.n, cl, samp, misc, bits, rk);
+        region_hash<LR, PPT, BLOCK, true>(c, g, pr, left, cl, samp, misc, bits, rk);
     else
-        bin_hash_pairs<LR, PPT, BLOCK, false, true>(c, rl, g, S, pr, p0, B.n, cl, samp, misc, bits, rk);
+        region_hash<LR, PPT, BLOCK, false>(c, g, pr, left, cl, samp, misc, bits, rk);
     __syncthreads();
     // a tile with more sampled pairs than it can stage stages none: it is listed, and the apply
     // phase of the SEAV buckets reads all of its sampled pairs again
     uint32_t ns = misc[0];
     if (ns > g.scap) {
         if (tid == 0) {
-            const uint64_t left = B.n - p0;
             ListedTile &t = ra.tile[atomicAdd(ra.tile_n, 1u)];   // (one entry per tile of the launch)
             t.pairs = B.pairs + 2 * p0;
-            t.n = left < (uint64_t)(PPT * BLOCK) ? (uint32_t)left : (uint32_t)(PPT * BLOCK);
-            t.slot = B.slot;
+            t.n = left;
+            t.slot = slot;
             t.swap = B.swap;
         }
         ns = 0;
@@ -952,29 +1040,30 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_num_sgpr(80))) void k_
         atomicAdd(&cs[bit >> g.S], 1u);
     }
     __syncthreads();
-    // padded counts (whole words); bucket_offsets then leaves cl[b] = cs[b] = segment base
-    for (uint32_t b = tid; b < nb; b += BLOCK) {
-        const uint32_t n = cl[b] + cs[b];
-        cl[b] = 0;
-        cs[b] = (n + 2) / 3 * 3;
-    }
-    __syncthreads();
-    bucket_offsets<BLOCK>(cl, cs, nb, misc + 1);
-    // room in the regions (the offsets of a thread's first two buckets stay in flight), and the
-    // padding marks
+    // padded counts (whole words) and their prefix sum; then, per bucket, its base, room in its
+    // region (the offsets of a thread's first two buckets stay in flight) and the padding marks
     // (two named registers: an array indexed by the loop counter would live in scratch memory)
-    uint32_t *rcur = ra.cur + (uint64_t)chunk * nb;
+    uint32_t local = 0;
+    for (uint32_t b = b_beg; b < b_end; ++b) local += (cl[b] + cs[b] + 2) / 3 * 3;
+    const uint32_t incl = wave_scan(local);
+    if (lane == 63u) misc[2 + wid] = incl;
+    __syncthreads();
+    const uint32_t wsum = lane < NW ? misc[2 + lane] : 0u, wincl = row_scan(wsum);
+    uint32_t run = __builtin_amdgcn_readlane(wincl, wid) - __builtin_amdgcn_readlane(wsum, wid) + incl - local;
+    const uint32_t nwords = __builtin_amdgcn_readlane(wincl, NW - 1) / 3;
+    uint32_t *rcur = ra.cur + (uint64_t)(ct.cbase[slot] + cc) * nb;
     uint32_t o_pre0 = 0u, o_pre1 = 0u;
-    for (uint32_t b = tid, m = 0; b < nb; b += BLOCK, ++m) {
-        const uint32_t s0 = cl[b], pe = cl[b + 1];
-        if (pe > s0) {
-            if (m == 0) o_pre0 = atomicAdd(rcur + b, (pe - s0) / 3);
-            else if (m == 1) o_pre1 = atomicAdd(rcur + b, (pe - s0) / 3);
-            stage[pe - 2] = stage[pe - 1] = (b ^ 1u) << g.S;
+    for (uint32_t b = b_beg, m = 0; b < b_end; ++b, ++m) {
+        const uint32_t n = (cl[b] + cs[b] + 2) / 3;
+        cl[b] = cs[b] = run;
+        run += 3 * n;
+        if (n) {
+            if (m == 0) o_pre0 = atomicAdd(rcur + b, n);
+            else if (m == 1) o_pre1 = atomicAdd(rcur + b, n);
+            stage[run - 2] = stage[run - 1] = (b ^ 1u) << g.S;
         }
     }
-    uint32_t *past = misc + 1;   // (the scan scratch is free) set when a segment does not fit its region
-    if (tid == 0) *past = 0u;
+    if (tid == 0) cl[nb] = 3 * nwords;
     __syncthreads();
     if (full) {   // every lane's items are valid
 #pragma unroll
@@ -997,7 +1086,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_num_sgpr(80))) void k_
     // taken here).  cs[b] becomes the distance from a stage word of bucket b to its place among the
     // chunk's regions; a segment that does not fit its region is listed under its bucket, its
     // remaining words go to the same places of the tile's part of the spill array.
-    for (uint32_t b = tid, m = 0; b < nb; b += BLOCK, ++m) {
+    for (uint32_t b = b_beg, m = 0; b < b_end; ++b, ++m) {
         const uint32_t s0 = cl[b], pe = cl[b + 1];
         if (pe > s0) {
             if ((stage[pe - 2] >> g.S) != b) stage[pe - 2] = stage[pe - 3];
@@ -1005,65 +1094,63 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_num_sgpr(80))) void k_
             const uint32_t w0 = s0 / 3, n = (pe - s0) / 3;
             const uint32_t o = m == 0 ? o_pre0 : m == 1 ? o_pre1 : atomicAdd(rcur + b, n);
             uint32_t capw;
-            const uint32_t in = region_in(ra, g.nb_ldca, B.slot, cc, b, &capw);
+            const uint32_t in = region_in(ra, g.nb_ldca, slot, cc, b, &capw);
             cs[b] = in + o - w0;
             if (o + n > capw) {
                 const uint32_t fit = o < capw ? capw - o : 0u;
-                const uint32_t lo = ct.lo[B.slot], nt = ct.hi[B.slot] - lo;
-                const uint32_t k = atomicAdd(ra.seg_n + B.slot * nb + b, 1u);   // below nt
-                ra.seg[(uint64_t)lo * nb + (uint64_t)b * nt + k] = SpillSeg{tile * ra.tile_words + w0 + fit, n - fit};
-                *past = 1u;
+                const uint32_t nt = ct.hi[slot] - t_lo;
+                const uint32_t k = atomicAdd(ra.seg_n + slot * nb + b, 1u);   // below nt
+                ra.seg[(uint64_t)t_lo * nb + (uint64_t)b * nt + k] = SpillSeg{tile * ra.tile_words + w0 + fit, n - fit};
+                misc[1] = 1u;
             }
         }
     }
     __syncthreads();
     // one thread per stage word: three 21-bit offsets per 64-bit word
-    const uint32_t smask = (1u << g.S) - 1u;
-    const uint32_t nwords = cl[nb] / 3;
-    uint64_t *dst = ra.items + chunk_at(ra, B.slot, cc);
+    uint64_t *dst = ra.items + chunk_at(ra, slot, cc);
     auto word = [&](uint32_t w, uint32_t &b) {
         const uint32_t s0 = stage[3 * w], s1 = stage[3 * w + 1], s2 = stage[3 * w + 2];
         b = s0 >> g.S;
         const uint32_t lo = (s0 & smask) | (s1 << 21), hi = ((s1 & smask) >> 11) | ((s2 & smask) << 10);
         return (uint64_t)lo | ((uint64_t)hi << 32);
     };
-    if (!*past) {
+    if (!misc[1]) {
         for (uint32_t w = tid; w < nwords; w += BLOCK) {
             uint32_t b;
             const uint64_t v = word(w, b);
             dst[w + cs[b]] = v;
         }
-        return;
-    }
-    // cl[b] becomes the first stage word past the region's room
-    for (uint32_t b = tid; b < nb; b += BLOCK) {
-        const uint32_t w0 = cl[b] / 3;
-        uint32_t capw;
-        const uint32_t o = cs[b] + w0 - region_in(ra, g.nb_ldca, B.slot, cc, b, &capw);
-        cl[b] = w0 + (o < capw ? capw - o : 0u);
-    }
-    __syncthreads();
-    uint64_t *spill = ra.spill_w + (uint64_t)tile * ra.tile_words;
-    for (uint32_t w = tid; w < nwords; w += BLOCK) {
-        uint32_t b;
-        const uint64_t v = word(w, b);
-        if (w < cl[b]) dst[w + cs[b]] = v;
-        else spill[w] = v;
+    } else {
+        // cl[b] becomes the first stage word past the region's room
+        for (uint32_t b = tid; b < nb; b += BLOCK) {
+            const uint32_t w0 = cl[b] / 3;
+            uint32_t capw;
+            const uint32_t o = cs[b] + w0 - region_in(ra, g.nb_ldca, slot, cc, b, &capw);
+            cl[b] = w0 + (o < capw ? capw - o : 0u);
+        }
+        __syncthreads();
+        uint64_t *spill = ra.spill_w + (uint64_t)tile * ra.tile_words;
+        for (uint32_t w = tid; w < nwords; w += BLOCK) {
+            uint32_t b;
+            const uint64_t v = word(w, b);
+            if (w < cl[b]) dst[w + cs[b]] = v;
+            else spill[w] = v;
+        }
     }
 }
 
 template <int LR>
-static hipError_t launch_region_lr(const Consts &c, const BinGeometry &g, const BatchList &bl, const SlotTable &st,
-                                   const ChunkTable &ct, const RegionArgs &ra, uint32_t n_tiles, hipStream_t s,
-                                   KTiming kt) {
+static hipError_t launch_region_lr(const Consts &c, const BinGeometry &g, const BatchList &bl, const ChunkTable &ct,
+                                   const RegionArgs &ra, uint32_t n_tiles, hipStream_t s, KTiming kt) {
     const uint32_t ppt = g.tile_pairs / g.block;
 #define SPD_RG_CASE(B, P)                                                                                        \
     else if (g.block == B && ppt == P)                                                                         \
         hipExtLaunchKernelGGL((k_region<LR, P, B>), dim3(n_tiles), dim3(B), g.lds_bytes, s, kt.start, kt.stop, 0, c, g, \
-                              bl, st, ct, ra);
+                              bl, ct, ra);
     if (false) {
     }
-    SPD_RG_CASE(1024, 16) SPD_RG_CASE(1024, 8) SPD_RG_CASE(1024, 4) SPD_RG_CASE(512, 16) SPD_RG_CASE(512, 8)
+    SPD_RG_CASE(1024, 16) SPD_RG_CASE(1024, 8) SPD_RG_CASE(1024, 7) SPD_RG_CASE(1024, 6) SPD_RG_CASE(1024, 5)
+    SPD_RG_CASE(1024, 4) SPD_RG_CASE(1024, 2) SPD_RG_CASE(512, 16) SPD_RG_CASE(512, 8)
     SPD_RG_CASE(512, 4) SPD_RG_CASE(256, 16) SPD_RG_CASE(256, 8)
 #undef SPD_RG_CASE
     else return hipErrorInvalidConfiguration;
@@ -1071,15 +1158,13 @@ static hipError_t launch_region_lr(const Consts &c, const BinGeometry &g, const 
 }
 
 hipError_t launch_region(const Consts &c, const BinGeometry &g, const BatchList &bl, uint32_t n_tiles,
-                         const ChunkTable &ct, const SlotPtrs *slots, const RegionArgs &ra, hipStream_t s, KTiming kt) {
+                         const ChunkTable &ct, const RegionArgs &ra, hipStream_t s, KTiming kt) {
     if (bl.n == 0 || n_tiles == 0 || (!bl.b && bl.n > kInlineBatches)) return hipErrorInvalidValue;
-    SlotTable st{};
-    for (uint32_t i = 0; i < ct.n; ++i) st.s[i] = slots[i];
     switch (c.lr) {
-    case 1: return launch_region_lr<1>(c, g, bl, st, ct, ra, n_tiles, s, kt);
-    case 2: return launch_region_lr<2>(c, g, bl, st, ct, ra, n_tiles, s, kt);
-    case 3: return launch_region_lr<3>(c, g, bl, st, ct, ra, n_tiles, s, kt);
-    case 4: return launch_region_lr<4>(c, g, bl, st, ct, ra, n_tiles, s, kt);
+    case 1: return launch_region_lr<1>(c, g, bl, ct, ra, n_tiles, s, kt);
+    case 2: return launch_region_lr<2>(c, g, bl, ct, ra, n_tiles, s, kt);
+    case 3: return launch_region_lr<3>(c, g, bl, ct, ra, n_tiles, s, kt);
+    case 4: return launch_region_lr<4>(c, g, bl, ct, ra, n_tiles, s, kt);
     default: return hipErrorInvalidValue;
     }
 }

@@ -18,6 +18,9 @@ namespace {
 
 constexpr uint32_t kMaxLds = 160 * 1024;       // LDS per workgroup on gfx950
 constexpr uint32_t kMaxBucketBits = 20;        // 2^20 bits = 128 KiB bitmap per apply workgroup
+constexpr double kScratchUs = 50.0;            // the time of allocating the scratch of a small scan
+constexpr uint64_t kDirectMaxPairs = 1u << 18; // default of spd_tuning.direct_max_pairs
+constexpr uint32_t kMinLaunchBucketBits = 16;  // the smallest bucket a launch chooses by itself
 constexpr uint64_t kSeavAlign = 1ull << (kMaxBucketBits - 3);  // SEAV padded to whole buckets
 
 struct Slot {
@@ -111,6 +114,7 @@ struct spd_ctx {
     uint64_t aux_words = 0;
     bool aux_zero = false;           // region layout: every aux word is zero between launches
     uint32_t close_per_cu[3] = {0, 0, 0};   // resident end-of-window workgroups per CU (64, 128, 256 lanes)
+    double small_gain = 0.0;         // what small scans without scratch would have saved with it (us)
     uint32_t list_parity = 0;        // region layout: which of two tile-list counts the next launch uses
     CloseBuf cbuf;                  // end-of-window buffers of spd_close_window
     uint64_t *close_counts = nullptr;   // finished workgroups of the running close (a context's closes
@@ -275,7 +279,7 @@ spd_status derive(const spd_params *p, spd_derived *d, std::string *why) {
 }
 
 void default_tuning(spd_tuning *t) {
-    t->direct_max_pairs = 1u << 18;
+    t->direct_max_pairs = kDirectMaxPairs;
     t->bucket_bits = 20;
     t->tile_pairs = 8192;
     t->bin_block = 1024;
@@ -438,11 +442,12 @@ spd_status clear_seav(spd_ctx *ctx, Slot &s, hipStream_t st) {
     return SPD_OK;
 }
 
-// Geometry of the binned scan for the current tuning; false if it does not fit the LDS.
-bool bin_geometry(const spd_ctx *ctx, BinGeometry *g) {
+// Geometry of the binned scan with buckets of at most 2^S bits and tiles of T pairs; false if it is
+// not possible.  (lds_bytes may be larger than a workgroup's LDS.)
+bool bin_geometry_at(const spd_ctx *ctx, uint32_t S, uint32_t T, BinGeometry *g) {
     const spd_tuning &t = ctx->tune;
     const uint64_t ldca_bits = ctx->d.ldca_words * 32;
-    uint32_t S = std::min<uint32_t>(t.bucket_bits, kMaxBucketBits);
+    S = std::min<uint32_t>(S, kMaxBucketBits);
     S = std::min<uint32_t>(S, ctx->p.log2lc + ctx->p.log2k);   // 2^S divides the LDCA bits
     if (S < 5) return false;
     g->S = S;
@@ -450,35 +455,75 @@ bool bin_geometry(const spd_ctx *ctx, BinGeometry *g) {
     g->nb = g->nb_ldca + (uint32_t)((ctx->seav_alloc * 8) >> S);
     if (g->nb > 65535) return false;
     g->block = t.bin_block;
+    g->tile_pairs = T;
+    // sampled pairs a tile stages (the others of a tile with more are recorded otherwise): the mean plus
+    // six standard deviations and a margin
+    const double expect = (double)T / (double)(1ull << ctx->d.tau);
+    const uint32_t scap = (uint32_t)std::ceil(expect + 6.0 * std::sqrt(expect) + 32.0);
+    g->scap = std::min<uint32_t>((scap + 63) / 64 * 64, T);
+    // bucket-major segments are padded to whole words: at most 2 more items per bucket
+    const uint64_t cap = (uint64_t)T * ctx->p.lr + (uint64_t)g->scap * ctx->p.sr + (t.bin_mode != 0 ? 2ull * g->nb : 0ull);
+    g->cap = (uint32_t)((cap + 5) / 6 * 6);
+    g->region = g->cap / 3 * 2;
+    if ((uint64_t)T * ctx->p.lr > 65535) return false;   // per-bucket ranks are 16 bits, 0xFFFF unused
+    const uint64_t stage_off = (2ull * (g->nb + 1) + 3) & ~3ull;   // same layout in every binning kernel
+    // + scan scratch (17 words) + the static per-row constants (3 per row)
+    g->lds_bytes = (uint32_t)(4ull * (stage_off + g->cap + 2ull * g->scap + 1 + 17 + 3ull * kMaxRows));
+    return true;
+}
+
+// Geometry of the binned scan for the current tuning; false if it does not fit the LDS.
+bool bin_geometry(const spd_ctx *ctx, BinGeometry *g) {
+    const spd_tuning &t = ctx->tune;
     for (uint32_t T = t.tile_pairs; T >= 2048; T /= 2) {
-        if (T % g->block) continue;
-        const uint32_t ppt = T / g->block;
+        if (T % t.bin_block) continue;
+        const uint32_t ppt = T / t.bin_block;
         if (ppt != 4 && ppt != 8 && ppt != 16) continue;
         // items are held in registers between counting and scattering: keep them spill-free
-        if (ppt * ctx->p.lr * g->block > 32u * 1024u) continue;
-        // sampled pairs a tile stages (more are recorded with global atomics): the mean plus
-        // six standard deviations and a margin
-        const double expect = (double)T / (double)(1ull << ctx->d.tau);
-        uint32_t scap = (uint32_t)std::ceil(expect + 6.0 * std::sqrt(expect) + 32.0);
-        scap = std::min<uint32_t>((scap + 63) / 64 * 64, T);
-        const bool bm = t.bin_mode != 0;
-        // bucket-major segments are padded to whole words: at most 2 more items per bucket
-        uint64_t cap = (uint64_t)T * ctx->p.lr + (uint64_t)scap * ctx->p.sr + (bm ? 2ull * g->nb : 0ull);
-        cap = (cap + 5) / 6 * 6;
-        if ((uint64_t)T * ctx->p.lr > 65535) continue;   // per-bucket ranks are 16 bits, 0xFFFF unused
-        const uint64_t stage_off = (2ull * (g->nb + 1) + 3) & ~3ull;   // same layout in k_bin and k_place
-        // + scan scratch (17 words) + the static per-row constants (3 per row)
-        const uint64_t lds = 4ull * (stage_off + cap + 2ull * scap + 1 + 17 + 3ull * kMaxRows);
-        if (lds <= kMaxLds) {
-            g->tile_pairs = T;
-            g->scap = scap;
-            g->cap = (uint32_t)cap;
-            g->region = cap / 3 * 2;
-            g->lds_bytes = (uint32_t)lds;
-            return true;
-        }
+        if (ppt * ctx->p.lr * t.bin_block > 32u * 1024u) continue;
+        if (bin_geometry_at(ctx, t.bucket_bits, T, g) && g->lds_bytes <= kMaxLds) return true;
     }
     return false;
+}
+
+// Geometry of one region launch over batches of n[i] pairs into n_slots slots, g0 being the tuning's:
+// with workgroups of 1024 and tiles of 8192 pairs or less, the bucket size and the tile are chosen for
+// the launch, up to the tuning's.
+//  * Buckets: the apply phase has a workgroup per (slot, bucket), so small sketches get smaller buckets,
+//    as many as there are compute units (4.1 MiB, 1,000,000 pairs: apply 9.5 us with 33 buckets, 5.4 to
+//    7.3 with 264).
+//  * Tiles: two workgroups of the binning kernel share a compute unit when their LDS fits, so tiles
+//    run in rounds of two per compute unit; of the tile sizes that fit twice (else of those that fit
+//    once), the one with the least rounds times a tile's time is taken.  A tile of 1024 p pairs takes
+//    about 2.8 + 1.31 p us in a full round (64 Mi pairs: 13.3 us at p = 8, 8.1 at p = 4).  With 1152
+//    buckets 8192 pairs do not fit twice: 8 x 16 Mi pairs 691 us, with p = 7 493 us.
+void region_geometry(const spd_ctx *ctx, const BinGeometry &g0, const std::vector<uint64_t> &n, uint32_t n_slots,
+                     BinGeometry *out) {
+    *out = g0;
+    if (g0.block != 1024 || g0.tile_pairs > 8192) return;
+    uint32_t S = g0.S;
+    BinGeometry g{};
+    while (S > kMinLaunchBucketBits && (uint64_t)n_slots * out->nb < ctx->n_cu && bin_geometry_at(ctx, S - 1, g0.tile_pairs, &g) &&
+           g.lds_bytes <= kMaxLds)
+        *out = g, --S;
+    double best = 0.0;
+    bool best_two = false;
+    for (uint32_t ppt : {8u, 7u, 6u, 5u, 4u, 2u}) {
+        const uint32_t T = ppt * 1024u;
+        if (T > g0.tile_pairs || ppt * ctx->p.lr > 32u) continue;
+        if (!bin_geometry_at(ctx, S, T, &g) || g.lds_bytes > kMaxLds) continue;
+        const bool two = g.lds_bytes <= kMaxLds / 2;
+        uint64_t tiles = 0;
+        for (uint64_t v : n) tiles += (v + T - 1) / T;
+        const uint64_t per_round = (uint64_t)ctx->n_cu * (two ? 2 : 1);
+        const double rounds = (double)((tiles + per_round - 1) / per_round);
+        const double time = rounds * (2.8 + 1.31 * ppt);
+        if (best == 0.0 || (two && !best_two) || (two == best_two && time < best)) {
+            best = time;
+            best_two = two;
+            *out = g;
+        }
+    }
 }
 
 void free_batch_ring(spd_ctx *ctx) {
@@ -686,7 +731,7 @@ struct RegionScratch {
 // all of its buckets from zero, and nothing else writes the slot.  SPD_E_INVALID (nothing enqueued) if the group's layout does not fit the
 // scratch.
 spd_status region_launch_at(spd_ctx *ctx, const BinGeometry &g, const BatchDesc *bd, uint32_t nbd, uint32_t tiles,
-                            const ChunkTable &ct, const SlotPtrs *sp, const ApplySlot *as, uint32_t nsl,
+                            const ChunkTable &ct, const ApplySlot *as, uint32_t nsl,
                             const RegionScratch &rs, hipStream_t s) {
     RegionArgs ra{};
     uint64_t items_words = 0, cur_words = 0;
@@ -726,7 +771,7 @@ spd_status region_launch_at(spd_ctx *ctx, const BinGeometry &g, const BatchDesc 
     *rs.aux_zero = false;   // until the launch's apply phase is enqueued
     {
         ProfKernel pk(ctx, SPD_K_BIN);
-        SPD_HIP(ctx, launch_region(ctx->c, g, bl, tiles, ct, sp, ra, s, pk.kt));
+        SPD_HIP(ctx, launch_region(ctx->c, g, bl, tiles, ct, ra, s, pk.kt));
     }
     if (!inl) {
         // the staging slot may be rewritten once the binning kernel (its only reader) has read it
@@ -755,19 +800,46 @@ spd_status region_launch_at(spd_ctx *ctx, const BinGeometry &g, const BatchDesc 
     return SPD_OK;
 }
 
+// Whether the context's scratch takes a group without being grown.
+bool region_ready(const spd_ctx *ctx, const BinGeometry &g, const ChunkTable &ct, uint32_t tiles) {
+    RegionArgs ra{};
+    uint64_t items_words = 0, cur_words = 0;
+    region_layout(ctx, g, ct, tiles, &ra, &items_words, &cur_words);
+    return items_words <= ctx->items_words && cur_words <= ctx->aux_words;
+}
+
 // The same in the context's scratch, grown on demand within the HBM budget: SPD_E_NOMEM (nothing
 // enqueued) if it does not fit.
 spd_status region_launch(spd_ctx *ctx, const BinGeometry &g, const std::vector<BatchDesc> &bd, uint32_t tiles,
-                         const ChunkTable &ct, const SlotPtrs *sp, const ApplySlot *as, uint32_t nsl, hipStream_t s) {
+                         const ChunkTable &ct, const ApplySlot *as, uint32_t nsl, hipStream_t s) {
     RegionArgs ra{};
     uint64_t items_words = 0, cur_words = 0;
     region_layout(ctx, g, ct, tiles, &ra, &items_words, &cur_words);
     if (ra.chunk_words >= (1ull << 31)) return fail(ctx, SPD_E_INVALID, "region layout: chunk too large");
-    spd_status st = ensure_scratch(ctx, items_words, 0, s);
+    // (refused before anything is given back: the scratch at hand may serve another geometry)
+    const uint64_t more = (items_words > ctx->items_words ? (items_words - ctx->items_words) * 4 : 0) +
+                          (cur_words > ctx->aux_words ? (cur_words - ctx->aux_words) * 4 : 0);
+    spd_status st = more ? reserve(ctx, more) : SPD_OK;
+    if (!st) st = ensure_scratch(ctx, items_words, 0, s);
     if (!st) st = ensure_aux(ctx, cur_words, s);
     if (st) return st;
     const RegionScratch rs{ctx->items, ctx->items_words, ctx->aux, ctx->aux_words, &ctx->aux_zero, &ctx->list_parity};
-    return region_launch_at(ctx, g, bd.data(), (uint32_t)bd.size(), tiles, ct, sp, as, nsl, rs, s);
+    return region_launch_at(ctx, g, bd.data(), (uint32_t)bd.size(), tiles, ct, as, nsl, rs, s);
+}
+
+// Microseconds that the binned kernels save over the direct one for `total` pairs into `slots` (below
+// zero: the direct kernel is faster), for batches up to direct_max_pairs.  Only at that limit's default
+// are the two compared; at any other value the limit alone decides.  Fitted to scans and closes of 4096
+// to 2^18 pairs with sketches of 4 to 144 MiB: the direct kernel takes 0.043 ns per LDCA bit; the binned
+// ones have 5.5 us more to launch and write each empty sketch up to 8 us slower than the direct kernel's
+// clear does, and read and write one that is not empty (0.48 us per MiB).  200,003 pairs into 4 MiB: 52 us
+// direct, 36 binned; 32,768 pairs: 32.6 and 36.0; into 72 MiB 42.4 and 52.1.
+double binned_gain_us(const spd_ctx *ctx, uint64_t total, const std::vector<Slot *> &slots) {
+    if (ctx->tune.direct_max_pairs != kDirectMaxPairs || ctx->tune.bin_mode != 2) return -1.0;
+    const double mib = (double)ctx->slot_bytes / 1048576.0;
+    double gain = (double)total * ctx->p.lr * 0.043e-3 - 5.5;
+    for (const Slot *sl : slots) gain -= sl->fresh ? std::min(8.0, 0.15 * mib) : 0.48 * mib;
+    return gain;
 }
 
 // Record batches into slots.  Batches of one slot are kept together so that each slot's tiles are
@@ -821,16 +893,19 @@ spd_status scan_work(spd_ctx *ctx, std::vector<WorkItem> &ws, hipStream_t s) {
     };
     if (ctx->sliding) return direct_launch(true);   // time stamps of the current slice, plain stores
     BinGeometry g{};
-    const bool binned = total > ctx->tune.direct_max_pairs && ctx->p.lr <= 4 && bin_geometry(ctx, &g);
+    const bool small = total <= ctx->tune.direct_max_pairs;
+    const double gain = small ? binned_gain_us(ctx, total, slots) : 0.0;
+    const bool binned = gain >= 0.0 && ctx->p.lr <= 4 && bin_geometry(ctx, &g);
     const bool bm = ctx->tune.bin_mode != 0;
-    if (!binned) {
+    auto direct_scan = [&]() -> spd_status {
         for (Slot *sl : slots)
             if (sl->fresh) {
                 spd_status st = clear_slot(ctx, *sl, s);
                 if (st) return st;
             }
         return direct_launch(false);
-    }
+    };
+    if (!binned) return direct_scan();
     // Binned: a slot's flags change only once a group covering it has been enqueued, so that an
     // error return (a budget refusal before anything was enqueued) leaves every slot as it was.
     // A fresh slot's buckets are written from zero by the apply phase of the region layout; the
@@ -854,6 +929,18 @@ spd_status scan_work(spd_ctx *ctx, std::vector<WorkItem> &ws, hipStream_t s) {
             for (uint64_t a = 0; a < w.n; a += split_at)
                 split.push_back(WorkItem{w.slot, w.pairs + 2 * a, std::min(split_at, w.n - a), w.swap});
         ws.swap(split);
+    }
+    // a region launch that covers the whole call has a geometry of its own
+    const BinGeometry g0 = g;
+    bool own = false;
+    if (ctx->tune.bin_mode == 2 && !lp && slots.size() <= (size_t)kMaxGroup) {
+        std::vector<uint64_t> n;
+        uint64_t tiles = 0;
+        for (auto &w : ws) n.push_back(w.n);
+        region_geometry(ctx, g0, n, (uint32_t)slots.size(), &g);
+        for (uint64_t v : n) tiles += (v + g.tile_pairs - 1) / g.tile_pairs;
+        own = tiles * g.cap < (1ull << 32);
+        if (!own) g = g0;
     }
     // binned: launch groups of at most kMaxGroup slots and launch_pairs pairs; per-tile regions also
     // take at most kMaxGroup batches per group, the region and exact-count layouts any number (one
@@ -925,10 +1012,23 @@ spd_status scan_work(spd_ctx *ctx, std::vector<WorkItem> &ws, hipStream_t s) {
             if (ctx->tune.bin_mode == 2) {
                 // the exact-count layout (less scratch) if the region layout does not fit the budget
                 chunk_table(&ct, as, nsl, region_chunk(tiles));
+                if (small && !region_ready(ctx, g, ct, tiles)) {
+                    // the direct kernel needs no scratch: a small scan has some allocated (about 50 us)
+                    // once scans like it would have saved that much
+                    ctx->small_gain += gain;
+                    if (ctx->small_gain < kScratchUs) return direct_scan();
+                }
                 ctx->merge_group = ctx->merge_into && group_start == 0 && i0 == ws.size();
-                spd_status st = region_launch(ctx, g, bd, tiles, ct, sp, as, nsl, s);
+                spd_status st = region_launch(ctx, g, bd, tiles, ct, as, nsl, s);
                 ctx->merge_group = false;
                 if (st && st != SPD_E_NOMEM) return st;
+                if (st && small) return direct_scan();   // (recording a pair twice changes nothing)
+                if (st && own) {   // (nothing was enqueued) the tuning's geometry may need less
+                    own = false;
+                    g = g0;
+                    i0 = group_start;
+                    continue;
+                }
                 if (!st) {
                     mark_written(owner, nsl);
                     ctx->stats.binned_launches++;
@@ -1021,6 +1121,10 @@ spd_status scan_noalloc(spd_ctx *ctx, Slot *sl, const uint32_t *pairs, uint64_t 
         if (!layout_of(tiles, &ct, &iw, &cw)) return false;
         return (cw * 4 + 255) / 256 * 256 + iw * 4 <= cap;
     };
+    // the launch's own geometry, when the array takes it
+    const BinGeometry g0 = g;
+    region_geometry(ctx, g0, {n}, 1, &g);
+    if (!fits((uint32_t)std::min<uint64_t>((n + g.tile_pairs - 1) / g.tile_pairs, 1u << 20))) g = g0;
     if (!fits(1))
         return fail(ctx, SPD_E_INVALID, "spd_scan_noalloc: one tile of this sketch geometry needs more scratch than "
                                         "SPD_NOALLOC_SCRATCH_BYTES");
@@ -1051,7 +1155,7 @@ spd_status scan_noalloc(spd_ctx *ctx, Slot *sl, const uint32_t *pairs, uint64_t 
         ApplySlot as[kMaxGroup] = {};
         sp[0] = ptrs_of(*sl);
         as[0] = ApplySlot{sl->ldca, reinterpret_cast<uint32_t *>(sl->seav), 0, tiles, sl->fresh ? 1u : 0u, 0};
-        spd_status st = region_launch_at(ctx, g, &bd, 1, tiles, ct, sp, as, 1, rs, s);
+        spd_status st = region_launch_at(ctx, g, &bd, 1, tiles, ct, as, 1, rs, s);
         if (st) return st;
         sl->fresh = false;
         ctx->stats.binned_launches++;
