@@ -297,7 +297,7 @@ const char *spd_last_error(const spd_ctx *ctx);
  * wait), fuses whatever batches are pending, from any routers and of any sizes, into one scan
  * launch group, and closes a window when its router has seen window_pairs pairs (a batch that
  * crosses the boundary is split) or when a batch is submitted with SPD_SUBMIT_CLOSE.  Closes run
- * on their own stream, replayed from a hipGraph captured per slot, and overlap later scans.  A
+ * on their own stream, those of a scan group in one launch, and overlap later scans.  A
  * window's result equals the result of scanning its pairs alone (Sections 3-4 are order-free).
  * ------------------------------------------------------------------------------------------ */
 typedef struct spd_server spd_server;
@@ -313,7 +313,8 @@ typedef struct spd_server_config {
     uint64_t hbm_budget_bytes;     /* device memory for slots and scratch (0: 4 GiB) */
     uint64_t max_group_pairs;      /* fused launch: at most this many pairs (0: 64 Mi) */
     uint32_t max_group_batches;    /* fused launch: at most this many batches (0: 1024) */
-    uint32_t use_graphs;           /* 1: replay each slot's end-of-window work from a hipGraph */
+    uint32_t use_graphs;           /* no longer used: the windows that a scan group completes are closed by one
+                                      kernel launch, so there is nothing to replay from a hipGraph */
     uint64_t min_scan_pairs;       /* while earlier scans are still running on the GPU, a router's queued
                                       pairs wait until this many are queued, its window can end, a close
                                       is requested or drain is called; an idle GPU takes whatever is

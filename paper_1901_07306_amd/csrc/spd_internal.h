@@ -314,11 +314,27 @@ struct CloseArgs {
     uint32_t parts_log2;   // each SEA's candidates are searched by 2^parts_log2 wavefronts
     uint32_t lp_mask[kMaxRows];   // the LP bits of each row
 };
+// What differs between the slots of a launch that closes several windows (bits only).
+struct CloseSlot {
+    const uint8_t *seav;
+    const uint32_t *ldca;
+    uint32_t *rec;
+    uint32_t *counters;
+    uint32_t *host_out;
+    uint32_t host_recs;
+    uint32_t rec_cap;
+};
+struct CloseTable {
+    CloseSlot s[kMaxGroup];
+};
 // LDS words per wavefront: every SE may be hot, then the queue.
 __host__ __device__ __forceinline__ uint32_t close_wave_words(uint32_t sea_bytes, uint32_t qcap) {
     return sea_bytes + qcap;
 }
 hipError_t launch_close(const Consts &c, const CloseArgs &a, int mode, uint32_t block, uint32_t grid, hipStream_t s);
+// The ends of n windows in one launch, grid workgroups each; a.counts holds kCloseCountBytes per window.
+hipError_t launch_close_many(const Consts &c, const CloseArgs &a, const CloseTable &t, uint32_t n, uint32_t block,
+                             uint32_t grid, hipStream_t s);
 // Workgroups of the end-of-window kernel that one compute unit holds at once (registers and LDS).
 uint32_t close_blocks_per_cu(int mode, uint32_t block, uint32_t sr, uint32_t lds_bytes);
 

@@ -2045,7 +2045,7 @@ __device__ __forceinline__ void filter_queue(const CloseArgs &a, const Consts &c
 // and 5 -> 28.)
 // RMAX: SR itself when it is 4, else 8 (the rows' registers).
 template <int MODE, int BLOCK, int RMAX>
-__global__ __launch_bounds__(BLOCK) void k_close(Consts c, CloseArgs a) {
+__device__ __forceinline__ void close_window(const Consts &c, const CloseArgs &a) {
     extern __shared__ uint32_t lds[];
     constexpr uint32_t NW = BLOCK / 64;
     constexpr uint32_t U = MODE == kCloseBits ? 8 : 2;   // words in flight per lane
@@ -2285,6 +2285,26 @@ __global__ __launch_bounds__(BLOCK) void k_close(Consts c, CloseArgs a) {
     __hip_atomic_store(a.host_out + 2, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+template <int MODE, int BLOCK, int RMAX>
+__global__ __launch_bounds__(BLOCK) void k_close(Consts c, CloseArgs a) { close_window<MODE, BLOCK, RMAX>(c, a); }
+
+// Several windows at once (the serving loop closes what a scan launch has completed): one window's close
+// waits for memory most of its time, so they run side by side, blockIdx.y naming the window.  16 windows
+// of 4 Mi pairs: 500 us one after another (13.5 us each, and the launches between them).
+template <int BLOCK, int RMAX>
+__global__ __launch_bounds__(BLOCK) void k_close_many(Consts c, CloseArgs a, CloseTable t) {
+    const CloseSlot s = t.s[blockIdx.y];
+    a.seav = s.seav;
+    a.ldca = s.ldca;
+    a.rec = s.rec;
+    a.counters = s.counters;
+    a.counts += blockIdx.y * (kCloseCountBytes / 8);
+    a.host_out = s.host_out;
+    a.host_recs = s.host_recs;
+    a.rec_cap = s.rec_cap;
+    close_window<kCloseBits, BLOCK, RMAX>(c, a);
+}
+
 // The instance for a mode, a workgroup size and a row count.
 typedef void (*CloseKernel)(Consts, CloseArgs);
 template <int MODE, int BLOCK>
@@ -2315,6 +2335,20 @@ hipError_t launch_close(const Consts &c, const CloseArgs &a, int mode, uint32_t 
     if (!k) return hipErrorInvalidConfiguration;
     const uint32_t lds = (block / 64) * close_wave_words(c.sea_bytes, a.qcap) * 4u;
     hipLaunchKernelGGL(k, dim3(grid), dim3(block), lds, s, c, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_close_many(const Consts &c, const CloseArgs &a, const CloseTable &t, uint32_t n, uint32_t block,
+                             uint32_t grid, hipStream_t s) {
+    if (n == 0 || n > (uint32_t)kMaxGroup) return hipErrorInvalidValue;
+    const bool four = c.sr == 4;
+    void (*k)(Consts, CloseArgs, CloseTable) = nullptr;
+    if (block == 256) k = four ? k_close_many<256, 4> : k_close_many<256, 8>;
+    else if (block == 128) k = four ? k_close_many<128, 4> : k_close_many<128, 8>;
+    else if (block == 64) k = four ? k_close_many<64, 4> : k_close_many<64, 8>;
+    else return hipErrorInvalidConfiguration;
+    const uint32_t lds = (block / 64) * close_wave_words(c.sea_bytes, a.qcap) * 4u;
+    hipLaunchKernelGGL(k, dim3(grid, n), dim3(block), lds, s, c, a, t);
     return hipGetLastError();
 }
 

@@ -59,9 +59,6 @@ struct CloseBuf {
     uint32_t h_rec_cap = 0;
     bool empty = false;               // the slot was fresh: nothing was launched
     uint32_t seq = 0;                 // the sequence number the last enqueued close will write
-    hipGraphExec_t graph = nullptr;   // captured close of graph_slot
-    const Slot *graph_slot = nullptr;
-    const uint32_t *graph_rec = nullptr;
 };
 
 }  // namespace
@@ -117,8 +114,9 @@ struct spd_ctx {
     double small_gain = 0.0;         // what small scans without scratch would have saved with it (us)
     uint32_t list_parity = 0;        // region layout: which of two tile-list counts the next launch uses
     CloseBuf cbuf;                  // end-of-window buffers of spd_close_window
-    uint64_t *close_counts = nullptr;   // finished workgroups of the running close (a context's closes
-                                        // run one after another)
+    uint64_t *close_counts = nullptr;   // finished workgroups of the running close (a context's launches
+                                        // of closes run one after another), per window of a launch
+    uint32_t close_windows = 1;         // windows one launch closes at most: kMaxGroup in the serving loop
     Slot *merge_into = nullptr;     // spd_scan_batches_merge: the global slot, while its scan runs
     bool merge_group = false;       // the region launch being enqueued covers the whole merged call
     bool merged = false;            // the merge was fused into that launch's apply phase
@@ -1185,9 +1183,10 @@ spd_status close_buf_init(spd_ctx *ctx, CloseBuf &cb) {
         if (st) return st;
     }
     if (!ctx->close_counts) {
-        spd_status st = dev_alloc(ctx, &ctx->close_counts, kCloseCountBytes);
+        const uint64_t bytes = (uint64_t)ctx->close_windows * kCloseCountBytes;
+        spd_status st = dev_alloc(ctx, &ctx->close_counts, bytes);
         if (st) return st;
-        SPD_HIP(ctx, hipMemset(ctx->close_counts, 0, kCloseCountBytes));   // once; each launch leaves them zero
+        SPD_HIP(ctx, hipMemset(ctx->close_counts, 0, bytes));   // once; each launch leaves them zero
     }
     if (!cb.h_counters) {
         SPD_HIP(ctx, hipHostMalloc((void **)&cb.h_counters, 16 + (uint64_t)kRecChunk * 8, hipHostMallocMapped));
@@ -1198,8 +1197,6 @@ spd_status close_buf_init(spd_ctx *ctx, CloseBuf &cb) {
 }
 
 void close_buf_free(spd_ctx *ctx, CloseBuf &cb) {
-    if (cb.graph) (void)hipGraphExecDestroy(cb.graph);
-    cb.graph = nullptr;
     dev_free(ctx, &cb.counters, 16 + (uint64_t)cb.rec_cap * 8);
     cb.rec = nullptr;
     if (cb.h_counters) (void)hipHostFree(cb.h_counters);
@@ -1301,38 +1298,33 @@ spd_status close_launch(spd_ctx *ctx, const Slot &sl, CloseBuf &cb, hipStream_t 
     return close_launch_ops(ctx, sl, cb, s);
 }
 
-// Same device work replayed from a hipGraph captured once per (slot, buffer); discrete mode only.
-spd_status close_launch_graph(spd_ctx *ctx, const Slot &sl, CloseBuf &cb, hipStream_t s) {
-    cb.empty = sl.fresh;
-    if (cb.empty) return SPD_OK;
-    spd_status st = close_buf_init(ctx, cb);
-    if (st) return st;
-    if (!cb.graph || cb.graph_slot != &sl || cb.graph_rec != cb.rec) {
-        if (cb.graph) (void)hipGraphExecDestroy(cb.graph);
-        cb.graph = nullptr;
-        hipGraph_t g = nullptr;
-        const bool prof = ctx->prof_on;
-        ctx->prof_on = false;   // no event nodes inside the graph
-        const uint32_t seq = cb.seq;   // (capture runs nothing)
-        SPD_HIP(ctx, hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-        spd_status cst = close_launch_ops(ctx, sl, cb, s);
-        hipError_t e = hipStreamEndCapture(s, &g);
-        cb.seq = seq;
-        ctx->prof_on = prof;
-        if (cst) {
-            if (g) (void)hipGraphDestroy(g);
-            return cst;
-        }
-        if (e != hipSuccess) return hip_fail(ctx, e, "hipStreamEndCapture");
-        e = hipGraphInstantiate(&cb.graph, g, nullptr, nullptr, 0);
-        (void)hipGraphDestroy(g);
-        if (e != hipSuccess) return hip_fail(ctx, e, "hipGraphInstantiate");
-        cb.graph_slot = &sl;
-        cb.graph_rec = cb.rec;
+// The end of window of several slots in one launch (discrete mode, the serving loop's slots).
+spd_status close_launch_many(spd_ctx *ctx, const std::vector<std::pair<const Slot *, CloseBuf *>> &closes, hipStream_t s) {
+    std::vector<std::pair<const Slot *, CloseBuf *>> work;
+    for (auto &w : closes) {
+        w.second->empty = w.first->fresh;
+        if (w.second->empty) continue;
+        spd_status st = close_buf_init(ctx, *w.second);
+        if (st) return st;
+        work.push_back(w);
     }
-    ProfScope ps(ctx, SPD_K_CLOSE, s);
-    SPD_HIP(ctx, hipGraphLaunch(cb.graph, s));
-    ++cb.seq;
+    for (size_t i0 = 0; i0 < work.size(); i0 += kMaxGroup) {
+        const uint32_t n = (uint32_t)std::min<size_t>(kMaxGroup, work.size() - i0);
+        CloseArgs a;
+        CloseTable t{};
+        uint32_t block = 0, grid = 0;
+        for (uint32_t k = 0; k < n; ++k) {
+            const CloseBuf &cb = *work[i0 + k].second;
+            spd_status st = close_args(ctx, *work[i0 + k].first, cb, &a, &block, &grid);
+            if (st) return st;
+            t.s[k] = CloseSlot{a.seav, a.ldca, a.rec, a.counters, a.host_out, a.host_recs, a.rec_cap};
+        }
+        // two rounds of resident workgroups over all windows
+        grid = std::min(grid, std::max(64u, (2 * grid + n - 1) / n));
+        ProfScope ps(ctx, SPD_K_CLOSE, s);
+        SPD_HIP(ctx, launch_close_many(ctx->c, a, t, n, block, grid, s));
+        for (uint32_t k = 0; k < n; ++k) ++work[i0 + k].second->seq;
+    }
     return SPD_OK;
 }
 
@@ -1428,6 +1420,7 @@ spd_status ctx_create(const spd_params *p, uint32_t n_routers, uint32_t n_slots,
     ctx->budget = budget;
     ctx->sliding = p->window_slices > 0;
     ctx->K = p->window_slices;
+    if (n_routers == 0) ctx->close_windows = kMaxGroup;   // the serving loop's
     ctx->at = ctx->sliding && p->sliding_counter == 0;
     ctx->at_groups = ctx->at ? kAtCodes - 1u - ctx->K : 0;   // K + G = 255: ages read mod 256 stay exact
     default_tuning(&ctx->tune);
@@ -1550,7 +1543,7 @@ void spd_destroy(spd_ctx *ctx) {
         }
         if (ctx->h2d_s) (void)hipStreamDestroy(ctx->h2d_s);
         close_buf_free(ctx, ctx->cbuf);
-        dev_free(ctx, &ctx->close_counts, kCloseCountBytes);
+        dev_free(ctx, &ctx->close_counts, (uint64_t)ctx->close_windows * kCloseCountBytes);
         for (auto &pc : ctx->pend) {
             close_buf_free(ctx, pc.cb);
             if (pc.done) (void)hipEventDestroy(pc.done);
@@ -2089,6 +2082,7 @@ struct SrvClosing {
     uint64_t pairs;
     Clock::time_point t_req;
     hipEvent_t done;
+    bool last;                    // of the closes that share `done`
 };
 
 struct SrvResult {
@@ -2100,7 +2094,7 @@ struct SrvResult {
 struct spd_server {
     spd_ctx *ctx = nullptr;       // method constants, kernels, scratch, profiler; its slots are the pool
     spd_server_config cfg{};
-    std::vector<CloseBuf> cbs;    // one per slot (with its captured graph)
+    std::vector<CloseBuf> cbs;    // one per slot
     std::vector<int> free_slots;
     std::vector<SrvRouter> routers;
     std::deque<SrvClosing> closing;
@@ -2171,7 +2165,7 @@ bool srv_reap(spd_server *S, bool block) {
         {
             std::lock_guard<std::mutex> lk(S->mu);
             S->closing.pop_front();
-            S->ev_pool.push_back(c.done);
+            if (c.last) S->ev_pool.push_back(c.done);
             S->free_slots.push_back(c.slot);
             S->done.push_back(std::move(res));
             S->st.windows++;
@@ -2285,36 +2279,32 @@ void srv_loop(spd_server *S) {
             if (!st && hipEventRecord(S->scan_ev, S->scan_s) != hipSuccess) st = SPD_E_HIP;
             S->scan_ev_set = !st;
         }
-        size_t pushed = 0;
-        for (auto &c : closes) {
-            if (st) break;
-            hipEvent_t scanned = srv_event(S), fin = srv_event(S);
-            if (!scanned || !fin) {
-                st = SPD_E_HIP;
-                break;
+        // the closes wait only for the scans issued so far (later groups overlap them) and run in one
+        // launch, side by side; one event tells that they have finished
+        if (!st && !closes.empty()) {
+            hipEvent_t scanned = nullptr, fin = nullptr;
+            {
+                std::lock_guard<std::mutex> g(S->mu);
+                scanned = srv_event(S);
+                fin = srv_event(S);
             }
-            // the close waits only for the scans issued so far; later groups overlap it
-            if (hipEventRecord(scanned, S->scan_s) != hipSuccess || hipStreamWaitEvent(S->close_s, scanned, 0) != hipSuccess) {
+            if (!scanned || !fin || hipEventRecord(scanned, S->scan_s) != hipSuccess ||
+                hipStreamWaitEvent(S->close_s, scanned, 0) != hipSuccess)
                 st = SPD_E_HIP;
-                break;
-            }
-            Slot &sl = S->ctx->slots[c.slot];
-            st = S->cfg.use_graphs ? close_launch_graph(S->ctx, sl, S->cbs[c.slot], S->close_s)
-                                   : close_launch(S->ctx, sl, S->cbs[c.slot], S->close_s);
-            if (st) break;
-            if (hipEventRecord(fin, S->close_s) != hipSuccess) {
-                st = SPD_E_HIP;
-                break;
-            }
+            std::vector<std::pair<const Slot *, CloseBuf *>> work;
+            for (auto &c : closes) work.emplace_back(&S->ctx->slots[c.slot], &S->cbs[c.slot]);
+            if (!st) st = close_launch_many(S->ctx, work, S->close_s);
+            if (!st && hipEventRecord(fin, S->close_s) != hipSuccess) st = SPD_E_HIP;
             std::lock_guard<std::mutex> g(S->mu);
-            S->ev_pool.push_back(scanned);   // reusable once recorded again later (ordering kept by the stream)
-            S->closing.push_back(SrvClosing{c.slot, c.router, c.window, c.pairs, c.t_req, fin});
-            S->launching--;
-            ++pushed;
-        }
-        if (pushed < closes.size()) {
+            if (!st) {
+                S->ev_pool.push_back(scanned);   // reusable once recorded again later (ordering kept by the stream)
+                for (auto &c : closes)
+                    S->closing.push_back(SrvClosing{c.slot, c.router, c.window, c.pairs, c.t_req, fin, &c == &closes.back()});
+            }
+            S->launching -= (uint32_t)closes.size();
+        } else if (!closes.empty()) {
             std::lock_guard<std::mutex> g(S->mu);
-            S->launching -= (uint32_t)(closes.size() - pushed);
+            S->launching -= (uint32_t)closes.size();
         }
         if (st) {
             srv_fault(S, st);
