@@ -276,7 +276,8 @@ hipError_t launch_apply(const BinGeometry &g, const ApplySlot *slots, uint32_t n
 hipError_t launch_apply_bm(const BinGeometry &g, const ApplySlot *slots, uint32_t n_slots, const uint32_t *items,
                            const uint32_t *base, uint32_t block, uint32_t unroll, hipStream_t s);
 hipError_t launch_apply_rg(const Consts &c, const BinGeometry &g, const ApplySlot *slots, uint32_t n_slots,
-                           const ChunkTable &ct, const RegionArgs &ra, uint32_t block, uint32_t unroll, hipStream_t s, KTiming kt = {});
+                           const ChunkTable &ct, const RegionArgs &ra, uint32_t block, uint32_t unroll, hipStream_t s,
+                           KTiming kt = {});
 // The apply phase with the router OR merge fused in: the global sketch (its LDCA and SEAV) :=
 // OR of the launch's slots; 1024-lane workgroups, buckets of at most 2^20 bits.
 hipError_t launch_apply_rg_merge(const Consts &c, const BinGeometry &g, const ApplySlot *slots, uint32_t n_slots,

@@ -1192,9 +1192,8 @@ hipError_t launch_clear(const ClearList &clear, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Apply phase of the region layout: one workgroup per (slot, bucket) ORs the used part of the
-// bucket's region in each of the slot's chunks into an LDS bitmap.  Work is split into pieces of
-// 64 * U words (one per wavefront at a time); a piece past its region's fill is skipped.
+// Apply phase of the region layout: one workgroup per (slot, bucket) ORs the used part of the bucket's
+// region in each of the slot's chunks into an LDS bitmap.
 __device__ __forceinline__ void apply_word(uint32_t *bm, uint64_t v) {
 #pragma unroll
     for (uint32_t f = 0; f < 3; ++f) {
@@ -1254,13 +1253,13 @@ __device__ __forceinline__ void apply_segments(const SpillSeg *__restrict__ seg,
     }
 }
 
-// The sampled pairs of the slot's listed tiles whose SEAV bits lie in this bucket (first_bit: the
-// bucket's first bit of the SEAV).  Rare, and wide: the method constants are read from the kernel
+// The sampled pairs of the slot's listed tiles whose SEAV bits lie in this bucket (n_bits of the SEAV
+// from first_bit on).  Rare, and wide: the method constants are read from the kernel
 // arguments (they are the first one) behind an opaque pointer, so that nothing of this is loaded on
 // the path of a launch that lists no tile.
 typedef __attribute__((address_space(4))) const Consts ArgConsts;
 template <int BLOCK>
-__device__ __forceinline__ void apply_listed(const RegionArgs &ra, uint32_t n, uint32_t si, uint32_t S, uint64_t first_bit,
+__device__ __forceinline__ void apply_listed(const RegionArgs &ra, uint32_t n, uint32_t si, uint64_t first_bit, uint32_t n_bits,
                                              uint32_t *bm) {
     auto args = __builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(args));
@@ -1276,82 +1275,115 @@ __device__ __forceinline__ void apply_listed(const RegionArgs &ra, uint32_t n, u
             const uint32_t rp = pr.x & c.rmask, lp = (uint32_t)((uint64_t)pr.x >> c.r);
             for (uint32_t r = 0; r < c.sr; ++r) {
                 const uint32_t byte = rp * c.sea_bytes + c.row_off[r] + row_index(lp, c.isb[r], c.ibn[r], c.L);
-                const uint64_t bit = (uint64_t)byte * 8u + b - first_bit;   // (wraps below the bucket)
-                if (bit >> S) continue;
+                const uint64_t bit = (uint64_t)byte * 8u + b - first_bit;   // (wraps below the part)
+                if (bit >= n_bits) continue;
                 atomicOr(&bm[bit >> 5], 1u << (bit & 31u));
             }
         }
     }
 }
 
-// Bucket b of slot si: loaded into the LDS bitmap bm (zero for a fresh slot: nothing else writes a
-// slot's memory during a launch), the filled part of the bucket's region in every chunk of the slot,
-// then its listed segments and tiles, applied with LDS atomicOr, the counters read zeroed for the
-// next launch, the bitmap stored back.  Ends with bm complete and visible to the whole workgroup.
+// Bucket b of slot si: loaded into the LDS bitmap bm (zero for a fresh slot:
+// nothing else writes a slot's memory during a launch), the filled part of the bucket's region in every
+// chunk of the slot, then its listed segments and tiles, applied with LDS atomicOr, the counters read
+// zeroed for the next launch, the bitmap stored back.  Ends with bm complete and visible to the whole
+// workgroup.
+// Bound by the LDS atomics of random words (about 9 items per ns and compute unit) for crowded buckets.
+// The region's words come in pieces of 64 * U, which the wavefronts take from a counter as they get
+// free.  (Dealt out in turn, 6 to 8 of a bucket's 37 us went by until the last wavefront had ended: 64 Mi
+// pairs, 83 -> 73 us; 5 Mi, 27 -> 23.5 us.)
 template <int BLOCK, int U>
 __device__ __forceinline__ void apply_bucket(const BinGeometry &g, const ApplySlot &A, uint32_t si, uint32_t b,
                                              const ChunkTable &ct, const RegionArgs &ra, uint32_t *bm) {
-    constexpr uint32_t NW = BLOCK / 64, PIECE = 64 * U;
+    constexpr uint32_t PIECE = 64 * U;
     const uint32_t words = 1u << (g.S - 5);
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     uint32_t *dst = b < g.nb_ldca ? A.ldca + (uint64_t)b * words : A.seav_w + (uint64_t)(b - g.nb_ldca) * words;
-    if (A.fresh) {
-        for (uint32_t w = tid; w < words; w += BLOCK) bm[w] = 0;
-    } else {
-        for (uint32_t w = tid; w < words; w += BLOCK) bm[w] = dst[w];
-    }
+    const uint32_t words4 = words / 4;
+    u32x4 *bm4 = reinterpret_cast<u32x4 *>(bm), *dst4 = reinterpret_cast<u32x4 *>(dst);
     const uint32_t n_seg = ra.seg_n[si * g.nb + b], n_tile = b < g.nb_ldca ? 0u : *ra.tile_n;
-    __syncthreads();
+    // the slot's chunks (at most kXcds + 1), one per lane: words filled, pieces, and pieces up to here
     const uint32_t c0 = ct.cbase[si], nch = ct.cbase[si + 1] - c0;
-    // pieces of PIECE words, dealt to the wavefronts in turn over all chunks
-    uint32_t p0 = wid;   // this wavefront's next piece, counted from the chunk's first
-    for (uint32_t cc = 0; cc < nch; ++cc) {
-        uint32_t cap_c;
-        const uint64_t at = chunk_at(ra, si, cc) + region_in(ra, g.nb_ldca, si, cc, b, &cap_c);
-        uint32_t len = ra.cur[(uint64_t)(c0 + cc) * g.nb + b];
-        len = len < cap_c ? len : cap_c;
-        const uint32_t np = (len + PIECE - 1) / PIECE;
-        const uint64_t *src = ra.items + at;
-        for (; p0 < np; p0 += NW) {
-            const uint32_t w0 = p0 * PIECE;
-            uint64_t v[U];
+    uint32_t cap_c = 0;
+    const uint32_t in_full = region_in(ra, g.nb_ldca, si, 0, b, &cap_c), cap_full = cap_c;
+    const uint32_t in_last = region_in(ra, g.nb_ldca, si, nch - 1, b, &cap_c), cap_last = cap_c;
+    uint32_t len = lane < nch ? ra.cur[(uint64_t)(c0 + lane) * g.nb + b] : 0u;
+    uint32_t *next_piece = bm + words;   // (after the bitmap, which has to start on 16 bytes)
+    if (tid == 0) *next_piece = 0;
+    if (A.fresh) {
+        for (uint32_t w = tid; w < words4; w += BLOCK) bm4[w] = u32x4{0u, 0u, 0u, 0u};
+        for (uint32_t w = words4 * 4 + tid; w < words; w += BLOCK) bm[w] = 0;
+    } else {
+        // eight 16-byte loads of a lane in flight (word by word, each waiting for the one before, took 20
+        // of a bucket's 24 us)
+        for (uint32_t w = tid; w < words4; w += 8 * BLOCK) {
+            u32x4 x[8];
 #pragma unroll
-            for (uint32_t k = 0; k < U; ++k) {
-                const uint32_t ww = w0 + k * 64 + lane;
-                v[k] = __builtin_nontemporal_load(src + (ww < len ? ww : len - 1));   // unconditional loads
-            }
+            for (uint32_t k = 0; k < 8; ++k) x[k] = dst4[w + k * BLOCK < words4 ? w + k * BLOCK : w];
 #pragma unroll
-            for (uint32_t k = 0; k < U; ++k)
-                if (w0 + k * 64 + lane < len) apply_word(bm, v[k]);
+            for (uint32_t k = 0; k < 8; ++k)
+                if (w + k * BLOCK < words4) bm4[w + k * BLOCK] = x[k];
         }
-        p0 -= np;
+        for (uint32_t w = words4 * 4 + tid; w < words; w += BLOCK) bm[w] = dst[w];
+    }
+    if (lane < nch) {
+        const uint32_t cap = lane == nch - 1 ? cap_last : cap_full;
+        len = len < cap ? len : cap;
+    }
+    const uint32_t np = (len + PIECE - 1) / PIECE, upto = wave_scan(np);
+    const uint32_t n_piece = __builtin_amdgcn_readlane(upto, 63);
+    __syncthreads();
+    auto take = [&]() -> uint32_t {
+        uint32_t p = 0;
+        if (lane == 0) p = atomicAdd(next_piece, 1u);
+        return __builtin_amdgcn_readfirstlane(p);
+    };
+    auto fetch = [&](uint32_t p, uint64_t (&v)[U], uint32_t &left) {   // p < n_piece
+        const uint32_t cc = (uint32_t)__popcll(__ballot(upto <= p));
+        const uint32_t l = __builtin_amdgcn_readlane(len, cc);
+        const uint32_t w0 = (p - (__builtin_amdgcn_readlane(upto, cc) - __builtin_amdgcn_readlane(np, cc))) * PIECE;
+        const uint64_t *src = ra.items + chunk_at(ra, si, cc) + (cc == nch - 1 ? in_last : in_full) + w0;
+        left = l - w0;
+#pragma unroll
+        for (uint32_t k = 0; k < U; ++k) {
+            const uint32_t w = k * 64 + lane;
+            v[k] = __builtin_nontemporal_load(src + (w < left ? w : left - 1));   // unconditional loads
+        }
+    };
+    auto apply = [&](const uint64_t (&v)[U], uint32_t left) {
+#pragma unroll
+        for (uint32_t k = 0; k < U; ++k)
+            if (k * 64 + lane < left) apply_word(bm, v[k]);
+    };
+    for (uint32_t p = take(); p < n_piece;) {
+        uint64_t v[U];
+        uint32_t left;
+        fetch(p, v, left);
+        p = take();
+        apply(v, left);
     }
     if (n_seg) {
         const uint32_t lo = ct.lo[si], nt = ct.hi[si] - lo;
-        apply_segments<BLOCK, U>(ra.seg + (uint64_t)lo * g.nb + (uint64_t)b * nt, n_seg, ra.spill_w, wid, lane, bm);
+        apply_segments<BLOCK, 2 * U>(ra.seg + (uint64_t)lo * g.nb + (uint64_t)b * nt, n_seg, ra.spill_w, wid, lane, bm);
     }
-    if (n_tile) apply_listed<BLOCK>(ra, n_tile, si, g.S, (uint64_t)(b - g.nb_ldca) << g.S, bm);
+    if (n_tile) apply_listed<BLOCK>(ra, n_tile, si, (uint64_t)(b - g.nb_ldca) << g.S, words * 32u, bm);
     __syncthreads();
     // the counters of this (slot, bucket) start the next launch at zero, and so does its tile count
-    for (uint32_t cc = tid; cc < nch; cc += BLOCK) ra.cur[(uint64_t)(c0 + cc) * g.nb + b] = 0u;
-    if (tid == 0) ra.seg_n[si * g.nb + b] = 0u;
-    if (tid == 0 && b == 0 && si == 0) *ra.tile_next = 0u;
-    const uint32_t words4 = words / 4;
-    if (words4) {
-        for (uint32_t w = tid; w < words4; w += BLOCK)
-            reinterpret_cast<u32x4 *>(dst)[w] = reinterpret_cast<const u32x4 *>(bm)[w];
-    } else {
-        for (uint32_t w = tid; w < words; w += BLOCK) dst[w] = bm[w];
+    if (tid < nch) ra.cur[(uint64_t)(c0 + tid) * g.nb + b] = 0u;
+    if (tid == 0) {
+        ra.seg_n[si * g.nb + b] = 0u;
+        if (b == 0 && si == 0) *ra.tile_next = 0u;
     }
+    for (uint32_t w = tid; w < words4; w += BLOCK) dst4[w] = bm4[w];
+    for (uint32_t w = words4 * 4 + tid; w < words; w += BLOCK) dst[w] = bm[w];
 }
 
 // One workgroup per (slot, bucket).  (The first argument is read by apply_listed.)
 template <int BLOCK, int U>
 __global__ __launch_bounds__(BLOCK) void k_apply_rg(Consts, BinGeometry g, ApplyTable at, ChunkTable ct, RegionArgs ra) {
-    extern __shared__ uint32_t bm[];
-    const uint32_t blk = blockIdx.x;
-    const uint32_t si = blk / g.nb, b = blk % g.nb;
+    extern __shared__ __align__(16) uint32_t bm[];
+    const uint32_t si = blockIdx.x / g.nb, b = blockIdx.x % g.nb;
     apply_bucket<BLOCK, U>(g, at.s[si], si, b, ct, ra, bm);
 }
 
@@ -1362,7 +1394,7 @@ __global__ __launch_bounds__(BLOCK) void k_apply_rg(Consts, BinGeometry g, Apply
 template <int U>
 __global__ __launch_bounds__(1024) void k_apply_rg_merge(Consts, BinGeometry g, ApplyTable at, uint32_t n_slots,
                                                          ChunkTable ct, RegionArgs ra, ApplySlot gs) {
-    extern __shared__ uint32_t bm[];
+    extern __shared__ __align__(16) uint32_t bm[];
     constexpr uint32_t BLOCK = 1024, PER = 32;   // words per lane of a 2^20-bit bucket
     const uint32_t words = 1u << (g.S - 5);
     const uint32_t tid = threadIdx.x, b = blockIdx.x;
@@ -1383,8 +1415,8 @@ __global__ __launch_bounds__(1024) void k_apply_rg_merge(Consts, BinGeometry g, 
 }
 
 template <int U>
-static void launch_apply_rg_u(const Consts &c, const BinGeometry &g, const ApplyTable &at, const ChunkTable &ct, const RegionArgs &ra,
-                              dim3 grid, uint32_t lds, uint32_t block, hipStream_t s, KTiming kt) {
+static void launch_apply_rg_u(const Consts &c, const BinGeometry &g, const ApplyTable &at, const ChunkTable &ct,
+                              const RegionArgs &ra, dim3 grid, uint32_t lds, uint32_t block, hipStream_t s, KTiming kt) {
     if (block == 1024)
         hipExtLaunchKernelGGL((k_apply_rg<1024, U>), grid, dim3(1024), lds, s, kt.start, kt.stop, 0, c, g, at, ct, ra);
     else if (block == 512)
@@ -1393,17 +1425,21 @@ static void launch_apply_rg_u(const Consts &c, const BinGeometry &g, const Apply
 }
 
 hipError_t launch_apply_rg(const Consts &c, const BinGeometry &g, const ApplySlot *slots, uint32_t n_slots,
-                           const ChunkTable &ct, const RegionArgs &ra, uint32_t block, uint32_t unroll, hipStream_t s, KTiming kt) {
+                           const ChunkTable &ct, const RegionArgs &ra, uint32_t block, uint32_t unroll, hipStream_t s,
+                           KTiming kt) {
     ApplyTable at{};
     if (n_slots == 0 || n_slots > (uint32_t)kMaxGroup || ct.n != n_slots) return hipErrorInvalidValue;
     if (block != 1024 && block != 512 && block != 256) return hipErrorInvalidConfiguration;
-    for (uint32_t i = 0; i < n_slots; ++i) at.s[i] = slots[i];
-    const uint32_t lds = (1u << (g.S - 5)) * 4u;
-    dim3 grid(n_slots * g.nb);
+    for (uint32_t i = 0; i < n_slots; ++i) {
+        at.s[i] = slots[i];
+        if (ct.cbase[i + 1] - ct.cbase[i] > 64u) return hipErrorInvalidValue;   // a lane per chunk
+    }
+    const uint32_t lds = (1u << (g.S - 5)) * 4u + 16u;
+    const dim3 grid(n_slots * g.nb);
     switch (unroll) {
-    case 8: launch_apply_rg_u<4>(c, g, at, ct, ra, grid, lds, block, s, kt); break;
-    case 16: launch_apply_rg_u<8>(c, g, at, ct, ra, grid, lds, block, s, kt); break;
-    case 32: launch_apply_rg_u<16>(c, g, at, ct, ra, grid, lds, block, s, kt); break;
+    case 8: launch_apply_rg_u<2>(c, g, at, ct, ra, grid, lds, block, s, kt); break;
+    case 16: launch_apply_rg_u<4>(c, g, at, ct, ra, grid, lds, block, s, kt); break;
+    case 32: launch_apply_rg_u<8>(c, g, at, ct, ra, grid, lds, block, s, kt); break;
     default: return hipErrorInvalidConfiguration;
     }
     return hipGetLastError();
@@ -1414,13 +1450,16 @@ hipError_t launch_apply_rg_merge(const Consts &c, const BinGeometry &g, const Ap
                                  hipStream_t s, KTiming kt) {
     ApplyTable at{};
     if (n_slots == 0 || n_slots > (uint32_t)kMaxGroup || ct.n != n_slots || g.S > 20) return hipErrorInvalidValue;
-    for (uint32_t i = 0; i < n_slots; ++i) at.s[i] = slots[i];
-    const uint32_t lds = (1u << (g.S - 5)) * 4u;
+    for (uint32_t i = 0; i < n_slots; ++i) {
+        at.s[i] = slots[i];
+        if (ct.cbase[i + 1] - ct.cbase[i] > 64u) return hipErrorInvalidValue;   // a lane per chunk
+    }
+    const uint32_t lds = (1u << (g.S - 5)) * 4u + 16u;
     const dim3 grid(g.nb), block(1024);
     switch (unroll) {
-    case 8: hipExtLaunchKernelGGL((k_apply_rg_merge<4>), grid, block, lds, s, kt.start, kt.stop, 0, c, g, at, n_slots, ct, ra, global); break;
-    case 16: hipExtLaunchKernelGGL((k_apply_rg_merge<8>), grid, block, lds, s, kt.start, kt.stop, 0, c, g, at, n_slots, ct, ra, global); break;
-    case 32: hipExtLaunchKernelGGL((k_apply_rg_merge<16>), grid, block, lds, s, kt.start, kt.stop, 0, c, g, at, n_slots, ct, ra, global); break;
+    case 8: hipExtLaunchKernelGGL((k_apply_rg_merge<2>), grid, block, lds, s, kt.start, kt.stop, 0, c, g, at, n_slots, ct, ra, global); break;
+    case 16: hipExtLaunchKernelGGL((k_apply_rg_merge<4>), grid, block, lds, s, kt.start, kt.stop, 0, c, g, at, n_slots, ct, ra, global); break;
+    case 32: hipExtLaunchKernelGGL((k_apply_rg_merge<8>), grid, block, lds, s, kt.start, kt.stop, 0, c, g, at, n_slots, ct, ra, global); break;
     default: return hipErrorInvalidConfiguration;
     }
     return hipGetLastError();
@@ -1552,7 +1591,7 @@ template <int BLOCK, int U>
 __global__ __launch_bounds__(BLOCK) void k_apply_bm(BinGeometry g, ApplyTable at, const uint64_t *__restrict__ items,
                                                     const uint32_t *__restrict__ base) {
     // U: 8-byte loads in flight per lane
-    extern __shared__ uint32_t bm[];
+    extern __shared__ __align__(16) uint32_t bm[];
     const uint32_t words = 1u << (g.S - 5);
     const uint32_t tid = threadIdx.x;
     const uint32_t blk = blockIdx.x;
