@@ -105,24 +105,21 @@ __host__ __device__ __forceinline__ uint32_t at_active(uint32_t v, uint32_t ct, 
 }
 constexpr uint32_t kAtMaxK = 254;   // G = 255 - K >= 1
 
-// The same test on the four counters of a 32-bit word at once.  Per byte, e = (ct - v) mod 256 without
-// borrows between bytes; e < K for K <= 128 is "top bit clear and the low 7 bits below K".  For a larger
-// K the complement is tested: 255 - e < 256 - K (at most 127) says that the counter is not active.
+// The same test on the four counters of a 32-bit word at once.  Per byte f = (v - ct + K - 1) mod 256,
+// which is below K iff the counter is active: iff f + (256 - K) carries nothing out of the byte.
 struct AtView {
-    uint32_t ct4;    // the current slice's code in every byte
-    uint32_t k4;     // min(K, 256 - K) in every byte
-    uint32_t flip;   // all ones when K > 128
+    uint32_t b, b7;    // (K - 1 - ct) mod 256 in every byte, and its low 7 bits
+    uint32_t c, c7;    // 256 - K in every byte, and its low 7 bits
 };
 __host__ __device__ __forceinline__ AtView at_view(uint32_t ct, uint32_t K) {
-    const bool wide = K > 128u;
-    return AtView{ct * 0x01010101u, (wide ? 256u - K : K) * 0x01010101u, wide ? ~0u : 0u};
+    const uint32_t b = ((K - 1u - ct) & 255u) * 0x01010101u, c = (256u - K) * 0x01010101u;   // 1 <= K <= kAtMaxK
+    return AtView{b, b & 0x7F7F7F7Fu, c, c & 0x7F7F7F7Fu};
 }
-// Bit 7 of byte j of the result is set iff counter j of w is active.
-__host__ __device__ __forceinline__ uint32_t at_active4(uint32_t w, const AtView &a) {
-    constexpr uint32_t H = 0x80808080u, L = 0x7F7F7F7Fu;
-    const uint32_t e = (((a.ct4 | H) - (w & L)) ^ ((a.ct4 ^ ~w) & H)) ^ a.flip;
-    const uint32_t d = ((e & L) | H) - a.k4;   // top bit: low 7 bits of e at least k4
-    return (~(e | d) ^ a.flip) & H;
+// Bit 7 of byte j of the result is set iff counter j of w is active (the other bits are arbitrary).
+__device__ __forceinline__ uint32_t at_flags4(uint32_t w, const AtView &a) {
+    const uint32_t s = (w & 0x7F7F7F7Fu) + a.b7, t = (s & 0x7F7F7F7Fu) + a.c7;
+    const uint32_t f = __builtin_amdgcn_bitop3_b32(s, w, a.b, 0x96);   // exclusive or of the three
+    return __builtin_amdgcn_bitop3_b32(f, a.c, t, 0x17);               // not their majority, which is the carry
 }
 
 // What the end-of-window kernel reads: bits, 16-bit time stamps, or AT counters.

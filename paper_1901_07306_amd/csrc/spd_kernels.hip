@@ -331,8 +331,8 @@ hipError_t launch_at_merge(uint8_t *dst, const uint8_t *const *src, uint32_t n_s
 
 // The bits of eight counters (two words) as one byte: counter j of a at bit j, of b at bit 4 + j.
 __device__ __forceinline__ uint32_t at_byte(uint32_t a, uint32_t b, const AtView &v) {
-    const uint32_t p = (at_active4(a, v) >> 7) | (at_active4(b, v) >> 3);   // bits 8 j and 8 j + 4
-    return (p | p >> 7 | p >> 14 | p >> 21) & 0xFFu;
+    const uint32_t p = ((at_flags4(a, v) >> 4) & 0x08080808u) | (at_flags4(b, v) & 0x80808080u);   // bits 8 j + 3 and 8 j + 7
+    return (p * 0x00204081u) >> 24;   // bit 8 j + 3 moves by 21 - 7 j (no two bits meet)
 }
 // 32 counters (two 16-byte vectors) as one word of bits, in order.
 __device__ __forceinline__ uint32_t at_word(const u32x4 &x, const u32x4 &y, const AtView &v) {
@@ -1909,19 +1909,48 @@ __device__ __forceinline__ uint32_t decode_raw(const CloseArgs &a, const RawWord
         return v;
     }
 }
-// The ones of an LDC word.  AT counters are packed in a fixed permuted order (counter 4h + j at bit
-// 8j + h): the LDCs of a candidate are all read the same way, so the AND of its rows and its weight
-// are unchanged.
+// 32 AT counters as one word of bits in a permuted order, counter 4 h + j at bit 8 j + h: a shift and a
+// merge for every four counters.  The order is the same for all words, so it serves wherever bits are
+// only compared with bits of the same place and counted: the AND of a candidate's LDCs, and the AND of
+// its SEs.  (In their own order, and with an at_flags4 of 14 operations, decoding was two thirds of the
+// arithmetic of the end of a sliding window, which kept the SIMDs busy for 37 of its 68 us.)
+__device__ __forceinline__ uint32_t at_word_permuted(const u32x4 &x, const u32x4 &y, const AtView &v) {
+    constexpr uint32_t H = 0x80808080u;
+    uint32_t p = at_flags4(x.x, v);
+    auto put = [&](uint32_t w) { p = ((p >> 1) & ~H) | (at_flags4(w, v) & H); };
+    put(x.y); put(x.z); put(x.w); put(y.x); put(y.y); put(y.z); put(y.w);
+    return p;
+}
+// The bits of an LDC word, or of four SEs: decoded as in decode_raw, but AT counters permuted.
 template <int MODE>
-__device__ __forceinline__ uint32_t decode_ldc(const CloseArgs &a, const RawWord<MODE> &r) {
+__device__ __forceinline__ uint32_t decode_any_order(const CloseArgs &a, const RawWord<MODE> &r) {
+    if constexpr (MODE == kCloseAt) return at_word_permuted(r.v[0], r.v[1], a.at);
+    else return decode_raw<MODE>(a, r);
+}
+// Of such a word of four SEs: without its first d SEs (0 to 3); the weights of the SEs, one per byte; the bits of
+// SE j (in any fixed order).  Permuted, SE q has bits 8 j + 2 q and 8 j + 2 q + 1 of the four bytes j.
+template <int MODE>
+__device__ __forceinline__ uint32_t skip_ses(uint32_t v, uint32_t d) {
+    if constexpr (MODE == kCloseAt) return (v >> (2 * d)) & ((0xFFu >> (2 * d)) * 0x01010101u);
+    else return v >> (8 * d);
+}
+template <int MODE>
+__device__ __forceinline__ uint32_t se_weights(uint32_t v) {
+    uint32_t t = v - ((v >> 1) & 0x55555555u);
     if constexpr (MODE == kCloseAt) {
-        const u32x4 x = r.v[0], y = r.v[1];
-        return (at_active4(x.x, a.at) >> 7) | (at_active4(x.y, a.at) >> 6) | (at_active4(x.z, a.at) >> 5) |
-               (at_active4(x.w, a.at) >> 4) | (at_active4(y.x, a.at) >> 3) | (at_active4(y.y, a.at) >> 2) |
-               (at_active4(y.z, a.at) >> 1) | at_active4(y.w, a.at);
+        const uint32_t even = ((t & 0x33333333u) * 0x01010101u) >> 24;          // SE 0, and 2 in the upper half
+        const uint32_t odd = (((t >> 2) & 0x33333333u) * 0x01010101u) >> 24;    // SE 1 and 3
+        t = even | odd << 8;
+        return (t & 0x0F0Fu) | (t & 0xF0F0u) << 12;
     } else {
-        return decode_raw<MODE>(a, r);
+        t = (t & 0x33333333u) + ((t >> 2) & 0x33333333u);
+        return (t + (t >> 4)) & 0x0F0F0F0Fu;
     }
+}
+template <int MODE>
+__device__ __forceinline__ uint32_t se_bits(uint32_t v, uint32_t j) {
+    if constexpr (MODE == kCloseAt) return (((v >> (2 * j)) & 0x03030303u) * 0x01041040u) >> 24;   // byte i to bit 2 i
+    else return (v >> (8 * j)) & 0xFFu;
 }
 // 32 bits of the SEAV from byte `byte` on; one byte of it; word `word` of the LDCA (below 2^27: a
 // sketch has fewer than 2^32 bits).
@@ -2020,34 +2049,69 @@ __device__ __forceinline__ void filter_candidates(const CloseArgs &a, const Cons
             if (live && sub == 0 && z0 <= c.z_theta) report(a, h, z0);
         }
     } else {
-        for (uint32_t e = share; e < n; e += NS) {
-            const uint32_t h = cand(e);
-            uint32_t ones = 0;
+        // Counters are 8 or 16 times the bits' bytes, and the AND of the rows has no more ones than its
+        // first row: a candidate whose first row alone is too empty is done (most of the false ones).
+        // Two candidates' first rows of AT counters are loaded together: 55 us of the sliding window
+        // below, one at a time 64, four (94 registers) 65; all rows of one at once 68.
+        constexpr uint32_t C = MODE == kCloseAt ? 2 : 1, RB = MODE == kCloseAt ? 2 : 1;
+        const uint32_t row_words = c.log2k - 5;
+        auto row_base = [&](uint32_t h, uint32_t r) { return ((r << c.log2lc) | ldc_col(h, r, c)) << row_words; };
+        for (uint32_t e = share; e < n; e += C * NS) {
+            uint32_t h[C], ones[C], ua[C], ub[C];
+#pragma unroll
+            for (uint32_t k = 0; k < C; ++k) {
+                h[k] = __builtin_amdgcn_readfirstlane(cand(e + k * NS < n ? e + k * NS : e));
+                ones[k] = 0;
+            }
             for (uint32_t w0 = 0; w0 < words; w0 += 128) {
                 const uint32_t wa = w0 + lane < words ? w0 + lane : words - 1;
                 const uint32_t wb = w0 + 64 + lane < words ? w0 + 64 + lane : words - 1;
-                uint32_t ua = 0xFFFFFFFFu, ub = 0xFFFFFFFFu;
-                constexpr uint32_t RB = MODE == kCloseAt ? 2 : 1;
-                for (uint32_t r0 = 0; r0 < c.lr; r0 += RB) {
-                    RawWord<MODE> x[RB], y[RB];
+                RawWord<MODE> x[C], y[C];
 #pragma unroll
-                    for (uint32_t rr = 0; rr < RB; ++rr) {
-                        const uint32_t r = r0 + rr < c.lr ? r0 + rr : c.lr - 1;
-                        const uint32_t base = ((r << c.log2lc) | ldc_col(h, r, c)) << (c.log2k - 5);
-                        x[rr] = load_ldc<MODE>(a, base + wa);
-                        y[rr] = load_ldc<MODE>(a, base + wb);
-                    }
-#pragma unroll
-                    for (uint32_t rr = 0; rr < RB; ++rr) {
-                        ua &= decode_ldc<MODE>(a, x[rr]);
-                        ub &= decode_ldc<MODE>(a, y[rr]);
-                    }
+                for (uint32_t k = 0; k < C; ++k) {
+                    const uint32_t base = row_base(h[k], 0);
+                    x[k] = load_ldc<MODE>(a, base + wa);
+                    y[k] = load_ldc<MODE>(a, base + wb);
                 }
-                ones += (w0 + lane < words ? __popc(ua) : 0u) + (w0 + 64 + lane < words ? __popc(ub) : 0u);
+#pragma unroll
+                for (uint32_t k = 0; k < C; ++k) {
+                    ua[k] = w0 + lane < words ? decode_any_order<MODE>(a, x[k]) : 0u;
+                    ub[k] = w0 + 64 + lane < words ? decode_any_order<MODE>(a, y[k]) : 0u;
+                    ones[k] += __popc(ua[k]) + __popc(ub[k]);
+                }
             }
-            ones = wave_sum(ones);
-            const uint32_t z0 = (1u << c.log2k) - ones;
-            if (lane == 0 && z0 <= c.z_theta) report(a, h, z0);
+#pragma unroll
+            for (uint32_t k = 0; k < C; ++k) {
+                uint32_t z0 = (1u << c.log2k) - __builtin_amdgcn_readfirstlane(wave_sum(ones[k]));
+                if (z0 > c.z_theta || e + k * NS >= n) continue;
+                if (c.lr > 1) {
+                    // the other rows (all of them again where a row takes several rounds)
+                    const bool once = words <= 128;
+                    uint32_t sum = 0;
+                    for (uint32_t w0 = 0; w0 < words; w0 += 128) {
+                        const uint32_t wa = w0 + lane < words ? w0 + lane : words - 1;
+                        const uint32_t wb = w0 + 64 + lane < words ? w0 + 64 + lane : words - 1;
+                        uint32_t va = once ? ua[k] : 0xFFFFFFFFu, vb = once ? ub[k] : 0xFFFFFFFFu;
+                        for (uint32_t r0 = once ? 1u : 0u; r0 < c.lr; r0 += RB) {
+                            RawWord<MODE> x[RB], y[RB];
+#pragma unroll
+                            for (uint32_t rr = 0; rr < RB; ++rr) {
+                                const uint32_t base = row_base(h[k], r0 + rr < c.lr ? r0 + rr : c.lr - 1);
+                                x[rr] = load_ldc<MODE>(a, base + wa);
+                                y[rr] = load_ldc<MODE>(a, base + wb);
+                            }
+#pragma unroll
+                            for (uint32_t rr = 0; rr < RB; ++rr) {
+                                va &= decode_any_order<MODE>(a, x[rr]);
+                                vb &= decode_any_order<MODE>(a, y[rr]);
+                            }
+                        }
+                        sum += (w0 + lane < words ? __popc(va) : 0u) + (w0 + 64 + lane < words ? __popc(vb) : 0u);
+                    }
+                    z0 = (1u << c.log2k) - wave_sum(sum);
+                }
+                if (lane == 0 && z0 <= c.z_theta) report(a, h[k], z0);
+            }
         }
     }
 }
@@ -2063,7 +2127,7 @@ __device__ __forceinline__ void filter_queue(const CloseArgs &a, const Consts &c
         for (uint32_t w = lane; w < words; w += 64) {
             uint32_t u = 0xFFFFFFFFu;
             for (uint32_t r = 0; r < c.lr; ++r)
-                u &= decode_ldc<MODE>(a, load_ldc<MODE>(a, (((r << c.log2lc) | ldc_col(h, r, c)) << (c.log2k - 5)) + w));
+                u &= decode_any_order<MODE>(a, load_ldc<MODE>(a, (((r << c.log2lc) | ldc_col(h, r, c)) << (c.log2k - 5)) + w));
             ones += __popc(u);
         }
         const uint32_t z0 = (1u << c.log2k) - wave_sum(ones);
@@ -2079,9 +2143,9 @@ __device__ __forceinline__ void filter_queue(const CloseArgs &a, const Consts &c
 // the filtering of all of them, so that an SEA with many candidates does not hold up one wavefront.
 // Bound by latency: a round trip for the SEAs, one or two per candidate filtered.
 // (64 Mi pairs, 16384 SEAs, 16 700 candidates: 39.6 us and a separate kernel of 4 us that copied the
-// counts and records out, now 25 us with both; 8 routers, 36 000 candidates 87 + 4 -> 44; a sliding
-// window of AT counters 89 + 4 and 17 for a bit view of the SEAV -> 64; of stamps, 1024 SEAs, 67 + 4
-// and 5 -> 28.)
+// counts and records out, now 29 us with both; 8 routers, 36 000 candidates 87 + 4 -> 51; a sliding
+// window of AT counters, 20 900 candidates, 89 + 4 and 17 for a bit view of the SEAV -> 55; of stamps,
+// 1024 SEAs, 67 + 4 and 5 -> 25.)
 // RMAX: SR itself when it is 4, else 8 (the rows' registers).
 template <int MODE, int BLOCK, int RMAX>
 __device__ __forceinline__ void close_window(const Consts &c, const CloseArgs &a) {
@@ -2133,8 +2197,8 @@ __device__ __forceinline__ void close_window(const Consts &c, const CloseArgs &a
                 const uint32_t w = w0 + k * 64 + lane;
                 v[k] = 0;
                 if (w0 + k * 64 < sea_words) {
-                    v[k] = decode_raw<MODE>(a, raw[k]);
-                    v[k] = w < sea_words ? v[k] >> (8 * (4 * w - word_byte(w))) : 0u;
+                    v[k] = decode_any_order<MODE>(a, raw[k]);
+                    v[k] = w < sea_words ? skip_ses<MODE>(v[k], 4 * w - word_byte(w)) : 0u;
                 }
             }
             if (w0 + 64 * U < sea_words) fetch(wi, w0 + 64 * U);
@@ -2143,10 +2207,7 @@ __device__ __forceinline__ void close_window(const Consts &c, const CloseArgs &a
             for (uint32_t k = 0; k < U; ++k) {
                 if (w0 + k * 64 >= sea_words) continue;
                 // bytes of weight >= kSeHot
-                uint32_t t = v[k] - ((v[k] >> 1) & 0x55555555u);
-                t = (t & 0x33333333u) + ((t >> 2) & 0x33333333u);
-                t = (t + (t >> 4)) & 0x0F0F0F0Fu;
-                uint32_t hot = (t + (0x80u - kSeHot) * 0x01010101u) & 0x80808080u;
+                uint32_t hot = (se_weights<MODE>(v[k]) + (0x80u - kSeHot) * 0x01010101u) & 0x80808080u;
                 if (!__ballot(hot != 0)) continue;
                 // places by lane: a prefix sum of the lanes' counts (0 to 4), one bit at a time
                 const uint32_t n = __popc(hot);
@@ -2157,7 +2218,7 @@ __device__ __forceinline__ void close_window(const Consts &c, const CloseArgs &a
                 while (hot) {
                     const uint32_t j = (uint32_t)__builtin_ctz(hot) >> 3;
                     hot &= hot - 1;
-                    list[pos++] = (byte0 + j) << 8 | ((v[k] >> (8 * j)) & 0xFFu);
+                    list[pos++] = (byte0 + j) << 8 | se_bits<MODE>(v[k], j);
                 }
             }
         }

@@ -1246,12 +1246,10 @@ spd_status close_args(spd_ctx *ctx, const Slot &sl, const CloseBuf &cb, CloseArg
     const uint64_t resident = (uint64_t)ctx->n_cu * ctx->close_per_cu[b / 128];
     // With few SEAs, each SEA's candidate search is split into parts (a power of two, at most 64) as
     // long as there are at most two wavefronts per SIMD: every part reads its whole SEA again (64 SEAs
-    // of 2 KiB, 1,000,000 pairs: 11.6 us with 32 parts, 15.5 with 64).  In
-    // sliding mode every SEA is split at least in two: its candidates' filters read 8 or 16 times the
-    // bytes, and the split halves the longest run of one wavefront (65.8 -> 63.7 us, 16384 SEAs).
+    // of 2 KiB, 1,000,000 pairs: 11.6 us with 32 parts, 15.5 with 64; 16384 SEAs of AT counters: 55 us
+    // whole, 63 in two parts, 86 in four).
     a->parts_log2 = 0;
     while (a->parts_log2 < 6 && ((uint64_t)a->n_rp << (a->parts_log2 + 1)) <= 8ull * ctx->n_cu) a->parts_log2++;
-    if (ctx->sliding && a->parts_log2 < 1) a->parts_log2 = 1;
     const uint64_t want = (((uint64_t)a->n_rp << a->parts_log2) + waves - 1) / waves;
     *grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(want, resident));
     return SPD_OK;
