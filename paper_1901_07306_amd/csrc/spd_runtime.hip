@@ -724,10 +724,18 @@ struct RegionScratch {
     uint32_t *parity;
 };
 
+// Whether work enqueued on s is being recorded into a graph.
+bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return s && hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+}
+
 // One group of the region layout in the given scratch: clear the counters (unless known zero), bin
 // into the regions, apply every (slot, bucket).  A fresh slot needs no clear: the apply phase writes
-// all of its buckets from zero, and nothing else writes the slot.  SPD_E_INVALID (nothing enqueued) if the group's layout does not fit the
-// scratch.
+// all of its buckets from zero, and nothing else writes the slot.  SPD_E_INVALID (nothing enqueued) if
+// the group's layout does not fit the scratch.
+// Recorded into a graph, the group runs when and as often as the graph is replayed: it then clears the
+// counters before and after itself, and what is known of them here stays as it was.
 spd_status region_launch_at(spd_ctx *ctx, const BinGeometry &g, const BatchDesc *bd, uint32_t nbd, uint32_t tiles,
                             const ChunkTable &ct, const ApplySlot *as, uint32_t nsl,
                             const RegionScratch &rs, hipStream_t s) {
@@ -759,14 +767,15 @@ spd_status region_launch_at(spd_ctx *ctx, const BinGeometry &g, const BatchDesc 
         if (st) return st;
         bl.b = bdev;
     }
-    if (!*rs.aux_zero) {   // after (re)allocation, another layout's use, or a failed launch
+    const bool recorded = capturing(s);
+    if (!*rs.aux_zero || recorded) {   // after (re)allocation, another layout's use, or a failed launch
         ProfScope ps(ctx, SPD_K_FILL, s);
         ClearList cl{};
         cl.p[cl.n] = rs.aux;
         cl.words[cl.n++] = rs.aux_words;
         SPD_HIP(ctx, launch_clear(cl, s));
     }
-    *rs.aux_zero = false;   // until the launch's apply phase is enqueued
+    if (!recorded) *rs.aux_zero = false;   // until the launch's apply phase is enqueued
     {
         ProfKernel pk(ctx, SPD_K_BIN);
         SPD_HIP(ctx, launch_region(ctx->c, g, bl, tiles, ct, ra, s, pk.kt));
@@ -793,6 +802,10 @@ spd_status region_launch_at(spd_ctx *ctx, const BinGeometry &g, const BatchDesc 
                                          pk.kt));
     }
     if (fuse) ctx->merged = true;
+    if (recorded) {
+        SPD_HIP(ctx, launch_fill_u32(rs.aux, 4, 0u, s));   // this launch's tile-list count
+        return SPD_OK;
+    }
     *rs.parity = par ^ 1u;
     *rs.aux_zero = true;
     return SPD_OK;
@@ -893,7 +906,8 @@ spd_status scan_work(spd_ctx *ctx, std::vector<WorkItem> &ws, hipStream_t s) {
     BinGeometry g{};
     const bool small = total <= ctx->tune.direct_max_pairs;
     const double gain = small ? binned_gain_us(ctx, total, slots) : 0.0;
-    const bool binned = gain >= 0.0 && ctx->p.lr <= 4 && bin_geometry(ctx, &g);
+    // (a small scan that is being recorded into a graph keeps to the kernel that needs no scratch)
+    const bool binned = gain >= 0.0 && ctx->p.lr <= 4 && !(small && capturing(s)) && bin_geometry(ctx, &g);
     const bool bm = ctx->tune.bin_mode != 0;
     auto direct_scan = [&]() -> spd_status {
         for (Slot *sl : slots)
