@@ -104,9 +104,10 @@ typedef struct spd_batch {
 
 /* Launch tuning.  Every setting gives the same sketch bits; only speed changes. */
 typedef struct spd_tuning {
-    uint64_t direct_max_pairs; /* batches up to this size use the direct-atomic scan kernel; at the default
-                                  (2^18) spd_scan, spd_scan_host and the batch scans take the binned
-                                  kernels below it too where those are faster */
+    uint64_t direct_max_pairs; /* batches up to this size use the direct-atomic scan kernel (default 2^18).
+                                  Until spd_set_tuning is called, spd_scan, spd_scan_host and the batch
+                                  scans take the binned kernels below it too where those are faster; a
+                                  limit that was set, whatever its value, is kept to exactly */
     uint32_t bucket_bits;      /* binned scan: log2 of sketch bits per LDS bucket (12..20), at most */
     uint32_t tile_pairs;       /* binned scan: pairs per tile (power of two, 2048..16384), at most: bin_mode 2
                                   with workgroups of 1024 and tiles of 8192 or less chooses both for the

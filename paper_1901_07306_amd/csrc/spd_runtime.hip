@@ -112,6 +112,7 @@ struct spd_ctx {
     bool aux_zero = false;           // region layout: every aux word is zero between launches
     uint32_t close_per_cu[3] = {0, 0, 0};   // resident end-of-window workgroups per CU (64, 128, 256 lanes)
     double small_gain = 0.0;         // what small scans without scratch would have saved with it (us)
+    bool limit_set = false;          // spd_set_tuning was called: direct_max_pairs is the caller's
     uint32_t list_parity = 0;        // region layout: which of two tile-list counts the next launch uses
     CloseBuf cbuf;                  // end-of-window buffers of spd_close_window
     uint64_t *close_counts = nullptr;   // finished workgroups of the running close (a context's launches
@@ -839,14 +840,14 @@ spd_status region_launch(spd_ctx *ctx, const BinGeometry &g, const std::vector<B
 }
 
 // Microseconds that the binned kernels save over the direct one for `total` pairs into `slots` (below
-// zero: the direct kernel is faster), for batches up to direct_max_pairs.  Only at that limit's default
-// are the two compared; at any other value the limit alone decides.  Fitted to scans and closes of 4096
+// zero: the direct kernel is faster), for batches up to direct_max_pairs.  The two are compared only
+// until the caller sets the limit; from then on it alone decides.  Fitted to scans and closes of 4096
 // to 2^18 pairs with sketches of 4 to 144 MiB: the direct kernel takes 0.043 ns per LDCA bit; the binned
 // ones have 5.5 us more to launch and write each empty sketch up to 8 us slower than the direct kernel's
 // clear does, and read and write one that is not empty (0.48 us per MiB).  200,003 pairs into 4 MiB: 52 us
 // direct, 36 binned; 32,768 pairs: 32.6 and 36.0; into 72 MiB 42.4 and 52.1.
 double binned_gain_us(const spd_ctx *ctx, uint64_t total, const std::vector<Slot *> &slots) {
-    if (ctx->tune.direct_max_pairs != kDirectMaxPairs || ctx->tune.bin_mode != 2) return -1.0;
+    if (ctx->limit_set || ctx->tune.bin_mode != 2) return -1.0;
     const double mib = (double)ctx->slot_bytes / 1048576.0;
     double gain = (double)total * ctx->p.lr * 0.043e-3 - 5.5;
     for (const Slot *sl : slots) gain -= sl->fresh ? std::min(8.0, 0.15 * mib) : 0.48 * mib;
@@ -2056,6 +2057,7 @@ spd_status spd_set_tuning(spd_ctx *ctx, const spd_tuning *t) {
     if (t->bin_mode > 2) return fail(ctx, SPD_E_INVALID, "bin_mode");
     if (t->region_words > (1u << 24)) return fail(ctx, SPD_E_INVALID, "region_words");
     ctx->tune = *t;
+    ctx->limit_set = true;
     BinGeometry g{};
     if (t->direct_max_pairs < UINT64_MAX && !bin_geometry(ctx, &g)) {
         // the binned path cannot run with this geometry: keep every batch on the direct path
