@@ -112,6 +112,7 @@ struct spd_ctx {
     bool aux_zero = false;           // region layout: every aux word is zero between launches
     uint32_t close_per_cu[3] = {0, 0, 0};   // resident end-of-window workgroups per CU (64, 128, 256 lanes)
     double small_gain = 0.0;         // what small scans without scratch would have saved with it (us)
+    bool small_scratch = false;      // the scratch was grown for a small scan, which can do without
     bool limit_set = false;          // spd_set_tuning was called: direct_max_pairs is the caller's
     uint32_t list_parity = 0;        // region layout: which of two tile-list counts the next launch uses
     CloseBuf cbuf;                  // end-of-window buffers of spd_close_window
@@ -372,8 +373,18 @@ void prof_harvest(spd_ctx *ctx) {
     ctx->prof_pending.clear();
 }
 
+void free_scratch(spd_ctx *ctx);
+
+// Small scans can do without their scratch: it makes room for what is needed.
+bool give_back_small_scratch(spd_ctx *ctx) {
+    if (!ctx->small_scratch) return false;
+    (void)hipDeviceSynchronize();
+    free_scratch(ctx);
+    return true;
+}
+
 spd_status reserve(spd_ctx *ctx, uint64_t bytes) {
-    if (ctx->budget && ctx->held + bytes > ctx->budget)
+    if (ctx->budget && ctx->held + bytes > ctx->budget && !(give_back_small_scratch(ctx) && ctx->held + bytes <= ctx->budget))
         return fail(ctx, SPD_E_NOMEM, "HBM budget exceeded: need " + std::to_string(ctx->held + bytes) +
                                           " bytes, budget " + std::to_string(ctx->budget));
     return SPD_OK;
@@ -385,7 +396,11 @@ spd_status dev_alloc(spd_ctx *ctx, T **p, uint64_t bytes) {
     if (st) return st;
     void *m = nullptr;
     hipError_t e = hipMalloc(&m, bytes ? bytes : 16);
-    if (e != hipSuccess) return hip_fail(ctx, e, "hipMalloc");
+    if (e != hipSuccess && give_back_small_scratch(ctx)) e = hipMalloc(&m, bytes ? bytes : 16);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();   // (reported here, not by the next launch)
+        return hip_fail(ctx, e, "hipMalloc");
+    }
     ctx->held += bytes;
     *p = static_cast<T *>(m);
     return SPD_OK;
@@ -688,6 +703,7 @@ void free_scratch(spd_ctx *ctx) {
     dev_free(ctx, &ctx->aux, ctx->aux_words * 4);
     ctx->items_words = ctx->meta_words = ctx->aux_words = 0;
     ctx->aux_zero = false;
+    ctx->small_scratch = false;
 }
 
 spd_status ensure_scratch(spd_ctx *ctx, uint64_t items_words, uint64_t meta_words, hipStream_t s) {
@@ -820,10 +836,8 @@ bool region_ready(const spd_ctx *ctx, const BinGeometry &g, const ChunkTable &ct
     return items_words <= ctx->items_words && cur_words <= ctx->aux_words;
 }
 
-// The same in the context's scratch, grown on demand within the HBM budget: SPD_E_NOMEM (nothing
-// enqueued) if it does not fit.
-spd_status region_launch(spd_ctx *ctx, const BinGeometry &g, const std::vector<BatchDesc> &bd, uint32_t tiles,
-                         const ChunkTable &ct, const ApplySlot *as, uint32_t nsl, hipStream_t s) {
+// The context's scratch grown for a group, within the HBM budget: SPD_E_NOMEM if it does not fit.
+spd_status region_room(spd_ctx *ctx, const BinGeometry &g, const ChunkTable &ct, uint32_t tiles, hipStream_t s) {
     RegionArgs ra{};
     uint64_t items_words = 0, cur_words = 0;
     region_layout(ctx, g, ct, tiles, &ra, &items_words, &cur_words);
@@ -834,6 +848,14 @@ spd_status region_launch(spd_ctx *ctx, const BinGeometry &g, const std::vector<B
     spd_status st = more ? reserve(ctx, more) : SPD_OK;
     if (!st) st = ensure_scratch(ctx, items_words, 0, s);
     if (!st) st = ensure_aux(ctx, cur_words, s);
+    return st;
+}
+
+// A group in the context's scratch, grown on demand: SPD_E_NOMEM (nothing enqueued) if it does not fit
+// the budget.
+spd_status region_launch(spd_ctx *ctx, const BinGeometry &g, const std::vector<BatchDesc> &bd, uint32_t tiles,
+                         const ChunkTable &ct, const ApplySlot *as, uint32_t nsl, hipStream_t s) {
+    spd_status st = region_room(ctx, g, ct, tiles, s);
     if (st) return st;
     const RegionScratch rs{ctx->items, ctx->items_words, ctx->aux, ctx->aux_words, &ctx->aux_zero, &ctx->list_parity};
     return region_launch_at(ctx, g, bd.data(), (uint32_t)bd.size(), tiles, ct, as, nsl, rs, s);
@@ -1026,16 +1048,21 @@ spd_status scan_work(spd_ctx *ctx, std::vector<WorkItem> &ws, hipStream_t s) {
                 // the exact-count layout (less scratch) if the region layout does not fit the budget
                 chunk_table(&ct, as, nsl, region_chunk(tiles));
                 if (small && !region_ready(ctx, g, ct, tiles)) {
-                    // the direct kernel needs no scratch: a small scan has some allocated (about 50 us)
-                    // once scans like it would have saved that much
+                    // the direct kernel needs no scratch: a small scan has it grown (about 50 us) once
+                    // scans like it would have saved that much, and stays direct if that is refused
                     ctx->small_gain += gain;
                     if (ctx->small_gain < kScratchUs) return direct_scan();
+                    ctx->small_gain = 0.0;
+                    const bool was = ctx->small_scratch;
+                    ctx->small_scratch = false;   // (not to be given back for its own growth)
+                    const spd_status grown = region_room(ctx, g, ct, tiles, s);
+                    ctx->small_scratch = was || !grown;
+                    if (grown) return direct_scan();
                 }
                 ctx->merge_group = ctx->merge_into && group_start == 0 && i0 == ws.size();
                 spd_status st = region_launch(ctx, g, bd, tiles, ct, as, nsl, s);
                 ctx->merge_group = false;
                 if (st && st != SPD_E_NOMEM) return st;
-                if (st && small) return direct_scan();   // (recording a pair twice changes nothing)
                 if (st && own) {   // (nothing was enqueued) the tuning's geometry may need less
                     own = false;
                     g = g0;

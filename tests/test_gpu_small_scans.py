@@ -51,3 +51,99 @@ def test_a_set_limit_is_kept():
         assert windows(det, 72, count=2) == [1, 1]
     finally:
         det.close()
+
+
+def detector(budget=0, n_routers=1):
+    return spd.Detector(spd.params_from(MP), n_routers=n_routers, hbm_budget_bytes=budget)
+
+
+def held_after(fn):
+    """(device bytes of a new context, and after fn(det))."""
+    det = detector()
+    try:
+        a = det.stats.device_bytes
+        fn(det)
+        return a, det.stats.device_bytes
+    finally:
+        det.close()
+
+
+def test_scratch_is_grown_when_it_has_paid():
+    """The first windows are direct, the later ones binned; a limit that is then set ends it."""
+    det = detector()
+    try:
+        log("case small scans: direct, then binned")
+        binned = windows(det, 81, count=12)
+        assert binned[0] == 0 and binned[-1] == 1 and binned == sorted(binned)
+        held = det.stats.device_bytes
+        windows(det, 82, count=2, n=150_001)
+        assert det.stats.device_bytes == held
+    finally:
+        det.close()
+
+
+def test_a_budget_without_room_for_scratch():
+    """Every window is scanned directly, within the budget and with the same result."""
+    base, _ = held_after(lambda det: None)
+    det = detector(budget=base + 4096)
+    try:
+        log("case small scans: no room for scratch")
+        assert windows(det, 83, count=14) == [0] * 14
+        assert det.stats.device_bytes == base
+    finally:
+        det.close()
+
+
+def test_scratch_of_small_scans_makes_room():
+    """A budget that holds the staging buffers of a host scan or the scratch of small scans, but not
+    both: the host scan is accepted as if the small scans had stayed direct."""
+    chunk = 500_000
+    rng = np.random.default_rng(84)
+    pairs = random_pairs(rng, chunk, n_hosts=9_000)
+    base, after = held_after(lambda det: windows(det, 85, count=12))
+    assert after > base
+    tune = dict(direct_max_pairs=1 << 30)   # (the host scan's chunk direct too: only its staging is allocated)
+    det = detector(budget=base + max(2 * 8 * chunk, after - base) + 4096)
+    try:
+        log("case small scans: their scratch makes room")
+        assert windows(det, 86, count=12)[-1] == 1
+        set_tuning(det, **tune)
+        det.scan_host(0, pairs, chunk_pairs=chunk)
+        assert_same_sketch(det, 0, oracle_sketch(MP, pairs), "host scan")
+    finally:
+        det.close()
+
+
+def test_budgets_of_a_large_scan():
+    """A scan that wants a geometry of its own under budgets from the least scratch a layout can do with
+    up to what it would like: never refused, always the same sketch."""
+    rng = np.random.default_rng(87)
+    parts = [random_pairs(rng, 300_001 + 70_000 * r, n_hosts=9_000) for r in range(3)]
+    dev = [to_dev(p) for p in parts]
+
+    def scan(det, mode=2):
+        if mode != 2:
+            set_tuning(det, bin_mode=mode, direct_max_pairs=0)
+        det.scan_batches([(r, x) for r, x in enumerate(dev)])
+
+    def held(mode):
+        det = detector(n_routers=3)
+        try:
+            scan(det, mode)
+            return det.stats.device_bytes
+        finally:
+            det.close()
+
+    low, high = held(1), held(2)
+    for budget in sorted({low + 65_536, *(int(low + (high - low) * k / 6) for k in range(1, 7))}):
+        det = detector(budget=budget, n_routers=3)
+        try:
+            log(f"case large scan under {budget} bytes")
+            for k in range(2):
+                scan(det)
+                for r in range(3):
+                    assert_same_sketch(det, r, oracle_sketch(MP, parts[r]), f"router {r}")
+                    det.reset(r)
+            assert det.stats.device_bytes <= budget
+        finally:
+            det.close()
