@@ -219,15 +219,18 @@ struct SpillSeg {
     uint32_t start;        // first word in the spill array
     uint32_t words;
 };
-// A tile with more sampled pairs than it could stage: its sampled pairs are read again by the apply
-// phase of the slot's SEAV buckets.
+// A tile with more sampled pairs than it could stage: its sampled pairs are read again, once, when the
+// apply phase has written the slot's SEAV buckets.
 struct ListedTile {
     const uint32_t *pairs; // the tile's first pair
     uint32_t n;            // pairs of the tile
-    uint32_t slot;
     uint32_t swap;
-    uint32_t pad[3];
 };
+// Counts of a launch's listed tiles, per slot: tiles listed, SEAV buckets written, tiles taken.
+struct ListCounts {
+    uint32_t listed[kMaxGroup], written[kMaxGroup], taken[kMaxGroup];
+};
+constexpr uint32_t kListWords = sizeof(ListCounts) / 4;
 struct RegionArgs {
     uint64_t slot_base[kMaxGroup];
     uint32_t full[kMaxGroup];                      // full chunks of each slot
@@ -238,9 +241,9 @@ struct RegionArgs {
     uint32_t *seg_n;       // [slots][nb] listed segments: zero before the launch, zeroed like cur
     SpillSeg *seg;         // per slot [nb][tiles of the slot]: at most one segment per tile and bucket
     uint64_t *spill_w;     // [tiles][cap / 3]: word w of a tile's stage, when it is past its region
-    uint32_t *tile_n;      // tiles listed by this launch (zero before the launch)
-    uint32_t *tile_next;   // the next launch's count: zeroed by this launch's apply phase
-    ListedTile *tile;      // [tiles]
+    ListCounts *list;      // of this launch (zero before it)
+    ListCounts *list_next; // the next launch's: zeroed by this launch's apply phase
+    ListedTile *tile;      // per slot [tiles of the slot]
     uint64_t chunk_words;  // nb_ldca * capw_l + (nb - nb_ldca) * capw_s
     uint32_t capw_l, capw_s;
     uint32_t tile_words;   // cap / 3: words of one tile's stage

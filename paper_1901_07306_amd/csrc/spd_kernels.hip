@@ -1021,15 +1021,14 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_num_sgpr(80))) void k_
     else
         region_hash<LR, PPT, BLOCK, false>(c, g, pr, left, cl, samp, misc, bits, rk);
     __syncthreads();
-    // a tile with more sampled pairs than it can stage stages none: it is listed, and the apply
-    // phase of the SEAV buckets reads all of its sampled pairs again
+    // a tile with more sampled pairs than it can stage stages none: it is listed, and its pairs are
+    // read again once the apply phase has written the SEAV buckets
     uint32_t ns = misc[0];
     if (ns > g.scap) {
         if (tid == 0) {
-            ListedTile &t = ra.tile[atomicAdd(ra.tile_n, 1u)];   // (one entry per tile of the launch)
+            ListedTile &t = ra.tile[t_lo + atomicAdd(&ra.list->listed[slot], 1u)];   // (one entry per tile of the slot)
             t.pairs = B.pairs + 2 * p0;
             t.n = left;
-            t.slot = slot;
             t.swap = B.swap;
         }
         ns = 0;
@@ -1253,39 +1252,125 @@ __device__ __forceinline__ void apply_segments(const SpillSeg *__restrict__ seg,
     }
 }
 
-// The sampled pairs of the slot's listed tiles whose SEAV bits lie in this bucket (n_bits of the SEAV
-// from first_bit on).  Rare, and wide: the method constants are read from the kernel
-// arguments (they are the first one) behind an opaque pointer, so that nothing of this is loaded on
-// the path of a launch that lists no tile.
+// Listed tiles are read once, when the slot's SEAV buckets are in memory.  The workgroups of the SEAV's
+// buckets (which come last in the grid) count them written, and with those of the LDCA buckets before them,
+// where the SEAV has few, wait a little for the last; then they take tiles from a counter and record their
+// sampled pairs with global atomics.  The wait is bounded, and a workgroup that gives up leaves: the one that
+// counts the last bucket takes whatever tiles are left, so no workgroup depends on another that has not
+// started.
+// What lists a tile is one sampled peer with more than about 1.6 % of its pairs (8192 pairs, tau = 7),
+// and then nearly every tile of a window is listed.  (Read again by every SEAV bucket, for the items
+// of its own: 8 Mi pairs with a peer of 2 % into 72 MiB, 7.2 ms; by a launch of its own of 32
+// workgroups: 0.92; so 0.20, of which 0.10 without such a peer too.)
+constexpr uint32_t kListedGroups = 64;   // workgroups that share a slot's listed tiles, or its SEAV buckets if more
+constexpr uint32_t kListedPolls = 32;    // of about two microseconds
+constexpr uint32_t kListedWords = 128;   // LDS words that record_listed needs at least
+__host__ __device__ __forceinline__ uint32_t apply_lds_words(uint32_t S) {   // and the piece counter after them
+    return 1u << (S - 5) < kListedWords ? kListedWords : 1u << (S - 5);
+}
+// Whether this workgroup, which has stored bucket b, may take tiles.
+__device__ __forceinline__ bool seav_written(uint32_t *written, uint32_t b, const BinGeometry &g, uint32_t *lds) {
+    const uint32_t buckets = g.nb - g.nb_ldca;
+    const bool mine = b >= g.nb_ldca;
+    if (!mine && b + kListedGroups < g.nb) return false;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's stores are in the L2
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t n = 0;
+        if (mine) {
+            // one release for the workgroup: it writes the L2 back
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            n = __hip_atomic_fetch_add(written, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+        }
+        for (uint32_t k = 0; n < buckets && k < kListedPolls; ++k) {
+            __builtin_amdgcn_s_sleep(32);   // (2048 cycles; polls of one address follow each other)
+            n = __hip_atomic_load(written, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        lds[0] = n;
+    }
+    __syncthreads();
+    const bool all = lds[0] >= buckets;
+    __syncthreads();
+    return all;
+}
+
+// Takes listed tiles and records their sampled pairs in the SEAV, and in a second one if there is one: the
+// sampled pairs are gathered in LDS, so that the lanes share their bits evenly and nothing waits for
+// memory between them.  A heavy flow's pairs set the same bits over and over, and atomics on one address
+// follow each other device-wide: a bit that the table in LDS still holds is not set again (8 Mi pairs, 30 %
+// of them one flow: @B@).
+// The method constants are read from the kernel arguments (they are the first one) behind an opaque
+// pointer, so that nothing of this is loaded on the path of a launch that lists no tile.
 typedef __attribute__((address_space(4))) const Consts ArgConsts;
 template <int BLOCK>
-__device__ __forceinline__ void apply_listed(const RegionArgs &ra, uint32_t n, uint32_t si, uint64_t first_bit, uint32_t n_bits,
-                                             uint32_t *bm) {
+__device__ __forceinline__ void record_listed(const ListedTile *tiles, uint32_t n, uint32_t *taken, uint32_t *seav,
+                                              uint32_t *seav2, uint32_t *lds, uint32_t lds_words) {
+    constexpr uint32_t U = 8;   // pairs in flight per lane
     auto args = __builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(args));
     ArgConsts &c = *(ArgConsts *)args;
-    for (uint32_t t = 0; t < n; ++t) {
-        const ListedTile T = ra.tile[t];
-        if (T.slot != si) continue;
+    // [0] tile, [1] sampled pairs gathered, then the table of bits, then the pairs (hip, H2 bit)
+    const uint32_t tab_bits = 31u - __builtin_clz(lds_words) - 2u;   // a quarter of the words (at least 128)
+    uint32_t *tab = lds + 2, *list = tab + (1u << tab_bits);
+    const uint32_t cap = (lds_words - 2u - (1u << tab_bits)) / 2u;
+    for (uint32_t i = threadIdx.x; i < (1u << tab_bits); i += BLOCK) tab[i] = ~0u;   // (no bit's address)
+    auto record = [&](uint32_t hip, uint32_t b, uint32_t r) {
+        const uint32_t rp = hip & c.rmask, lp = (uint32_t)((uint64_t)hip >> c.r);
+        const uint32_t bit = (rp * c.sea_bytes + c.row_off[r] + row_index(lp, c.isb[r], c.ibn[r], c.L)) * 8u + b;
+        uint32_t *t = tab + (bit * 0x9E3779B1u >> (32u - tab_bits));
+        if (*t == bit) return;
+        *t = bit;
+        global_or(seav + (bit >> 5), 1u << (bit & 31u));
+        if (seav2) global_or(seav2 + (bit >> 5), 1u << (bit & 31u));
+    };
+    for (;;) {
+        if (threadIdx.x == 0) {
+            lds[0] = __hip_atomic_fetch_add(taken, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            lds[1] = 0;
+        }
+        __syncthreads();
+        const uint32_t t = __builtin_amdgcn_readfirstlane(lds[0]);
+        if (t >= n) break;
+        const ListedTile T = tiles[t];
         const u32x2 *pairs = reinterpret_cast<const u32x2 *>(T.pairs);
-        for (uint32_t i = threadIdx.x; i < T.n; i += BLOCK) {
-            const u32x2 pr = load_pair(pairs, i, T.swap);
-            if (mas_hi(pr.y, c.mul[0], c.add[0]) & c.tau_mask) continue;
-            const uint32_t b = mas_hi(pr.y, c.mul[1], c.add[1]) >> 29;
-            const uint32_t rp = pr.x & c.rmask, lp = (uint32_t)((uint64_t)pr.x >> c.r);
-            for (uint32_t r = 0; r < c.sr; ++r) {
-                const uint32_t byte = rp * c.sea_bytes + c.row_off[r] + row_index(lp, c.isb[r], c.ibn[r], c.L);
-                const uint64_t bit = (uint64_t)byte * 8u + b - first_bit;   // (wraps below the part)
-                if (bit >= n_bits) continue;
-                atomicOr(&bm[bit >> 5], 1u << (bit & 31u));
+        for (uint32_t i0 = 0; i0 < T.n; i0 += U * BLOCK) {
+            u32x2 pr[U];
+#pragma unroll
+            for (uint32_t k = 0; k < U; ++k) {
+                const uint32_t i = i0 + k * BLOCK + threadIdx.x;
+                pr[k] = load_pair(pairs, i < T.n ? i : T.n - 1, T.swap);
             }
+#pragma unroll
+            for (uint32_t k = 0; k < U; ++k) {
+                const bool valid = i0 + k * BLOCK + threadIdx.x < T.n;
+                if (!valid || (mas_hi(pr[k].y, c.mul[0], c.add[0]) & c.tau_mask)) continue;
+                const uint32_t b = mas_hi(pr[k].y, c.mul[1], c.add[1]) >> 29;
+                const uint32_t e = atomicAdd(&lds[1], 1u);
+                if (e < cap) {
+                    list[2 * e] = pr[k].x;
+                    list[2 * e + 1] = b;
+                } else {   // (buckets of fewer than 2^18 bits)
+                    for (uint32_t r = 0; r < c.sr; ++r) record(pr[k].x, b, r);
+                }
+            }
+            __syncthreads();
+            const uint32_t m = (lds[1] < cap ? lds[1] : cap) * c.sr;
+            for (uint32_t w = threadIdx.x; w < m; w += BLOCK) {
+                const uint32_t e = w / c.sr;
+                record(list[2 * e], list[2 * e + 1], w - e * c.sr);
+            }
+            __syncthreads();
+            if (threadIdx.x == 0) lds[1] = 0;
+            __syncthreads();
         }
     }
+    __syncthreads();
 }
 
 // Bucket b of slot si: loaded into the LDS bitmap bm (zero for a fresh slot:
-// nothing else writes a slot's memory during a launch), the filled part of the bucket's region in every
-// chunk of the slot, then its listed segments and tiles, applied with LDS atomicOr, the counters read
+// nothing else writes the bucket's memory before it is stored), the filled part of the bucket's region in
+// every chunk of the slot, then its listed segments, applied with LDS atomicOr, the counters read
 // zeroed for the next launch, the bitmap stored back.  Ends with bm complete and visible to the whole
 // workgroup.
 // Bound by the LDS atomics of random words (about 9 items per ns and compute unit) for crowded buckets.
@@ -1302,7 +1387,7 @@ __device__ __forceinline__ void apply_bucket(const BinGeometry &g, const ApplySl
     uint32_t *dst = b < g.nb_ldca ? A.ldca + (uint64_t)b * words : A.seav_w + (uint64_t)(b - g.nb_ldca) * words;
     const uint32_t words4 = words / 4;
     u32x4 *bm4 = reinterpret_cast<u32x4 *>(bm), *dst4 = reinterpret_cast<u32x4 *>(dst);
-    const uint32_t n_seg = ra.seg_n[si * g.nb + b], n_tile = b < g.nb_ldca ? 0u : *ra.tile_n;
+    const uint32_t n_seg = ra.seg_n[si * g.nb + b];
     // the slot's chunks (at most kXcds + 1), one per lane: words filled, pieces, and pieces up to here
     const uint32_t c0 = ct.cbase[si], nch = ct.cbase[si + 1] - c0;
     uint32_t cap_c = 0;
@@ -1367,24 +1452,25 @@ __device__ __forceinline__ void apply_bucket(const BinGeometry &g, const ApplySl
         const uint32_t lo = ct.lo[si], nt = ct.hi[si] - lo;
         apply_segments<BLOCK, 2 * U>(ra.seg + (uint64_t)lo * g.nb + (uint64_t)b * nt, n_seg, ra.spill_w, wid, lane, bm);
     }
-    if (n_tile) apply_listed<BLOCK>(ra, n_tile, si, (uint64_t)(b - g.nb_ldca) << g.S, words * 32u, bm);
     __syncthreads();
-    // the counters of this (slot, bucket) start the next launch at zero, and so does its tile count
+    // the counters of this (slot, bucket) start the next launch at zero, and so do its tile lists
     if (tid < nch) ra.cur[(uint64_t)(c0 + tid) * g.nb + b] = 0u;
-    if (tid == 0) {
-        ra.seg_n[si * g.nb + b] = 0u;
-        if (b == 0 && si == 0) *ra.tile_next = 0u;
-    }
+    if (tid == 0) ra.seg_n[si * g.nb + b] = 0u;
+    if (b == 0 && si == 0 && tid < kListWords) reinterpret_cast<uint32_t *>(ra.list_next)[tid] = 0u;
     for (uint32_t w = tid; w < words4; w += BLOCK) dst4[w] = bm4[w];
     for (uint32_t w = words4 * 4 + tid; w < words; w += BLOCK) dst[w] = bm[w];
 }
 
-// One workgroup per (slot, bucket).  (The first argument is read by apply_listed.)
+// One workgroup per (slot, bucket).  (The first argument is read by record_listed.)  At most 80 scalar
+// registers, as in k_region: small buckets leave room for two workgroups per compute unit.
 template <int BLOCK, int U>
-__global__ __launch_bounds__(BLOCK) void k_apply_rg(Consts, BinGeometry g, ApplyTable at, ChunkTable ct, RegionArgs ra) {
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_num_sgpr(80))) void k_apply_rg(Consts, BinGeometry g, ApplyTable at, ChunkTable ct, RegionArgs ra) {
     extern __shared__ __align__(16) uint32_t bm[];
     const uint32_t si = blockIdx.x / g.nb, b = blockIdx.x % g.nb;
     apply_bucket<BLOCK, U>(g, at.s[si], si, b, ct, ra, bm);
+    const uint32_t n = ra.list->listed[si];
+    if (n && seav_written(&ra.list->written[si], b, g, bm))
+        record_listed<BLOCK>(ra.tile + ct.lo[si], n, &ra.list->taken[si], at.s[si].seav_w, nullptr, bm, apply_lds_words(g.S));
 }
 
 // The same with the router OR merge fused in (Section 4.2): one workgroup per bucket applies the
@@ -1412,6 +1498,13 @@ __global__ __launch_bounds__(1024) void k_apply_rg_merge(Consts, BinGeometry g, 
 #pragma unroll
     for (uint32_t k = 0; k < PER; ++k)
         if (k * BLOCK + tid < words) dst[k * BLOCK + tid] = acc[k];
+    uint32_t listed = 0;
+    for (uint32_t si = 0; si < n_slots; ++si) listed |= ra.list->listed[si];
+    if (!listed || !seav_written(&ra.list->written[0], b, g, bm)) return;
+    for (uint32_t si = 0; si < n_slots; ++si) {
+        const uint32_t n = ra.list->listed[si];
+        if (n) record_listed<BLOCK>(ra.tile + ct.lo[si], n, &ra.list->taken[si], at.s[si].seav_w, gs.seav_w, bm, apply_lds_words(g.S));
+    }
 }
 
 template <int U>
@@ -1434,7 +1527,7 @@ hipError_t launch_apply_rg(const Consts &c, const BinGeometry &g, const ApplySlo
         at.s[i] = slots[i];
         if (ct.cbase[i + 1] - ct.cbase[i] > 64u) return hipErrorInvalidValue;   // a lane per chunk
     }
-    const uint32_t lds = (1u << (g.S - 5)) * 4u + 16u;
+    const uint32_t lds = apply_lds_words(g.S) * 4u + 16u;
     const dim3 grid(n_slots * g.nb);
     switch (unroll) {
     case 8: launch_apply_rg_u<2>(c, g, at, ct, ra, grid, lds, block, s, kt); break;
@@ -1454,7 +1547,7 @@ hipError_t launch_apply_rg_merge(const Consts &c, const BinGeometry &g, const Ap
         at.s[i] = slots[i];
         if (ct.cbase[i + 1] - ct.cbase[i] > 64u) return hipErrorInvalidValue;   // a lane per chunk
     }
-    const uint32_t lds = (1u << (g.S - 5)) * 4u + 16u;
+    const uint32_t lds = apply_lds_words(g.S) * 4u + 16u;
     const dim3 grid(g.nb), block(1024);
     switch (unroll) {
     case 8: hipExtLaunchKernelGGL((k_apply_rg_merge<2>), grid, block, lds, s, kt.start, kt.stop, 0, c, g, at, n_slots, ct, ra, global); break;

@@ -114,7 +114,7 @@ struct spd_ctx {
     double small_gain = 0.0;         // what small scans without scratch would have saved with it (us)
     bool small_scratch = false;      // the scratch was grown for a small scan, which can do without
     bool limit_set = false;          // spd_set_tuning was called: direct_max_pairs is the caller's
-    uint32_t list_parity = 0;        // region layout: which of two tile-list counts the next launch uses
+    uint32_t list_parity = 0;        // region layout: which of two sets of tile-list counts the next launch uses
     CloseBuf cbuf;                  // end-of-window buffers of spd_close_window
     uint64_t *close_counts = nullptr;   // finished workgroups of the running close (a context's launches
                                         // of closes run one after another), per window of a launch
@@ -628,7 +628,7 @@ static uint64_t region_tile_words(const BinGeometry &g) {
 }
 
 // The region layout of one launch over the slots of ct (pointers left null): items_words = 32-bit
-// words of the regions, the spill words, the segment lists and the tile list; cur_words = two
+// words of the regions, the spill words, the segment lists and the tile lists; cur_words = two sets of
 // tile-list counts, the segment counts and the region counters, a multiple of 4.
 void region_layout(const spd_ctx *ctx, const BinGeometry &g, const ChunkTable &ct, uint64_t tiles, RegionArgs *ra,
                    uint64_t *items_words, uint64_t *cur_words) {
@@ -650,7 +650,7 @@ void region_layout(const spd_ctx *ctx, const BinGeometry &g, const ChunkTable &c
     }
     ra->tile_words = g.cap / 3;
     *items_words = words * 2 + tiles * region_tile_words(g);
-    *cur_words = (4 + ((uint64_t)ct.cbase[ct.n] + ct.n) * g.nb + 3) / 4 * 4;
+    *cur_words = (2 * kListWords + ((uint64_t)ct.cbase[ct.n] + ct.n) * g.nb + 3) / 4 * 4;
 }
 
 // Tiles per chunk of a region launch over `tiles` tiles.  The binning kernel deals the tiles to the
@@ -692,7 +692,7 @@ void region_bound(const spd_ctx *ctx, const BinGeometry &g, uint64_t tiles, uint
         words = A * (double)tiles + B * std::sqrt(n * (double)tiles) + n * C;
     }
     *items_words = (uint64_t)std::ceil(words) * 2 + tiles * region_tile_words(g);
-    *cur_words = (4 + (uint64_t)(kXcds + 2 * kMaxGroup) * g.nb + 3) / 4 * 4;
+    *cur_words = (2 * kListWords + (uint64_t)(kXcds + 2 * kMaxGroup) * g.nb + 3) / 4 * 4;
 }
 
 void free_scratch(spd_ctx *ctx) {
@@ -730,8 +730,8 @@ spd_status ensure_scratch(spd_ctx *ctx, uint64_t items_words, uint64_t meta_word
 }
 
 // Scratch of one region-layout group: the item regions, spill words and lists (`items`), the counters
-// (`aux`), whether every aux word is known to be zero, and which of the two tile-list counts the
-// group uses.
+// (`aux`), whether every aux word is known to be zero, and which of the two sets of tile-list counts
+// the group uses.
 struct RegionScratch {
     uint32_t *items;
     uint64_t items_words;
@@ -768,9 +768,9 @@ spd_status region_launch_at(spd_ctx *ctx, const BinGeometry &g, const BatchDesc 
     ra.spill_w = ra.items + region_words / 2;
     ra.seg = reinterpret_cast<SpillSeg *>(ra.spill_w + (uint64_t)tiles * ra.tile_words);
     ra.tile = reinterpret_cast<ListedTile *>(ra.seg + (uint64_t)tiles * g.nb);
-    ra.tile_n = rs.aux + par;
-    ra.tile_next = rs.aux + (par ^ 1u);
-    ra.seg_n = rs.aux + 4;
+    ra.list = reinterpret_cast<ListCounts *>(rs.aux) + par;
+    ra.list_next = reinterpret_cast<ListCounts *>(rs.aux) + (par ^ 1u);
+    ra.seg_n = rs.aux + 2 * kListWords;
     ra.cur = ra.seg_n + (uint64_t)ct.n * g.nb;
     // a few batches travel in the kernel arguments; more go through the pinned staging ring
     BatchList bl{};
@@ -820,7 +820,7 @@ spd_status region_launch_at(spd_ctx *ctx, const BinGeometry &g, const BatchDesc 
     }
     if (fuse) ctx->merged = true;
     if (recorded) {
-        SPD_HIP(ctx, launch_fill_u32(rs.aux, 4, 0u, s));   // this launch's tile-list count
+        SPD_HIP(ctx, launch_fill_u32(rs.aux, 2 * kListWords, 0u, s));   // this launch's tile-list counts
         return SPD_OK;
     }
     *rs.parity = par ^ 1u;
