@@ -113,6 +113,8 @@ struct spd_ctx {
     uint32_t close_per_cu[3] = {0, 0, 0};   // resident end-of-window workgroups per CU (64, 128, 256 lanes)
     double small_gain = 0.0;         // what small scans without scratch would have saved with it (us)
     bool small_scratch = false;      // the scratch was grown for a small scan, which can do without
+    bool fixed_scratch = false;      // serving loop: the scratch is reserved at creation; a launch's own geometry
+                                     // and the binning of small scans have to do with it
     bool limit_set = false;          // spd_set_tuning was called: direct_max_pairs is the caller's
     uint32_t list_parity = 0;        // region layout: which of two sets of tile-list counts the next launch uses
     CloseBuf cbuf;                  // end-of-window buffers of spd_close_window
@@ -1047,7 +1049,15 @@ spd_status scan_work(spd_ctx *ctx, std::vector<WorkItem> &ws, hipStream_t s) {
             if (ctx->tune.bin_mode == 2) {
                 // the exact-count layout (less scratch) if the region layout does not fit the budget
                 chunk_table(&ct, as, nsl, region_chunk(tiles));
-                if (small && !region_ready(ctx, g, ct, tiles)) {
+                const bool ready = region_ready(ctx, g, ct, tiles);
+                if (ctx->fixed_scratch && !ready && own) {
+                    own = false;
+                    g = g0;
+                    i0 = group_start;
+                    continue;
+                }
+                if (ctx->fixed_scratch && !ready && small) return direct_scan();
+                if (small && !ready) {
                     // the direct kernel needs no scratch: a small scan has it grown (about 50 us) once
                     // scans like it would have saved that much, and stays direct if that is refused
                     ctx->small_gain += gain;
@@ -2434,7 +2444,26 @@ spd_status spd_server_create(const spd_params *p, const spd_server_config *cfg, 
             if (!r && mode) r = ensure_aux(ctx, aux_words, nullptr);
             return r;
         };
+        // Slots that the rest of the budget holds.
+        auto slots_left = [&](uint64_t more) {
+            const uint64_t used = ctx->held + more, one = ctx->slot_bytes + (uint64_t)kRecInit * 8 + 64;
+            const uint64_t n = ctx->budget > used ? (ctx->budget - used) / one : 0;
+            return S->cfg.max_slots ? std::min<uint64_t>(n, S->cfg.max_slots) : n;
+        };
         st = reserve(ctx->tune.bin_mode);
+        if (!st && ctx->tune.bin_mode == 2) {
+            // a launch's own geometry has up to twice as many buckets as there are compute units, and a
+            // counter for each in every chunk: room for those (some 100 KiB), unless it costs a slot that
+            // could be in use (two per router)
+            BinGeometry gs{};
+            uint32_t nb = g.nb;
+            for (uint32_t b = g.S; b-- > kMinLaunchBucketBits && nb < ctx->n_cu && bin_geometry_at(ctx, b, g.tile_pairs, &gs);)
+                nb = gs.nb;
+            const uint64_t aux_words = (2 * kListWords + (uint64_t)(kXcds + 2 * kMaxGroup) * nb + 3) / 4 * 4;
+            const uint64_t more = aux_words > ctx->aux_words ? (aux_words - ctx->aux_words) * 4 : 0;
+            if (more && slots_left(more) >= std::min<uint64_t>(slots_left(0), 2ull * S->cfg.n_routers))
+                st = ensure_aux(ctx, aux_words, nullptr);
+        }
         if (ctx->tune.bin_mode == 2) {
             // the region layout needs the most scratch: under a budget that would then hold no window
             // slot, the server keeps the exact-count layout
@@ -2446,6 +2475,7 @@ spd_status spd_server_create(const spd_params *p, const spd_server_config *cfg, 
                 st = reserve(1);
             }
         }
+        ctx->fixed_scratch = true;
         if (!st && ctx->tune.bin_mode) st = ensure_batch_ring(ctx, S->cfg.max_group_batches);
         if (st) {
             spd_server_destroy(S);
