@@ -328,10 +328,11 @@ struct CloseSlot {
 struct CloseTable {
     CloseSlot s[kMaxGroup];
 };
-// LDS words per wavefront: every SE may be hot, then the queue.
+// LDS words per wavefront: every SE may be hot, then the queue; and beside them its two static words.
 __host__ __device__ __forceinline__ uint32_t close_wave_words(uint32_t sea_bytes, uint32_t qcap) {
     return sea_bytes + qcap;
 }
+constexpr uint32_t kCloseStaticWords = 2;
 hipError_t launch_close(const Consts &c, const CloseArgs &a, int mode, uint32_t block, uint32_t grid, hipStream_t s);
 // The ends of n windows in one launch, grid workgroups each; a.counts holds kCloseCountBytes per window.
 hipError_t launch_close_many(const Consts &c, const CloseArgs &a, const CloseTable &t, uint32_t n, uint32_t block,

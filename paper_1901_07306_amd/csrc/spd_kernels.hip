@@ -2245,7 +2245,7 @@ __device__ __forceinline__ void close_window(const Consts &c, const CloseArgs &a
     extern __shared__ uint32_t lds[];
     constexpr uint32_t NW = BLOCK / 64;
     constexpr uint32_t U = MODE == kCloseBits ? 8 : 2;   // words in flight per lane
-    __shared__ uint32_t wave_q[NW], wave_cand[NW];
+    __shared__ uint32_t wave_q[NW], wave_cand[NW];   // kCloseStaticWords each
     const uint32_t sr = RMAX == 4 ? 4u : c.sr;
     const uint32_t lane = threadIdx.x & 63u, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t per_wave = close_wave_words(c.sea_bytes, a.qcap);

@@ -1285,10 +1285,15 @@ spd_status close_args(spd_ctx *ctx, const Slot &sl, const CloseBuf &cb, CloseArg
     a->qcap = 256;
     for (uint32_t i = 0; i < ctx->p.sr; ++i)
         a->lp_mask[i] = row_bits_in_lp((1u << ctx->d.ibn[i]) - 1u, ctx->d.isb[i], ctx->c.L);
-    const uint64_t per_wave = close_wave_words(ctx->c.sea_bytes, a->qcap);   // LDS words
+    const uint64_t per_wave = close_wave_words(ctx->c.sea_bytes, a->qcap);   // dynamic LDS words
+    uint32_t max_ibn = 0;
+    for (uint32_t i = 0; i < ctx->p.sr; ++i) max_ibn = std::max(max_ibn, ctx->d.ibn[i]);
+    // (rows of one size are what the limit is stated for: SR rows of the longest, and the queue)
+    if ((((uint64_t)ctx->p.sr << max_ibn) + a->qcap) * 4ull > kMaxLds)
+        return fail(ctx, SPD_E_INVALID, "SEA rows too large for the end-of-window kernel");
     uint32_t b = ctx->tune.close_block;
-    while (b > 64 && (b / 64) * per_wave * 4ull > kMaxLds) b /= 2;
-    if ((b / 64) * per_wave * 4ull > kMaxLds)
+    while (b > 64 && (b / 64) * (per_wave + kCloseStaticWords) * 4ull > kMaxLds) b /= 2;
+    if ((b / 64) * (per_wave + kCloseStaticWords) * 4ull > kMaxLds)
         return fail(ctx, SPD_E_INVALID, "SEA rows too large for the end-of-window kernel");
     const uint32_t waves = b / 64;
     *block = b;
