@@ -1299,7 +1299,7 @@ __device__ __forceinline__ bool seav_written(uint32_t *written, uint32_t b, cons
 // sampled pairs are gathered in LDS, so that the lanes share their bits evenly and nothing waits for
 // memory between them.  A heavy flow's pairs set the same bits over and over, and atomics on one address
 // follow each other device-wide: a bit that the table in LDS still holds is not set again (8 Mi pairs, 30 %
-// of them one flow: @B@).
+// of them one flow: 2.2 ms; with the atomics alone, in a launch of their own, 55).
 // The method constants are read from the kernel arguments (they are the first one) behind an opaque
 // pointer, so that nothing of this is loaded on the path of a launch that lists no tile.
 typedef __attribute__((address_space(4))) const Consts ArgConsts;
@@ -2270,12 +2270,18 @@ __device__ __forceinline__ void close_window(const Consts &c, const CloseArgs &a
         for (uint32_t k = 0; k < U; ++k)
             if (w0 + k * 64 < sea_words) raw[k] = load_sea<MODE>(a, sea + word_byte(w0 + k * 64 + lane));
     };
+    // the candidates of a round, one per lane, to the queue, which is filtered when it is full
     auto flush = [&]() {
         wave_lds_sync();
         filter_queue<MODE>(a, c, queue, qn, lane);
         n_cand += qn;
         qn = 0;
         wave_lds_sync();
+    };
+    auto push = [&](uint64_t bal, uint32_t h) {
+        if (bal >> lane & 1u) queue[qn + __popcll(bal & lane_lt)] = h;
+        qn += (uint32_t)__popcll(bal);
+        if (qn + 64 > a.qcap) flush();
     };
 
     uint32_t wi = blockIdx.x * NW + wid;
@@ -2350,16 +2356,111 @@ __device__ __forceinline__ void close_window(const Consts &c, const CloseArgs &a
         }
         if (prod == 0) continue;
         wave_lds_sync();
-        if (prod <= lmask) {
+        const bool each_lp = prod > lmask;
+        bool crowded = prod > 2048u;
+        if (crowded && prod <= 8192u && !each_lp) {   // (short rows: too few entries for a step of their own)
+            crowded = false;
+#pragma unroll
+            for (uint32_t i = 0; i < (uint32_t)RMAX; ++i) crowded = crowded || cnt[i] >= 16u;
+        }
+        if (crowded) {
+            // Crowded, in two steps.  The tuples of the other rows, one per lane: those whose own bits agree
+            // and whose SEs share enough bits (few: two overlaps of two bits alone leave one in 16) meet the
+            // longest row's entries, one per lane.  With as many tuples as hosts in this SEA, or more, every
+            // LP instead (the candidate definition), its SEs in LDS in place of the list: the upper bits of an
+            // LP decide the rows that take none of the lowest six, and the 64 LPs of those that pass are
+            // tested together.
+            // (One lane per whole tuple or LP: windows of 64 SEAs at theta = 64, 200,000 pairs, 2.69 ms, so
+            // 0.115; 256 SEAs at theta = 128, 1,000,000 pairs, 4.55 and 0.19.)
+            // (The constants of the rows come from the kernel arguments behind an opaque pointer: nothing of
+            // this is kept in registers by a launch without such an SEA.)
+            auto args = __builtin_amdgcn_kernarg_segment_ptr();
+            asm volatile("" : "+s"(args));
+            ArgConsts &rc = *(ArgConsts *)args;
+            auto *lp_mask = ((__attribute__((address_space(4))) const CloseArgs *)((ArgConsts *)args + 1))->lp_mask;
+            uint32_t cm = cnt[0], im = 0, bm = begin[0], mask = lp_mask[0], isbm = rc.isb[0], cover = 0, total = 1;
+#pragma unroll
+            for (uint32_t i = 1; i < (uint32_t)RMAX; ++i)
+                if (i < sr && cnt[i] > cm) cm = cnt[i], im = i, bm = begin[i], mask = lp_mask[i], isbm = rc.isb[i];
+            float rcp[RMAX];
+#pragma unroll
+            for (uint32_t i = 0; i < (uint32_t)RMAX; ++i) {
+                rcp[i] = __builtin_amdgcn_rcpf((float)cnt[i]);
+                if (i >= sr || i == im) continue;
+                total *= cnt[i];
+                cover |= lp_mask[i];
+            }
+            mask &= cover;   // the bits that the longest row shares with others
+            const bool small = total <= (1u << 20);
+            uint8_t *se = reinterpret_cast<uint8_t *>(list);
+            if (each_lp) {
+                total = (uint32_t)((lmask + 1) >> 6);
+                cm = 64;
+#pragma nounroll
+                for (uint32_t b = lane; b < c.sea_bytes; b += 64) se[b] = (uint8_t)load_se<MODE>(a, sea + b);
+                wave_lds_sync();
+            }
+            // (shares interleaved one by one: the other rows' tuples may be few)
+            for (uint64_t t0 = part; t0 < total; t0 += 64u * P) {
+                uint32_t lp = 0, seu = 0xFFu, differ = 0;
+                bool ok = t0 + (uint64_t)lane * P < total;
+                uint32_t u = ok ? (uint32_t)t0 + lane * P : 0u;
+                if (each_lp) {
+                    lp = u << 6;
+#pragma unroll
+                    for (uint32_t i = 0; i < (uint32_t)RMAX; ++i)
+                        if (i < sr && !(lp_mask[i] & 63u)) seu &= se[rc.row_off[i] + row_index(lp, rc.isb[i], rc.ibn[i], c.L)];
+                } else {
+                    uint32_t bits[RMAX];
+#pragma unroll
+                    for (uint32_t i = 0; i < (uint32_t)RMAX; ++i) {
+                        bits[i] = 0;
+                        if (i >= sr || i == im) continue;
+                        const uint32_t q = small ? (uint32_t)(((float)u + 0.5f) * rcp[i]) : u / cnt[i];
+                        const uint32_t e = list[begin[i] + u - q * cnt[i]];
+                        u = q;
+                        bits[i] = lp24 ? e >> 8 : row_bits_in_lp(e >> 8, rc.isb[i], c.L);
+                        seu &= e;
+                        lp |= bits[i];
+                    }
+#pragma unroll
+                    for (uint32_t i = 0; i < (uint32_t)RMAX; ++i)
+                        if (i < sr && i != im) differ |= (lp & lp_mask[i]) ^ bits[i];
+                }
+                ok = ok && __popc(seu) >= kSeHot && differ == 0;
+                for (uint64_t left = __ballot(ok); left; left &= left - 1) {
+                    const uint32_t l = (uint32_t)__builtin_ctzll(left);
+                    const uint32_t lp1 = __builtin_amdgcn_readlane(lp, l), seu1 = __builtin_amdgcn_readlane(seu, l);
+                    for (uint32_t e0 = 0; e0 < cm; e0 += 64) {
+                        uint32_t lp2 = lp1 | lane, seu2 = seu1;
+                        bool cand = true;
+                        if (each_lp) {
+#pragma unroll
+                            for (uint32_t i = 0; i < (uint32_t)RMAX; ++i)
+                                if (i < sr && (lp_mask[i] & 63u)) seu2 &= se[rc.row_off[i] + row_index(lp2, rc.isb[i], rc.ibn[i], c.L)];
+                        } else {
+                            cand = e0 + lane < cm;
+                            const uint32_t e = list[bm + (cand ? e0 + lane : e0)];
+                            const uint32_t b = lp24 ? e >> 8 : row_bits_in_lp(e >> 8, isbm, c.L);
+                            cand = cand && ((lp1 ^ b) & mask) == 0;
+                            seu2 &= e;
+                            lp2 = lp1 | b;
+                        }
+                        const uint64_t bal = __ballot(cand && __popc(seu2) >= kSeHot);
+                        if (bal) push(bal, (uint32_t)((uint64_t)lp2 << c.r | rp));
+                    }
+                }
+            }
+        } else {
             const uint32_t total = (uint32_t)prod;
             // the product CIS of the hot lists (Section 3.2), one tuple per lane: the tuple number's
             // mixed-radix digits (row 0 least significant) pick its entries.  A digit's quotient is
-            // exact in single precision below 2^20: (u + 1/2) / cnt is at least 1 / (2 cnt) from an
+            // exact in single precision (below 2^20): (u + 1/2) / cnt is at least 1 / (2 cnt) from an
             // integer, and the product's relative error is below 2^-22.  (Integer divisions took three
             // quarters of this kernel: 64 Mi pairs, 16384 SEAs of one tuple on average.)  Few tuples
             // are enumerated by every part, which keeps its share of the candidates: their filtering
             // is what takes time then.
-            const bool all = total <= 256u, small = total <= (1u << 20);
+            const bool all = total <= 256u;
             const uint32_t first = all ? 0u : part * 64u, stride = all ? 64u : 64u * P;
             float rcp[RMAX];
 #pragma unroll
@@ -2377,7 +2478,7 @@ __device__ __forceinline__ void close_window(const Consts &c, const CloseArgs &a
                         bits[i] = 0;
                         if (i >= sr) continue;
                         uint32_t q = 0;
-                        if (i + 1 < sr) q = small ? (uint32_t)(((float)u + 0.5f) * rcp[i]) : u / cnt[i];
+                        if (i + 1 < sr) q = (uint32_t)(((float)u + 0.5f) * rcp[i]);
                         const uint32_t e = list[begin[i] + u - q * cnt[i]];
                         u = q;
                         bits[i] = lp24 ? e >> 8 : row_bits_in_lp(e >> 8, c.isb[i], c.L);
@@ -2400,27 +2501,7 @@ __device__ __forceinline__ void close_window(const Consts &c, const CloseArgs &a
                     cand = cand && (j & part_mask) == part;
                     bal = __ballot(cand);
                 }
-                if (cand) queue[qn + __popcll(bal & lane_lt)] = h;
-                qn += (uint32_t)__popcll(bal);
-                if (qn + 64 > a.qcap) flush();
-            }
-        } else {
-            // as many tuples as hosts in this SEA, or more: test every LP directly (the candidate definition)
-            for (uint64_t l0 = (uint64_t)part * 64u; l0 <= lmask; l0 += 64u * P) {
-                const uint64_t l = l0 + lane;
-                bool cand = false;
-                if (l <= lmask) {
-                    uint32_t seu = 0xFFu;
-#pragma unroll
-                    for (uint32_t i = 0; i < (uint32_t)RMAX; ++i)
-                        if (i < sr)
-                            seu &= load_se<MODE>(a, sea + c.row_off[i] + row_index((uint32_t)l, c.isb[i], c.ibn[i], c.L));
-                    cand = __popc(seu) >= kSeHot;
-                }
-                const uint64_t bal = __ballot(cand);
-                if (cand) queue[qn + __popcll(bal & lane_lt)] = (uint32_t)((l << c.r) | rp);
-                qn += (uint32_t)__popcll(bal);
-                if (qn + 64 > a.qcap) flush();
+                push(bal, h);
             }
         }
     }
@@ -2478,14 +2559,20 @@ __device__ __forceinline__ void close_window(const Consts &c, const CloseArgs &a
     __hip_atomic_store(a.host_out + 2, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// Wavefronts per SIMD that the registers leave room for: with many small SEAs (2^20 of 64 bytes) the LDS
+// leaves eight, and one wavefront less costs a tenth.  (One more in the instances for any row count spills
+// to memory.)
+constexpr uint32_t close_waves(int mode, int rows) {
+    return rows != 4 ? (mode == kCloseStamps ? 4u : 6u) : mode == kCloseBits ? 7u : mode == kCloseAt ? 6u : 5u;
+}
 template <int MODE, int BLOCK, int RMAX>
-__global__ __launch_bounds__(BLOCK) void k_close(Consts c, CloseArgs a) { close_window<MODE, BLOCK, RMAX>(c, a); }
+__global__ __launch_bounds__(BLOCK, close_waves(MODE, RMAX)) void k_close(Consts c, CloseArgs a) { close_window<MODE, BLOCK, RMAX>(c, a); }
 
 // Several windows at once (the serving loop closes what a scan launch has completed): one window's close
 // waits for memory most of its time, so they run side by side, blockIdx.y naming the window.  16 windows
 // of 4 Mi pairs: 500 us one after another (13.5 us each, and the launches between them).
 template <int BLOCK, int RMAX>
-__global__ __launch_bounds__(BLOCK) void k_close_many(Consts c, CloseArgs a, CloseTable t) {
+__global__ __launch_bounds__(BLOCK, close_waves(kCloseBits, RMAX)) void k_close_many(Consts c, CloseArgs a, CloseTable t) {
     const CloseSlot s = t.s[blockIdx.y];
     a.seav = s.seav;
     a.ldca = s.ldca;
