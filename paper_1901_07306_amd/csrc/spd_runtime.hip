@@ -20,6 +20,8 @@ constexpr uint32_t kMaxLds = 160 * 1024;       // LDS per workgroup on gfx950
 constexpr uint32_t kMaxBucketBits = 20;        // 2^20 bits = 128 KiB bitmap per apply workgroup
 constexpr double kScratchUs = 50.0;            // the time of allocating the scratch of a small scan
 constexpr uint64_t kDirectMaxPairs = 1u << 18; // default of spd_tuning.direct_max_pairs
+constexpr double kRegionRoom = 2.0;            // a region's words: times the expected number of its items
+constexpr double kRegionRoomTight = 1.25;      // the same where a budget has no room for that
 constexpr uint32_t kMinLaunchBucketBits = 16;  // the smallest bucket a launch chooses by itself
 constexpr uint64_t kSeavAlign = 1ull << (kMaxBucketBits - 3);  // SEAV padded to whole buckets
 
@@ -116,6 +118,7 @@ struct spd_ctx {
     bool fixed_scratch = false;      // serving loop: the scratch is reserved at creation; a launch's own geometry
                                      // and the binning of small scans have to do with it
     bool limit_set = false;          // spd_set_tuning was called: direct_max_pairs is the caller's
+    double region_room = kRegionRoom;   // of the launch being laid out
     uint32_t list_parity = 0;        // region layout: which of two sets of tile-list counts the next launch uses
     CloseBuf cbuf;                  // end-of-window buffers of spd_close_window
     uint64_t *close_counts = nullptr;   // finished workgroups of the running close (a context's launches
@@ -603,11 +606,11 @@ void scratch_need(const BinGeometry &g, uint32_t bin_mode, uint64_t tiles, uint6
 }
 
 // Region layout: 64-bit words per (chunk, bucket) region of a chunk of t tiles whose bucket expects
-// E items: 2 E (a bucket that holds a heavy host gets far more than its share) plus eight standard
+// E items: `room` E (a bucket that holds a heavy host gets far more than its share) plus eight standard
 // deviations of a binomial count, the padding of t tiles (at most two items each) and a margin, three
 // items per word.  Room past the fill costs memory, not traffic.
-static uint32_t region_capw(double E, double t) {
-    return (uint32_t)std::ceil((2.0 * E + 8.0 * std::sqrt(E) + 2.0 * t + 64.0) / 3.0);
+static uint32_t region_capw(double room, double E, double t) {
+    return (uint32_t)std::ceil((room * E + 8.0 * std::sqrt(E) + 2.0 * t + 64.0) / 3.0);
 }
 
 // Expected items per tile of one LDCA bucket and of one SEAV bucket.
@@ -619,7 +622,7 @@ static void region_load(const spd_ctx *ctx, const BinGeometry &g, double *el, do
 }
 
 static uint32_t region_cap(const spd_ctx *ctx, double e_tile, double t) {
-    return ctx->tune.region_words ? ctx->tune.region_words : region_capw(e_tile * t, t);
+    return ctx->tune.region_words ? ctx->tune.region_words : region_capw(ctx->region_room, e_tile * t, t);
 }
 
 // 32-bit words per tile of a region launch beside the regions: every word of the tile's stage has a
@@ -688,7 +691,7 @@ void region_bound(const spd_ctx *ctx, const BinGeometry &g, uint64_t tiles, uint
     if (ctx->tune.region_words) {
         words = n * (nbl + nbs) * ctx->tune.region_words;
     } else {
-        const double A = (nbl * (2.0 * el + 2.0) + nbs * (2.0 * es + 2.0)) / 3.0;
+        const double A = (nbl * (kRegionRoom * el + 2.0) + nbs * (kRegionRoom * es + 2.0)) / 3.0;
         const double B = 8.0 * (nbl * std::sqrt(el) + nbs * std::sqrt(es)) / 3.0;
         const double C = (nbl + nbs) * (64.0 / 3.0 + 1.0);
         words = A * (double)tiles + B * std::sqrt(n * (double)tiles) + n * C;
@@ -970,6 +973,7 @@ spd_status scan_work(spd_ctx *ctx, std::vector<WorkItem> &ws, hipStream_t s) {
     // a region launch that covers the whole call has a geometry of its own
     const BinGeometry g0 = g;
     bool own = false;
+    ctx->region_room = kRegionRoom;
     if (ctx->tune.bin_mode == 2 && !lp && slots.size() <= (size_t)kMaxGroup) {
         std::vector<uint64_t> n;
         uint64_t tiles = 0;
@@ -1073,7 +1077,12 @@ spd_status scan_work(spd_ctx *ctx, std::vector<WorkItem> &ws, hipStream_t s) {
                 spd_status st = region_launch(ctx, g, bd, tiles, ct, as, nsl, s);
                 ctx->merge_group = false;
                 if (st && st != SPD_E_NOMEM) return st;
-                if (st && own) {   // (nothing was enqueued) the tuning's geometry may need less
+                if (st && ctx->region_room > kRegionRoomTight) {   // (nothing was enqueued)
+                    ctx->region_room = kRegionRoomTight;
+                    i0 = group_start;
+                    continue;
+                }
+                if (st && own) {   // the tuning's geometry may need less
                     own = false;
                     g = g0;
                     i0 = group_start;
@@ -1172,6 +1181,7 @@ spd_status scan_noalloc(spd_ctx *ctx, Slot *sl, const uint32_t *pairs, uint64_t 
         return (cw * 4 + 255) / 256 * 256 + iw * 4 <= cap;
     };
     // the launch's own geometry, when the array takes it
+    ctx->region_room = kRegionRoom;
     const BinGeometry g0 = g;
     region_geometry(ctx, g0, {n}, 1, &g);
     if (!fits((uint32_t)std::min<uint64_t>((n + g.tile_pairs - 1) / g.tile_pairs, 1u << 20))) g = g0;

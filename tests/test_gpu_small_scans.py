@@ -147,3 +147,26 @@ def test_budgets_of_a_large_scan():
             assert det.stats.device_bytes <= budget
         finally:
             det.close()
+
+
+def test_budget_below_the_wanted_regions():
+    """A budget that holds the region layout only with less room in its regions: still that layout (no
+    counting pass), with the same sketches."""
+    rng = np.random.default_rng(88)
+    pairs = random_pairs(rng, 4_000_001, n_hosts=60_000)
+    x = to_dev(pairs)
+    ref = oracle_sketch(MP, pairs)
+    base, high = held_after(lambda det: det.scan(0, x))
+    det = detector(budget=base + int(0.93 * (high - base)))
+    try:
+        log("case regions with less room")
+        for k in range(2):
+            det.profile_enable(True)
+            det.scan(0, x)
+            prof = det.profile()
+            det.profile_enable(False)
+            assert prof["count"][0] == 0 and prof["bin"][0] == 1
+            assert_same_sketch(det, 0, ref, f"window {k}")
+            det.reset(0)
+    finally:
+        det.close()
