@@ -700,6 +700,23 @@ void region_bound(const spd_ctx *ctx, const BinGeometry &g, uint64_t tiles, uint
     *cur_words = (2 * kListWords + (uint64_t)(kXcds + 2 * kMaxGroup) * g.nb + 3) / 4 * 4;
 }
 
+// Bytes that the serving loop weighs the region layout with (see spd_server_create).
+uint64_t region_reserve(const spd_ctx *ctx, const BinGeometry &g, uint64_t tiles) {
+    double el, es;
+    region_load(ctx, g, &el, &es);
+    const double nbl = g.nb_ldca, nbs = g.nb - g.nb_ldca, t = kChunk, R = (double)std::min<uint64_t>(tiles, kMaxGroup * (kChunk - 1ull));
+    double words;
+    if (ctx->tune.region_words) {
+        words = ((double)tiles + kMaxGroup) * (nbl + nbs) * ctx->tune.region_words;
+    } else {
+        const double full = nbl * region_capw(kRegionRoomTight, el * t, t) + nbs * region_capw(kRegionRoomTight, es * t, t);
+        words = (double)(tiles / kChunk) * full + (nbl * (kRegionRoomTight * el + 2.0) + nbs * (kRegionRoomTight * es + 2.0)) / 3.0 * R +
+                8.0 * (nbl * std::sqrt(el) + nbs * std::sqrt(es)) / 3.0 * std::sqrt(kMaxGroup * R) + kMaxGroup * (nbl + nbs) * (64.0 / 3.0 + 1.0);
+    }
+    return ((uint64_t)std::ceil(words) * 2 + std::min<uint64_t>(tiles * g.cap / 3, 0xFFFFFFFFull) * 3 + tiles +
+            4 + (tiles / kChunk + kMaxGroup) * g.nb) * 4;
+}
+
 void free_scratch(spd_ctx *ctx) {
     dev_free(ctx, &ctx->items, ctx->items_words * 4);
     dev_free(ctx, &ctx->meta, ctx->meta_words * 4);
@@ -2459,36 +2476,43 @@ spd_status spd_server_create(const spd_params *p, const spd_server_config *cfg, 
             if (!r && mode) r = ensure_aux(ctx, aux_words, nullptr);
             return r;
         };
-        // Slots that the rest of the budget holds.
-        auto slots_left = [&](uint64_t more) {
-            const uint64_t used = ctx->held + more, one = ctx->slot_bytes + (uint64_t)kRecInit * 8 + 64;
-            const uint64_t n = ctx->budget > used ? (ctx->budget - used) / one : 0;
+        // Window slots that the budget holds with `more` bytes held than are now.
+        auto slots_left = [&](int64_t more) -> uint64_t {
+            const int64_t room = (int64_t)(ctx->budget - ctx->held) - more;   // (the budget is never passed)
+            const uint64_t n = room > 0 ? (uint64_t)room / (ctx->slot_bytes + (uint64_t)kRecInit * 8 + 64) : 0;
             return S->cfg.max_slots ? std::min<uint64_t>(n, S->cfg.max_slots) : n;
         };
+        const uint64_t in_use = 2ull * S->cfg.n_routers;   // slots that could be in use: open, and being closed
         st = reserve(ctx->tune.bin_mode);
+        if (ctx->tune.bin_mode == 2) {
+            // The region layout needs the most scratch: under a budget that holds too few window slots
+            // beside it, the server keeps the exact-count layout.  Too few is none beside a reserve that
+            // counts chunks of kChunk tiles and three words of spill for each of a tile's, unless no slot
+            // that could be in use is lost.
+            const uint64_t scratch = (ctx->items_words + ctx->aux_words) * 4;
+            uint64_t other, meta;
+            scratch_need(g, 1, tiles, &other, &meta);
+            other = (other + 3 * meta + (uint64_t)kMaxGroup * g.nb + 1 + (tiles / kChunk + kMaxGroup) * g.nb) * 4;
+            const uint64_t judged = std::max(scratch, region_reserve(ctx, g, tiles)), slots = slots_left(0);
+            const bool room = slots_left((int64_t)(judged - scratch)) > 0 ||
+                              (slots > 0 && slots >= std::min(slots_left((int64_t)other - (int64_t)scratch), in_use));
+            if (st == SPD_E_NOMEM || (!st && !room)) {
+                free_scratch(ctx);
+                ctx->tune.bin_mode = 1;
+                st = reserve(1);
+            }
+        }
         if (!st && ctx->tune.bin_mode == 2) {
             // a launch's own geometry has up to twice as many buckets as there are compute units, and a
             // counter for each in every chunk: room for those (some 100 KiB), unless it costs a slot that
-            // could be in use (two per router)
+            // could be in use
             BinGeometry gs{};
             uint32_t nb = g.nb;
             for (uint32_t b = g.S; b-- > kMinLaunchBucketBits && nb < ctx->n_cu && bin_geometry_at(ctx, b, g.tile_pairs, &gs);)
                 nb = gs.nb;
             const uint64_t aux_words = (2 * kListWords + (uint64_t)(kXcds + 2 * kMaxGroup) * nb + 3) / 4 * 4;
             const uint64_t more = aux_words > ctx->aux_words ? (aux_words - ctx->aux_words) * 4 : 0;
-            if (more && slots_left(more) >= std::min<uint64_t>(slots_left(0), 2ull * S->cfg.n_routers))
-                st = ensure_aux(ctx, aux_words, nullptr);
-        }
-        if (ctx->tune.bin_mode == 2) {
-            // the region layout needs the most scratch: under a budget that would then hold no window
-            // slot, the server keeps the exact-count layout
-            const uint64_t one_slot = ctx->slot_bytes + (uint64_t)kRecInit * 8 + 64;
-            const bool room = ctx->held + one_slot <= ctx->budget;
-            if (st == SPD_E_NOMEM || (!st && !room)) {
-                free_scratch(ctx);
-                ctx->tune.bin_mode = 1;
-                st = reserve(1);
-            }
+            if (more && slots_left((int64_t)more) >= std::min(slots_left(0), in_use)) st = ensure_aux(ctx, aux_words, nullptr);
         }
         ctx->fixed_scratch = true;
         if (!st && ctx->tune.bin_mode) st = ensure_batch_ring(ctx, S->cfg.max_group_batches);

@@ -170,3 +170,14 @@ def test_budget_below_the_wanted_regions():
             det.reset(0)
     finally:
         det.close()
+
+
+@pytest.mark.parametrize("budget_mib,group,at_least", [(512, 16 << 20, 81), (256, 1 << 20, 11), (1536, 64 << 20, 44)])
+def test_server_slots_under_a_budget(budget_mib, group, at_least):
+    """A tight budget keeps the slots it has always held for routers that could use them all."""
+    srv = spd.Server(spd.params_from(MP), 4_000, hbm_budget_bytes=budget_mib << 20, max_group_pairs=group)
+    try:
+        log(f"case server slots: {budget_mib} MiB, groups of {group} pairs: {srv.stats['slots']}")
+        assert srv.stats["slots"] >= at_least
+    finally:
+        srv.close()
