@@ -12,8 +12,8 @@
 //              fixed-capacity (chunk of tiles, bucket) regions, read by k_apply_rg (the default,
 //              one pass over the pairs); k_count + k_place write one exact bucket-major stream,
 //              read by k_apply_bm; k_bin writes per-tile regions, gathered by k_apply.
-// End of window (Sections 3.2-3.3): k_close gives one wavefront per SEA (one RP): hot-SE lists
-// by ballot, the candidate product with Eq. 3 consistency and the SEU weight test, then the
+// End of window (Sections 3.2-3.3): k_close gives one wavefront per SEA (one RP) or part of one: hot-SE
+// lists by ballot, the candidate product with Eq. 3 consistency and the SEU weight test, then the
 // ULDC of each candidate (AND over LR rows, popcount by wavefront reduction).
 #include <hip/hip_ext.h>
 
@@ -1210,8 +1210,8 @@ __device__ __forceinline__ void apply_word(uint32_t *bm, uint64_t v) {
 // What does not fit a region is ordered by bucket too, and applied in LDS like the rest.  It was once
 // appended word by word to one list (one counter: its atomics are serialized device-wide) and recorded
 // with global atomics by a kernel of its own: 8 Mi pairs, half of them from four hosts, took 606 us of
-// binning + 1930 us of that kernel, now 47 + 105 us of binning and apply; 5 Mi pairs with 60 planted
-// hosts 84 + 36 us, now 31 us; and without such words the kernel's launch is saved (4 us).
+// binning + 1930 us of that kernel, now 47 + 101 us of binning and apply; 5 Mi pairs with 60 planted
+// hosts 84 + 36 us, now 28 us; and without such words the kernel's launch is saved (4 us).
 //
 // The listed segments of one (slot, bucket): each wavefront takes 64 at a time (one descriptor per
 // lane) and reads the first 64 words of eight segments before it waits, since most segments are
@@ -2538,7 +2538,9 @@ __device__ __forceinline__ void close_window(const Consts &c, const CloseArgs &a
     }
     // Every wavefront's records have been written through to host memory before its workgroup counts
     // itself finished, so no cache has to be written back (a release per workgroup cost 11 us over
-    // 1280 of them); the last workgroup publishes the counts and, last of all, the close's sequence
+    // 1280 of them).  That rests on the hardware, not on the memory model: system-scope stores to coherent
+    // host memory are write-through on this chip, and the counter waited for falls when they are
+    // acknowledged.  The last workgroup publishes the counts and, last of all, the close's sequence
     // number, which the host may poll instead of waiting for the stream.
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();

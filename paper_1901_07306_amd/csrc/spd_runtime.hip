@@ -513,7 +513,8 @@ bool bin_geometry(const spd_ctx *ctx, BinGeometry *g) {
 //    7.3 with 264).
 //  * Tiles: two workgroups of the binning kernel share a compute unit when their LDS fits, so tiles
 //    run in rounds of two per compute unit; of the tile sizes that fit twice (else of those that fit
-//    once), the one with the least rounds times a tile's time is taken.  A tile of 1024 p pairs takes
+//    once; their registers do then too: at most 58 vector registers where p LR < 20), the one with the
+//    least rounds times a tile's time is taken.  A tile of 1024 p pairs takes
 //    about 2.8 + 1.31 p us in a full round (64 Mi pairs: 13.3 us at p = 8, 8.1 at p = 4).  With 1152
 //    buckets 8192 pairs do not fit twice: 8 x 16 Mi pairs 691 us, with p = 7 493 us.
 void region_geometry(const spd_ctx *ctx, const BinGeometry &g0, const std::vector<uint64_t> &n, uint32_t n_slots,
@@ -1180,7 +1181,7 @@ spd_status scan_noalloc(spd_ctx *ctx, Slot *sl, const uint32_t *pairs, uint64_t 
         ctx->stats.pairs_scanned += n;
         return SPD_OK;
     }
-    // the most tiles per launch whose region layout (items, spill list, counters) fits the array;
+    // the most tiles per launch whose region layout (items, spill array, lists, counters) fits the array;
     // the layout grows with the tile count, so a binary search finds it
     const uint64_t cap = SPD_NOALLOC_SCRATCH_BYTES;
     auto layout_of = [&](uint32_t tiles, ChunkTable *ct, uint64_t *iw, uint64_t *cw) {
@@ -1217,7 +1218,7 @@ spd_status scan_noalloc(spd_ctx *ctx, Slot *sl, const uint32_t *pairs, uint64_t 
     layout_of(tmax, &ct, &iw, &cw);
     const uint64_t aux_bytes = (cw * 4 + 255) / 256 * 256;
     // counters first (cleared by the first launch of this call: the array keeps the last call's
-    // contents), then the regions and the spill list
+    // contents), then the regions, the spill array and the lists
     bool aux_zero = false;
     uint32_t parity = 0;
     const RegionScratch rs{reinterpret_cast<uint32_t *>(ctx->noalloc + aux_bytes), (cap - aux_bytes) / 4,
