@@ -115,6 +115,9 @@ struct spd_ctx {
     uint32_t close_per_cu[3] = {0, 0, 0};   // resident end-of-window workgroups per CU (64, 128, 256 lanes)
     double small_gain = 0.0;         // what small scans without scratch would have saved with it (us)
     bool small_scratch = false;      // the scratch was grown for a small scan, which can do without
+    bool scanning = false;           // a scan is being enqueued: its scratch stays where it is
+    bool recorded = false;           // a graph holds a launch that uses the scratch: never given back or
+                                     // grown for a small scan
     bool fixed_scratch = false;      // serving loop: the scratch is reserved at creation; a launch's own geometry
                                      // and the binning of small scans have to do with it
     bool limit_set = false;          // spd_set_tuning was called: direct_max_pairs is the caller's
@@ -380,9 +383,9 @@ void prof_harvest(spd_ctx *ctx) {
 
 void free_scratch(spd_ctx *ctx);
 
-// Small scans can do without their scratch: it makes room for what is needed.
+// Small scans can do without their scratch: it makes room for what is needed (outside a scan).
 bool give_back_small_scratch(spd_ctx *ctx) {
-    if (!ctx->small_scratch) return false;
+    if (!ctx->small_scratch || ctx->scanning || ctx->recorded) return false;
     (void)hipDeviceSynchronize();
     free_scratch(ctx);
     return true;
@@ -568,7 +571,11 @@ spd_status ensure_batch_ring(spd_ctx *ctx, size_t n) {
         for (uint32_t k = 0; k < kBdRing; ++k) {
             SPD_HIP(ctx, hipHostMalloc((void **)&ctx->bd_host[k], cap * sizeof(BatchDesc), hipHostMallocDefault));
             spd_status st = dev_alloc(ctx, &ctx->bd_dev[k], (uint64_t)cap * sizeof(BatchDesc));
-            if (st) return st;
+            if (st) {
+                ctx->bd_cap = cap;   // (what was allocated is given back)
+                free_batch_ring(ctx);
+                return st;
+            }
         }
         ctx->bd_cap = cap;
     }
@@ -843,6 +850,7 @@ spd_status region_launch_at(spd_ctx *ctx, const BinGeometry &g, const BatchDesc 
     }
     if (fuse) ctx->merged = true;
     if (recorded) {
+        if (rs.aux == ctx->aux) ctx->recorded = true;
         SPD_HIP(ctx, launch_fill_u32(rs.aux, 2 * kListWords, 0u, s));   // this launch's tile-list counts
         return SPD_OK;
     }
@@ -859,19 +867,34 @@ bool region_ready(const spd_ctx *ctx, const BinGeometry &g, const ChunkTable &ct
     return items_words <= ctx->items_words && cur_words <= ctx->aux_words;
 }
 
-// The context's scratch grown for a group, within the HBM budget: SPD_E_NOMEM if it does not fit.
+// The context's scratch grown (32-bit words), within the HBM budget: SPD_E_NOMEM if it does not fit, and the
+// scratch at hand, which may serve another geometry, is then still there where that can be told beforehand.
+spd_status grow_scratch(spd_ctx *ctx, uint64_t items_words, uint64_t meta_words, uint64_t aux_words, hipStream_t s) {
+    if (items_words <= ctx->items_words && meta_words <= ctx->meta_words && aux_words <= ctx->aux_words) return SPD_OK;
+    if (ctx->small_scratch && !ctx->recorded) {   // made anew: nothing is held that a small scan alone needed
+        const uint64_t have = (ctx->items_words + 3 * ctx->meta_words + ctx->aux_words) * 4;
+        const uint64_t need = (items_words + 3 * meta_words + aux_words) * 4;
+        if (ctx->budget && ctx->held - have + need > ctx->budget)
+            return fail(ctx, SPD_E_NOMEM, "HBM budget exceeded: scratch of " + std::to_string(need) + " bytes");
+        SPD_HIP(ctx, hipStreamSynchronize(s));
+        free_scratch(ctx);
+    } else {
+        const uint64_t more = (items_words > ctx->items_words ? (items_words - ctx->items_words) * 4 : 0) +
+                              (aux_words > ctx->aux_words ? (aux_words - ctx->aux_words) * 4 : 0);
+        spd_status st = more ? reserve(ctx, more) : SPD_OK;
+        if (st) return st;
+    }
+    spd_status st = ensure_scratch(ctx, items_words, meta_words, s);
+    if (!st) st = ensure_aux(ctx, aux_words, s);
+    return st;
+}
+
 spd_status region_room(spd_ctx *ctx, const BinGeometry &g, const ChunkTable &ct, uint32_t tiles, hipStream_t s) {
     RegionArgs ra{};
     uint64_t items_words = 0, cur_words = 0;
     region_layout(ctx, g, ct, tiles, &ra, &items_words, &cur_words);
     if (ra.chunk_words >= (1ull << 31)) return fail(ctx, SPD_E_INVALID, "region layout: chunk too large");
-    // (refused before anything is given back: the scratch at hand may serve another geometry)
-    const uint64_t more = (items_words > ctx->items_words ? (items_words - ctx->items_words) * 4 : 0) +
-                          (cur_words > ctx->aux_words ? (cur_words - ctx->aux_words) * 4 : 0);
-    spd_status st = more ? reserve(ctx, more) : SPD_OK;
-    if (!st) st = ensure_scratch(ctx, items_words, 0, s);
-    if (!st) st = ensure_aux(ctx, cur_words, s);
-    return st;
+    return grow_scratch(ctx, items_words, 0, cur_words, s);
 }
 
 // A group in the context's scratch, grown on demand: SPD_E_NOMEM (nothing enqueued) if it does not fit
@@ -902,6 +925,11 @@ double binned_gain_us(const spd_ctx *ctx, uint64_t total, const std::vector<Slot
 // Record batches into slots.  Batches of one slot are kept together so that each slot's tiles are
 // one contiguous range of the binned launch.
 spd_status scan_work(spd_ctx *ctx, std::vector<WorkItem> &ws, hipStream_t s) {
+    struct Scanning {
+        spd_ctx *ctx;
+        explicit Scanning(spd_ctx *c) : ctx(c) { ctx->scanning = true; }
+        ~Scanning() { ctx->scanning = false; }
+    } scanning(ctx);
     std::stable_sort(ws.begin(), ws.end(), [](const WorkItem &x, const WorkItem &y) {
         return std::less<Slot *>()(x.slot, y.slot);
     });
@@ -1044,7 +1072,7 @@ spd_status scan_work(spd_ctx *ctx, std::vector<WorkItem> &ws, hipStream_t s) {
         uint64_t items_words, meta_words;
         scratch_need(g, ctx->tune.bin_mode, tiles, &items_words, &meta_words);
         if (ctx->tune.bin_mode == 0) {
-            spd_status st = ensure_scratch(ctx, items_words, meta_words, s);
+            spd_status st = grow_scratch(ctx, items_words, meta_words, 0, s);
             if (st) return st;
             for (uint32_t k = 0; k < nsl; ++k)   // SEAV bits may be recorded directly by the binning
                 if (as[k].fresh) {
@@ -1078,17 +1106,18 @@ spd_status scan_work(spd_ctx *ctx, std::vector<WorkItem> &ws, hipStream_t s) {
                     i0 = group_start;
                     continue;
                 }
-                if (ctx->fixed_scratch && !ready && small) return direct_scan();
+                if ((ctx->fixed_scratch || ctx->recorded) && !ready && small) return direct_scan();
+                // (nor is the descriptor ring allocated for a small scan of many batches)
+                if (small && nbd > kInlineBatches && nbd > ctx->bd_cap) return direct_scan();
                 if (small && !ready) {
                     // the direct kernel needs no scratch: a small scan has it grown (about 50 us) once
                     // scans like it would have saved that much, and stays direct if that is refused
                     ctx->small_gain += gain;
                     if (ctx->small_gain < kScratchUs) return direct_scan();
                     ctx->small_gain = 0.0;
-                    const bool was = ctx->small_scratch;
-                    ctx->small_scratch = false;   // (not to be given back for its own growth)
+                    const bool spare = ctx->small_scratch;
                     const spd_status grown = region_room(ctx, g, ct, tiles, s);
-                    ctx->small_scratch = was || !grown;
+                    ctx->small_scratch = spare || !grown;
                     if (grown) return direct_scan();
                 }
                 ctx->merge_group = ctx->merge_into && group_start == 0 && i0 == ws.size();
@@ -1114,8 +1143,7 @@ spd_status scan_work(spd_ctx *ctx, std::vector<WorkItem> &ws, hipStream_t s) {
             }
             chunk_table(&ct, as, nsl, kChunk);
             const uint32_t chunks = ct.cbase[nsl];
-            spd_status st = ensure_scratch(ctx, items_words, meta_words, s);
-            if (!st) st = ensure_aux(ctx, (uint64_t)nsl * g.nb + 1 + (uint64_t)chunks * g.nb, s);
+            spd_status st = grow_scratch(ctx, items_words, meta_words, (uint64_t)nsl * g.nb + 1 + (uint64_t)chunks * g.nb, s);
             if (st) return st;
             uint32_t *base = ctx->aux, *cstart = ctx->aux + nsl * g.nb + 1;
             ctx->aux_zero = false;

@@ -74,3 +74,40 @@ def test_replayed_scan(small, warm):
     finally:
         s.synchronize()
         det.close()
+
+
+def test_recorded_scratch_stays():
+    """A graph holds a large scan; small scans of another geometry follow, which would have grown the
+    scratch that the graph uses: they stay direct, and the replays are right."""
+    mp = st.CONFIGS["plain_1m"].params.replace(r=12, log2lc=14)   # 17 MiB
+    rng = np.random.default_rng(71)
+    det = spd.Detector(spd.params_from(mp))
+    s = torch.cuda.Stream()
+    try:
+        with torch.cuda.stream(s):
+            pairs = random_pairs(rng, 300_001, n_hosts=10_000)
+            x = to_dev(pairs)
+            det.scan(0, x)
+            det.reset(0)
+            first = random_pairs(rng, 50)
+            det.scan(0, to_dev(first))
+            s.synchronize()
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g, stream=s, capture_error_mode="thread_local"):
+                det.scan(0, x)
+            held = det.stats.device_bytes
+            seen = [first]
+            for k in range(12):
+                log(f"case recorded scratch, pass {k}")
+                g.replay()
+                small = random_pairs(rng, 250_001, n_hosts=8_000)
+                det.scan(0, to_dev(small))
+                seen += [pairs, small]
+                s.synchronize()
+                assert_same_sketch(det, 0, oracle_sketch(mp, np.concatenate(seen)), f"pass {k}")
+                pairs = random_pairs(rng, 300_001, n_hosts=10_000)
+                x.copy_(to_dev(pairs))
+            assert det.stats.device_bytes == held
+    finally:
+        s.synchronize()
+        det.close()

@@ -181,3 +181,31 @@ def test_server_slots_under_a_budget(budget_mib, group, at_least):
         assert srv.stats["slots"] >= at_least
     finally:
         srv.close()
+
+
+@pytest.mark.parametrize("room", [4_096, 40_000, 400_000])
+def test_many_batches_and_later_allocations(room):
+    """Small scans of one and of twenty batches in turn, then a large scan, under a budget that holds the
+    scratch of the small ones and a little more: nothing is refused that a direct scan would take, and no
+    allocation of a call takes the scratch away from under it."""
+    rng = np.random.default_rng(89)
+    base, after = held_after(lambda det: windows(det, 90, count=12))
+    big = random_pairs(rng, 700_001, n_hosts=20_000)
+    _, low = held_after(lambda det: (set_tuning(det, bin_mode=1, direct_max_pairs=0), det.scan_batches(
+        [(0, q) for q in to_dev(big).split(40_000)])))
+    det = detector(budget=max(after + room, low + room), n_routers=1)
+    try:
+        log(f"case small scans of many batches, {room} bytes beside their scratch")
+        for k in range(14):
+            pairs = random_pairs(rng, N, n_hosts=N // 30)
+            x = to_dev(pairs)
+            det.scan_batches([(0, q) for q in x.split(N if k % 2 else N // 20)])
+            assert_same_sketch(det, 0, oracle_sketch(MP, pairs), f"window {k}")
+            det.reset(0)
+        for k in range(2):
+            det.scan_batches([(0, q) for q in to_dev(big).split(40_000)])
+            assert_same_sketch(det, 0, oracle_sketch(MP, big), f"large window {k}")
+            det.reset(0)
+            windows(det, 91 + k, count=2)
+    finally:
+        det.close()
